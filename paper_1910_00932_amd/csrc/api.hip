@@ -39,13 +39,30 @@ static int make_convp(const tsm_conv_desc* d, ConvP* p, const char* who) {
 
 static inline bool use_mfma(const ConvP& p, int dtype) { return dtype == TSM_BF16 && mfma_conv_supported(p); }
 
-// ---- internal conv runners (channels-innermost) -----------------------------------------
-// Rows of the statistics partial buffer run_conv_fwd fills for this convolution.
-int conv_stats_blocks(const ConvP& p, int dtype) {
-    return use_mfma(p, dtype) ? conv_mfma_fwd_blocks(p) : red_blocks(p.rows_out(), p.Cout, dtype);
+// The general implicit-GEMM kernels take the rest, up to the few shapes only the plain kernels know.
+static inline bool use_gen(const ConvP& p, int dtype, const Arena& ws) {
+    return !use_mfma(p, dtype) && !ws.lean && gen_conv_supported(p);
 }
 
-// stats_partial: fp32 [conv_stats_blocks(p, dtype)][2*Cout] or null.
+// ---- internal conv runners (channels-innermost) -----------------------------------------
+// Rows of the statistics partial buffer run_conv_fwd fills for this convolution.
+int conv_stats_blocks(const ConvP& p, int dtype, const Arena& ws) {
+    if (use_mfma(p, dtype)) return conv_mfma_fwd_blocks(p);
+    return use_gen(p, dtype, ws) ? gen_fwd_blocks(p) : red_blocks(p.rows_out(), p.Cout, dtype);
+}
+
+// Weights in the order a general kernel reads: packed into the workspace, or the caller's own where they are in it.
+static int gen_weights(const ConvP& p, int dtype, bool dgrad, const void* w, const void** wp, Arena& ws, bool dry, hipStream_t s) {
+    const size_t n = gen_pack_elems(p, dtype, dgrad);
+    *wp = w;
+    if (n == 0) return TSM_OK;
+    void* pk = ws.take(n * dtype_size(dtype));
+    RUN(gen_pack_weights(p, dtype, dgrad, w, pk, s));
+    *wp = pk;
+    return TSM_OK;
+}
+
+// stats_partial: fp32 [conv_stats_blocks(p, dtype, ws)][2*Cout] or null.
 int run_conv_fwd(const ConvP& p, int dtype, const void* x, const void* w, const bf16_t* wp, void* y,
                  float* stats_partial, Arena& ws, bool dry, hipStream_t s) {
     if (use_mfma(p, dtype)) {
@@ -55,6 +72,10 @@ int run_conv_fwd(const ConvP& p, int dtype, const void* x, const void* w, const 
             wp = pk;
         }
         RUN(conv_mfma_fwd(p, (const bf16_t*)x, wp, (bf16_t*)y, stats_partial, nullptr, s));
+    } else if (use_gen(p, dtype, ws)) {
+        const void* gw;
+        TSM_TRY(gen_weights(p, dtype, false, w, &gw, ws, dry, s));
+        RUN(gen_conv_fwd(p, dtype, x, gw, y, stats_partial, s));
     } else {
         RUN(conv_direct_fwd(p, dtype, x, w, y, s));
         if (stats_partial) RUN(channel_stats(dtype, y, p.rows_out(), p.Cout, stats_partial, s));
@@ -75,6 +96,10 @@ int run_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* w, con
             wd = pk;
         }
         RUN(conv_mfma_dgrad(p, (const bf16_t*)dy, wd, (bf16_t*)dx, (const bf16_t*)addend, fuse, s, addend_stride));
+    } else if (use_gen(p, dtype, ws)) {
+        const void* gw;
+        TSM_TRY(gen_weights(p, dtype, true, w, &gw, ws, dry, s));
+        RUN(gen_conv_dgrad(p, dtype, dy, gw, dx, addend, s));
     } else {
         RUN(conv_direct_dgrad(p, dtype, dy, w, dx, addend, s));
     }
@@ -90,17 +115,23 @@ int run_conv_wgrad(const ConvP& p, int dtype, const void* x, const void* dy, flo
         RUN(conv_mfma_wgrad(p, (const bf16_t*)x, (const bf16_t*)dy, dwp_zeroed, p.Cin, true, s));
         return TSM_OK;
     }
-    if (use_mfma(p, dtype) && p.taps() > 1) {
+    const bool gen = use_gen(p, dtype, ws);
+    if ((gen || use_mfma(p, dtype)) && p.taps() > 1) {
         // several taps: accumulate in the packed order (contiguous atomics), then permute into dw
         float* dwp = ws.take_n<float>(n);
         RUN(fill_zero(dwp, n * sizeof(float), s));
-        RUN(conv_mfma_wgrad(p, (const bf16_t*)x, (const bf16_t*)dy, dwp, p.Cin, true, s));
+        if (gen)
+            RUN(gen_conv_wgrad(p, dtype, x, dy, dwp, true, s));
+        else
+            RUN(conv_mfma_wgrad(p, (const bf16_t*)x, (const bf16_t*)dy, dwp, p.Cin, true, s));
         RUN(unpack_wgrad(dwp, dw, p.Cout, p.Cin, p.taps(), p.Cin, accumulate, s));
         return TSM_OK;
     }
     if (!accumulate) RUN(fill_zero(dw, n * sizeof(float), s));
     if (use_mfma(p, dtype))
         RUN(conv_mfma_wgrad(p, (const bf16_t*)x, (const bf16_t*)dy, dw, p.Cin, false, s));
+    else if (gen)
+        RUN(gen_conv_wgrad(p, dtype, x, dy, dw, false, s));
     else
         RUN(conv_direct_wgrad(p, dtype, x, dy, dw, s));
     return TSM_OK;
@@ -111,7 +142,7 @@ enum { CONV_FWD = 0, CONV_DGRAD = 1, CONV_WGRAD = 2 };
 
 static int conv_entry(int which, const tsm_conv_desc* d, const void* a0, const void* a1, void* out, float* ch_sum,
                       float* ch_sumsq, int accumulate, void* wsp, size_t ws_bytes, bool dry, hipStream_t s,
-                      size_t* need) {
+                      size_t* need, bool lean = false) {
     const char* who = which == CONV_FWD ? "tsm_conv_fwd" : which == CONV_DGRAD ? "tsm_conv_dgrad" : "tsm_conv_wgrad";
     ConvP p;
     TSM_TRY(make_convp(d, &p, who));
@@ -123,9 +154,10 @@ static int conv_entry(int which, const tsm_conv_desc* d, const void* a0, const v
         if (ws_bytes > 0 && !wsp) return fail(TSM_ERR_NULLPTR, "%s: null workspace", who);
     }
     Arena ws(dry ? nullptr : wsp, dry ? (size_t)-1 : ws_bytes);
+    ws.lean = lean;
     if (!dry) {  // size check first, with a dry pass of the same plan
         size_t req = 0;
-        TSM_TRY(conv_entry(which, d, a0, a1, out, ch_sum, ch_sumsq, accumulate, nullptr, 0, true, s, &req));
+        TSM_TRY(conv_entry(which, d, a0, a1, out, ch_sum, ch_sumsq, accumulate, nullptr, 0, true, s, &req, lean));
         if (req > ws_bytes) return fail(TSM_ERR_WORKSPACE, "%s: workspace %zu bytes, need %zu", who, ws_bytes, req);
     }
     const int es = (int)dtype_size(d->dtype);
@@ -140,7 +172,7 @@ static int conv_entry(int which, const tsm_conv_desc* d, const void* a0, const v
             RUN(transpose_frames(a0, xt, p.F, p.Cin, p.H * p.W, es, s));
             x = xt;
         }
-        const int nb = conv_stats_blocks(p, d->dtype);
+        const int nb = conv_stats_blocks(p, d->dtype, ws);
         float* part = (ch_sum || dry) ? ws.take_n<float>((size_t)nb * 2 * p.Cout) : nullptr;
         TSM_TRY(run_conv_fwd(p, d->dtype, x, a1, nullptr, y, ch_sum ? part : nullptr, ws, dry, s));
         if (ch_sum) RUN(stats_to_float(part, nb, p.Cout, ch_sum, ch_sumsq, s));
@@ -298,7 +330,7 @@ static int block_fwd_stages(BlockPlan& b, const void* x, Arena& ws, bool dry, hi
     const void* cur = x;
     for (int i = 0; i < b.nst; ++i) {
         StageDef& st = b.st[i];
-        const int nb = conv_stats_blocks(st.p, b.dtype);
+        const int nb = conv_stats_blocks(st.p, b.dtype, ws);
         float* part = ws.take_n<float>((size_t)nb * 2 * st.p.Cout);
         TSM_TRY(run_conv_fwd(st.p, b.dtype, cur, st.w, st.wp, b.y[i], part, ws, dry, s));
         RUN(bn_finalize(part, nb, st.p.rows_out(), st.p.Cout, st.g, st.b, b.eps, b.bn[i], st.run_mean, st.run_var,
@@ -313,7 +345,7 @@ static int block_fwd_stages(BlockPlan& b, const void* x, Arena& ws, bool dry, hi
 
 static int block_fwd_shortcut(BlockPlan& b, const void* x, Arena& ws, bool dry, hipStream_t s) {
     StageDef& st = b.ds;
-    const int nb = conv_stats_blocks(st.p, b.dtype);
+    const int nb = conv_stats_blocks(st.p, b.dtype, ws);
     float* part = ws.take_n<float>((size_t)nb * 2 * st.p.Cout);
     TSM_TRY(run_conv_fwd(st.p, b.dtype, x, st.w, st.wp, b.yd, part, ws, dry, s));
     RUN(bn_finalize(part, nb, st.p.rows_out(), st.p.Cout, st.g, st.b, b.eps, b.bnd, st.run_mean, st.run_var,
@@ -844,7 +876,12 @@ static int noalloc_scratch(void** out) {
 int tsm_conv_fwd_noalloc(const tsm_conv_desc* d, const void* x, const void* w, void* y, float* ch_sum, float* ch_sumsq,
                          void* stream) {
     size_t need = 0;
+    bool lean = false;
     TSM_TRY(conv_entry(CONV_FWD, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, true, nullptr, &need));
+    if (need > (size_t)TSM_NOALLOC_SCRATCH_BYTES) {
+        lean = true;
+        TSM_TRY(conv_entry(CONV_FWD, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, true, nullptr, &need, lean));
+    }
     if (need > (size_t)TSM_NOALLOC_SCRATCH_BYTES)
         return fail(TSM_ERR_WORKSPACE, "tsm_conv_fwd_noalloc: this convolution needs %zu bytes of scratch, the built-in buffer holds %zu",
                     need, (size_t)TSM_NOALLOC_SCRATCH_BYTES);
@@ -856,9 +893,9 @@ int tsm_conv_fwd_noalloc(const tsm_conv_desc* d, const void* x, const void* w, v
     void* scratch = nullptr;
     TSM_TRY(noalloc_scratch(&scratch));
     // Nothing in the buffer has to start at zero: the packed weights and the transposed copies are written in full
-    // before they are read, and every block of the convolution clears its own statistics row first.
+    // before they are read, and the blocks of the convolution clear their statistics rows first or write them in full.
     return conv_entry(CONV_FWD, d, x, w, y, ch_sum, ch_sumsq, 0, scratch, (size_t)TSM_NOALLOC_SCRATCH_BYTES, false,
-                      (hipStream_t)stream, nullptr);
+                      (hipStream_t)stream, nullptr, lean);
 }
 
 size_t tsm_block_infer_workspace_bytes(const tsm_block_desc* d) {

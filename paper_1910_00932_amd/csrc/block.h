@@ -42,7 +42,7 @@ struct BlockPlan {
     uint8_t* out_bits = nullptr;  // optional: receives the ReLU decisions of the block's output (see block_tail_fwd)
 };
 
-int conv_stats_blocks(const ConvP& p, int dtype);
+int conv_stats_blocks(const ConvP& p, int dtype, const Arena& ws);
 int run_conv_fwd(const ConvP& p, int dtype, const void* x, const void* w, const bf16_t* wp, void* y,
                  float* stats_partial, Arena& ws, bool dry, hipStream_t s);
 // Rows of the partial buffer a fused data gradient fills (see DgradFuse); 0 when it cannot fuse.

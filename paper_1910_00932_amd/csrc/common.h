@@ -40,6 +40,9 @@ inline int fold_of(int C, int fold_div, int* fold) {
 struct Arena {
     char* base;
     size_t cap, used;
+    // A caller with a fixed scratch buffer that the general kernels' packed weights and statistics rows do not fit:
+    // fp32 and ragged-channel convolutions then run on the plain kernels, which need neither.
+    bool lean = false;
     Arena(void* p, size_t bytes) : base((char*)p), cap(bytes), used(0) {}
     void* take(size_t bytes) {
         size_t a = align_up(bytes);

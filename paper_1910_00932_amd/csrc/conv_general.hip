@@ -1,0 +1,692 @@
+// Implicit-GEMM convolutions for what the 64-channel kernels of conv_mfma.hip do not take: fp32 storage with any
+// channel counts, and bf16 storage whose channel counts or shift groups are not multiples of eight.
+//
+// Both storage types run the same code: a K step is 128 bytes of every tile row (32 floats or 64 bf16), staged through
+// LDS, and only the instruction that multiplies a 16-byte fragment pair differs -- v_mfma_f32_32x32x16_bf16, or four
+// v_mfma_f32_32x32x2_f32 (fp32 products and sums: no precision is given up against a scalar fmaf loop).
+//
+// What bounds them: fp32 runs at the fp32 matrix rate (157 TFLOP/s, 64 cycles per instruction and 4 KB of LDS
+// fragments per 4096 of those cycles: neither LDS nor memory comes close), so plain register prefetch and two stages are
+// enough and tiles are chosen for how well they fill the last round.
+//
+// Against one thread per output element (1.2 TFLOP/s whatever the layer; those kernels are kept in direct.hip for strides
+// beyond 2 and filters beyond 8): fp32 train step at 4 clips of 8 x 224^2 655 -> 16.1 ms; fp32 64-channel basic block at
+// 2 clips of 8 x 14^2, forward and backward, 1077 -> 201 us; bf16 72 -> 200 channels 3x3 at 4 clips of 8 x 29^2, all
+// three directions, 17.7 ms -> 211 us.
+//
+// The shift is index arithmetic as in conv_mfma.hip.  A 16-byte vector of channels that straddles two shift groups is
+// put together from one masked load per group; where rows are not 16-byte aligned (channel counts that are no multiple
+// of the vector) it is loaded element by element.
+#include "internal.h"
+
+namespace tsm {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+static constexpr int KB = 128;          // bytes of every tile row per K step
+static constexpr int PITCH = KB + 16;   // LDS row pitch: rows 36 banks apart
+
+struct GenArgs {
+    const void* src;       // x (fwd) or dy (dgrad), channels innermost
+    const void* wp;        // packed weights [Cd][taps][CsP]
+    void* dst;
+    const void* addend;    // dgrad: added to dx (nullable)
+    float* stats;          // fwd: [mtiles][2*Cd] partial sums of y and y^2 (nullable)
+    int F, T;
+    int Hs, Ws, Cs, CsP;   // source frame; CsP = channels per tap in wp, a multiple of the vector
+    int Hd, Wd, Cd;
+    int KT, KH, KW, stride, padh, padw;
+    int fold;              // fwd: shift of source channels; dgrad: adjoint shift of destination channels
+    int Kp;                // taps * CsP
+    int ntiles, mtiles;
+    // parity classes of destination pixels (see IgemmArgs in conv_mfma.hip)
+    int ncls, cstep;
+    int ph[4], pw[4], hc[4], wc[4], mt0[5];
+    int a0h[4], nth[4], a0w[4], ntw[4];
+};
+
+__device__ __forceinline__ int grp_dt(int c, int fold) { return c < fold ? 1 : (c < 2 * fold ? -1 : 0); }
+
+// Bits of a 16-byte vector that belong to elements lo <= e < hi.
+template <typename T>
+__device__ __forceinline__ u32x4 elem_mask(int lo, int hi) {
+    u32x4 m;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (sizeof(T) == 4)
+            m[q] = (q >= lo && q < hi) ? 0xffffffffu : 0u;
+        else
+            m[q] = ((2 * q >= lo && 2 * q < hi) ? 0xffffu : 0u) | ((2 * q + 1 >= lo && 2 * q + 1 < hi) ? 0xffff0000u : 0u);
+    }
+    return m;
+}
+
+// Channels ch .. ch+VE-1 of S(x) at one pixel: `p` points at channel 0 of the pixel in the row's own frame (it may lie
+// outside the tensor: nothing is read unless the masks allow it), `sp_ok` tells whether the tap lies inside the frame,
+// tmask has bit 30 / 31 set where frame t+1 / t-1 is in the clip, d0 is the frame offset of a temporal tap.
+template <typename T, bool RAG>
+__device__ __forceinline__ u32x4 load_shifted(const T* p, bool sp_ok, uint32_t tmask, int ch, int C, int fold, int d0, long frame) {
+    constexpr int VE = 16 / sizeof(T);
+    auto in_clip = [&](int d) { return d == 0 || (d > 0 ? (tmask >> 30) & 1u : tmask >> 31) != 0; };
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (!sp_ok) return v;
+    if (!RAG) {
+        const int d = d0 + grp_dt(ch, fold);
+        if (in_clip(d)) v = *(const u32x4*)(p + d * frame + ch);
+        return v;
+    }
+    if (C % VE == 0) {
+        if (ch < fold && in_clip(1)) v = *(const u32x4*)(p + frame + ch) & elem_mask<T>(0, fold - ch);
+        if (ch < 2 * fold && ch + VE > fold && in_clip(-1)) v |= *(const u32x4*)(p - frame + ch) & elem_mask<T>(fold - ch, 2 * fold - ch);
+        if (ch + VE > 2 * fold && in_clip(d0)) v |= *(const u32x4*)(p + d0 * frame + ch) & elem_mask<T>(2 * fold - ch, VE);
+        return v;
+    }
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+        const int c = ch + e;
+        const int d = d0 + grp_dt(c, fold);
+        if (c < C && in_clip(d)) {
+            const T* q = p + d * frame + c;
+            if (sizeof(T) == 4)
+                v[e & 3] = *(const uint32_t*)q;
+            else
+                v[(e >> 1) & 3] |= (uint32_t)*(const bf16_t*)q << (16 * (e & 1));
+        }
+    }
+    return v;
+}
+
+// One 16-byte fragment pair per (i, j): lane = row lane % 32 of the operand, K elements of its half (lane / 32).
+template <typename T, int MI, int NJ>
+__device__ __forceinline__ void mma(const u32x4* a, const u32x4* b, f32x16 (&acc)[MI][NJ]) {
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i][e]), __uint_as_float(b[j][e]), acc[i][j], 0, 0, 0);
+    }
+}
+
+struct GenRow {
+    long off;        // element offset of the row's tap origin, channel 0 (only used for taps inside the frame)
+    uint32_t mask;   // bits 0..7 / 8..15: tap rows / columns inside the frame; 30 / 31: frame t+1 / t-1 in the clip
+    int dst;         // destination row, -1 beyond the last one
+};
+
+// D[pixels x channels], one tile per block.
+template <typename T, int BM, int BN, int WM, int WN, bool DGRAD, bool RAG>
+__global__ void __launch_bounds__(256, 2) gen_igemm_kernel(GenArgs a) {
+    static_assert(WM * WN == 4, "four wavefronts");
+    constexpr int TM = BM / WM, TN = BN / WN;
+    constexpr int MI = TM / 32, NJ = TN / 32;
+    constexpr int VE = 16 / (int)sizeof(T);
+    constexpr int KV = KB / 16, KE = KB / (int)sizeof(T);
+    constexpr int RPP = 256 / KV;
+    constexpr int PA = BM / RPP, PB = BN / RPP;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * (BM + BN) * PITCH];
+    __shared__ GenRow s_row[BM];
+    static_assert(2 * WM * 2 * BN * 4 <= 2 * (BM + BN) * PITCH, "the statistics slots reuse the stages");
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int kvec = tid % KV, lrow = tid / KV;
+
+    // tiles that share their pixels have indices 8 apart: one XCD, one L2
+    const int bid = (int)blockIdx.x;
+    const int mt = ((bid >> 3) / a.ntiles) * 8 + (bid & 7);
+    if (mt >= a.mtiles) return;
+    const int n0 = ((bid >> 3) % a.ntiles) * BN;
+    int cls = 0;
+    while (cls + 1 < a.ncls && mt >= a.mt0[cls + 1]) ++cls;
+    const int nth = a.nth[cls], ntw = a.ntw[cls];
+    const long frame = (long)a.Hs * a.Ws * a.Cs;
+
+    if (tid < BM) {
+        const int hc = a.hc[cls], wc = a.wc[cls];
+        const long m = (long)(mt - a.mt0[cls]) * BM + tid;
+        GenRow r;
+        r.off = 0; r.mask = 0; r.dst = -1;
+        if (m < (long)a.F * hc * wc) {
+            const int f = (int)(m / (hc * wc));
+            const int q = (int)(m - (long)f * (hc * wc));
+            const int qh = q / wc, qw = q - qh * wc;
+            const int dh = qh * a.cstep + a.ph[cls], dw = qw * a.cstep + a.pw[cls];
+            const int oh = DGRAD ? (dh - a.padh + a.a0h[cls]) / a.cstep : dh * a.stride - a.padh;
+            const int ow = DGRAD ? (dw - a.padw + a.a0w[cls]) / a.cstep : dw * a.stride - a.padw;
+            const int t = f % a.T;
+            for (int th = 0; th < nth; ++th)
+                if (oh + th >= 0 && oh + th < a.Hs) r.mask |= 1u << th;
+            for (int tw = 0; tw < ntw; ++tw)
+                if (ow + tw >= 0 && ow + tw < a.Ws) r.mask |= 1u << (8 + tw);
+            if (t + 1 < a.T) r.mask |= 1u << 30;
+            if (t >= 1) r.mask |= 1u << 31;
+            r.off = ((long)f * a.Hs * a.Ws + (long)oh * a.Ws + ow) * a.Cs;
+            r.dst = (f * a.Hd + dh) * a.Wd + dw;
+        }
+        s_row[tid] = r;
+    }
+    __syncthreads();
+
+    const T* aptr[PA];
+    uint32_t amask[PA];
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+        const GenRow r = s_row[i * RPP + lrow];
+        aptr[i] = (const T*)a.src + r.off;
+        amask[i] = r.mask;
+    }
+    const T* bptr[PB];
+#pragma unroll
+    for (int j = 0; j < PB; ++j) {
+        const int n = n0 + j * RPP + lrow;
+        bptr[j] = n < a.Cd ? (const T*)a.wp + (long)n * a.Kp : nullptr;
+    }
+    const int ntaps = a.KT * nth * ntw;
+    const int nk = (ntaps * a.CsP + KE - 1) / KE;
+    int kt = 0, th = 0, tw = 0, ltap = 0, ch = kvec * VE;   // position of this thread's vector in the K range
+    auto wrap = [&]() {
+        while (ch >= a.CsP) {
+            ch -= a.CsP;
+            ++ltap;
+            if (++tw >= ntw) { tw = 0; if (++th >= nth) { th = 0; ++kt; } }
+        }
+    };
+    wrap();
+
+    u32x4 areg[PA], breg[PB];
+    auto load = [&]() {
+        const bool kvalid = ltap < ntaps;
+        const uint32_t need = (1u << th) | (1u << (8 + tw));
+        const int d0 = kt - a.KT / 2;
+        const int toff = (th * a.Ws + tw) * a.Cs;
+#pragma unroll
+        for (int i = 0; i < PA; ++i)
+            areg[i] = load_shifted<T, RAG>(aptr[i] + toff, kvalid && (amask[i] & need) == need, amask[i], ch, a.Cs, DGRAD ? 0 : a.fold, d0, frame);
+        const int woff = ((kt * a.KH + a.a0h[cls] + th * a.cstep) * a.KW + a.a0w[cls] + tw * a.cstep) * a.CsP + ch;
+#pragma unroll
+        for (int j = 0; j < PB; ++j) breg[j] = (kvalid && bptr[j]) ? *(const u32x4*)(bptr[j] + woff) : u32x4{0u, 0u, 0u, 0u};
+        ch += KE;
+        wrap();
+    };
+    auto store = [&](int buf) {
+        unsigned char* A = smem + buf * (BM + BN) * PITCH;
+#pragma unroll
+        for (int i = 0; i < PA; ++i) *(u32x4*)(A + (i * RPP + lrow) * PITCH + kvec * 16) = areg[i];
+#pragma unroll
+        for (int j = 0; j < PB; ++j) *(u32x4*)(A + (BM + j * RPP + lrow) * PITCH + kvec * 16) = breg[j];
+    };
+
+    f32x16 acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    if (nk > 0) {
+        load();
+        store(0);
+        __syncthreads();
+    }
+    for (int k = 0; k < nk; ++k) {
+        const int buf = k & 1;
+        if (k + 1 < nk) load();
+        const unsigned char* A = smem + buf * (BM + BN) * PITCH + (wm * TM + (lane & 31)) * PITCH + 16 * (lane >> 5);
+        const unsigned char* B = smem + buf * (BM + BN) * PITCH + (BM + wn * TN + (lane & 31)) * PITCH + 16 * (lane >> 5);
+#pragma unroll
+        for (int ks = 0; ks < KB / 32; ++ks) {
+            u32x4 af[MI], bf[NJ];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) af[i] = *(const u32x4*)(A + i * 32 * PITCH + ks * 32);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) bf[j] = *(const u32x4*)(B + j * 32 * PITCH + ks * 32);
+            mma<T, MI, NJ>(af, bf, acc);
+        }
+        if (k + 1 < nk) store(buf ^ 1);
+        __syncthreads();
+    }
+
+    // ---- epilogue: lane = channel lane % 32, register r = row 8*(r/4) + 4*(lane/32) + r%4 of the 32x32 block; a
+    // half-wavefront stores 32 consecutive channels of one pixel
+    float* s_part = (float*)smem;   // [2][WM*2][BN]
+    const int hw_d = a.Hd * a.Wd;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int cl = wn * TN + j * 32 + (lane & 31), col = n0 + cl;
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int m = s_row[row].dst;
+                if (m < 0 || col >= a.Cd) continue;
+                T* const dst = (T*)a.dst;
+                if (!DGRAD) {
+                    const T q = Elem<T>::st(acc[i][j][r]);
+                    const float v = Elem<T>::ld(q);
+                    s1 += v;
+                    s2 = fmaf(v, v, s2);
+                    dst[(long)m * a.Cd + col] = q;
+                } else {
+                    const int dt = grp_dt(col, a.fold);
+                    auto emit = [&](long mr, float v) {
+                        const long at = mr * a.Cd + col;
+                        // (rounded once before the addition, like the kernels that stage the result)
+                        if (a.addend) v = Elem<T>::ld(Elem<T>::st(v)) + Elem<T>::ld(((const T*)a.addend)[at]);
+                        dst[at] = Elem<T>::st(v);
+                    };
+                    if (dt == 0) {
+                        emit(m, acc[i][j][r]);
+                    } else {
+                        const uint32_t mask = s_row[row].mask;
+                        const bool next = (mask >> 30) & 1u, prev = mask >> 31;   // frame t+1 / t-1 is in the clip
+                        if (dt > 0 ? next : prev) emit(m + (long)dt * hw_d, acc[i][j][r]);
+                        // the frame that receives nothing from inside the clip
+                        if (dt > 0 ? !prev : !next) emit(m, 0.f);
+                    }
+                }
+            }
+        }
+        if (!DGRAD && a.stats) {
+            const int slot = wm * 2 + (lane >> 5);
+            s_part[slot * BN + cl] = s1;
+            s_part[(WM * 2 + slot) * BN + cl] = s2;
+        }
+    }
+    if (!DGRAD && a.stats) {
+        __syncthreads();
+        if (tid < 2 * BN) {
+            const int stat = tid / BN, cl = tid % BN;
+            float v = 0.f;
+#pragma unroll
+            for (int sl = 0; sl < WM * 2; ++sl) v += s_part[(stat * WM * 2 + sl) * BN + cl];
+            if (n0 + cl < a.Cd) a.stats[(size_t)mt * 2 * a.Cd + stat * a.Cd + n0 + cl] = v;
+        }
+    }
+}
+
+// ---- weight gradient: D[Cout x (tap, Cin)], reduced over a chunk of output pixels, fp32 atomics -------------------
+struct GenWgradArgs {
+    const void* x;
+    const void* dy;
+    float* dw;             // element (co, ci, tap) at co*so + ci*si + tap*st
+    long so;
+    int si, st;
+    int F, T, H, W, Cin, CinP, Ho, Wo, Cout;
+    int KT, KH, KW, stride, pad, fold;
+    long M, chunk;
+    int K;                 // taps * CinP: columns of D, padded per tap
+    int col_tiles;
+};
+
+static constexpr int GPX = 32;   // pixels per step
+
+// Operand rows go to LDS as loaded, [pixel][channel].  fp32: a lane reads its channel of pixel 2k + lane/32 (32
+// consecutive words per half-wavefront).  bf16: the transposing read, rows padded by 64 bytes so that the four pixels
+// x two channel blocks that 32 lanes read together fall into different banks.
+template <typename T, int BCO, int BCI, int WM, int WN, bool RAG>
+__global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
+    static_assert(WM * WN == 4, "four wavefronts");
+    constexpr int TM = BCO / WM, TN = BCI / WN;
+    constexpr int MI = TM / 32, NJ = TN / 32;
+    constexpr int VE = 16 / (int)sizeof(T);
+    constexpr int PADB = sizeof(T) == 2 ? 64 : 0;
+    constexpr int ROWA = BCO * (int)sizeof(T) + PADB, ROWB = BCI * (int)sizeof(T) + PADB;
+    constexpr int STAGE = GPX * (ROWA + ROWB);
+    constexpr int AV = BCO / VE, BV = BCI / VE;
+    constexpr int RA = 256 / AV, RB = 256 / BV;        // rows per load pass
+    constexpr int PA = GPX / RA, PB = GPX / RB;
+    static_assert(256 % AV == 0 && 256 % BV == 0 && GPX % RA == 0 && GPX % RB == 0, "tile / thread mismatch");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * STAGE];
+    __shared__ GenRow s_pix[3][GPX];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int co0 = ((int)blockIdx.y / a.col_tiles) * BCO;
+    const int j0 = ((int)blockIdx.y % a.col_tiles) * BCI;
+    const long mbeg = (long)blockIdx.x * a.chunk;
+    long mend = mbeg + a.chunk;
+    if (mend > a.M) mend = a.M;
+    if (mbeg >= mend) return;
+    const int hw = a.Ho * a.Wo;
+    const long frame = (long)a.H * a.W * a.Cin;
+
+    const int avec = tid % AV, arow = tid / AV;
+    const int bvec = tid % BV, brow = tid / BV;
+    // this thread's column vector: (tap, first channel) for life
+    const int jb = j0 + bvec * VE;
+    const bool col_ok = jb < a.K;
+    const int tap = col_ok ? jb / a.CinP : 0, ch = col_ok ? jb - tap * a.CinP : 0;
+    const int kw = tap % a.KW, kh = (tap / a.KW) % a.KH, kt = tap / (a.KW * a.KH);
+    const uint32_t need = (1u << kh) | (1u << (8 + kw));
+    const int d0 = kt - a.KT / 2;
+    const int toff = (kh * a.W + kw) * a.Cin;
+
+    auto decode = [&](int st) {
+        if (tid < GPX) {
+            const long m = mbeg + (long)st * GPX + tid;
+            GenRow r;
+            r.off = 0; r.mask = 0; r.dst = 0;
+            if (m < mend) {
+                const int f = (int)(m / hw);
+                const int pix = (int)(m - (long)f * hw);
+                const int oh = pix / a.Wo, ow = pix - oh * a.Wo;
+                const int ih = oh * a.stride - a.pad, iw = ow * a.stride - a.pad;
+                const int t = f % a.T;
+                for (int h = 0; h < a.KH; ++h)
+                    if (ih + h >= 0 && ih + h < a.H) r.mask |= 1u << h;
+                for (int w = 0; w < a.KW; ++w)
+                    if (iw + w >= 0 && iw + w < a.W) r.mask |= 1u << (8 + w);
+                if (t + 1 < a.T) r.mask |= 1u << 30;
+                if (t >= 1) r.mask |= 1u << 31;
+                r.off = ((long)f * a.H * a.W + (long)ih * a.W + iw) * a.Cin;
+            }
+            s_pix[st % 3][tid] = r;
+        }
+    };
+    u32x4 ar[PA], br[PB];
+    auto load = [&](int st) {
+#pragma unroll
+        for (int i = 0; i < PA; ++i) {
+            const long m = mbeg + (long)st * GPX + arow + i * RA;
+            ar[i] = load_shifted<T, RAG>((const T*)a.dy + m * a.Cout, m < mend && co0 + avec * VE < a.Cout, 0u, co0 + avec * VE, a.Cout, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+            const GenRow r = s_pix[st % 3][brow + i * RB];
+            br[i] = load_shifted<T, RAG>((const T*)a.x + r.off + toff, col_ok && (r.mask & need) == need, r.mask, ch, a.Cin, a.fold, d0, frame);
+        }
+    };
+    auto store = [&](int buf) {
+        unsigned char* S = smem + buf * STAGE;
+#pragma unroll
+        for (int i = 0; i < PA; ++i) *(u32x4*)(S + (arow + i * RA) * ROWA + avec * 16) = ar[i];
+#pragma unroll
+        for (int i = 0; i < PB; ++i) *(u32x4*)(S + GPX * ROWA + (brow + i * RB) * ROWB + bvec * 16) = br[i];
+    };
+
+    f32x16 acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    auto multiply = [&](int buf) {
+        const unsigned char* A = smem + buf * STAGE;
+        const unsigned char* B = A + GPX * ROWA;
+        if constexpr (sizeof(T) == 4) {
+            const float* pa = (const float*)(A + (lane >> 5) * ROWA) + wm * TM + (lane & 31);
+            const float* pb = (const float*)(B + (lane >> 5) * ROWB) + wn * TN + (lane & 31);
+#pragma unroll
+            for (int k = 0; k < GPX; k += 2) {
+                float af[MI], bf[NJ];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) af[i] = pa[k * (ROWA / 4) + i * 32];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) bf[j] = pb[k * (ROWB / 4) + j * 32];
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+            }
+        } else {
+            // lane = 32*kg + 16*mblk + 4*e + c supplies channels 4c.. of pixel 8*kg + e and receives four pixels of one channel
+            const int c = lane & 3, e = (lane >> 2) & 3, mblk = (lane >> 4) & 1, kg = lane >> 5;
+            auto frag = [&](const unsigned char* base, int row, int chan) {
+                const unsigned char* p = base + (8 * kg + e) * row + (chan + 16 * mblk + 4 * c) * 2;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 4 * row));
+                return __builtin_bit_cast(u32x4, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            };
+#pragma unroll
+            for (int k = 0; k < GPX; k += 16) {
+                u32x4 af[MI], bf[NJ];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) af[i] = frag(A + k * ROWA, ROWA, wm * TM + i * 32);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) bf[j] = frag(B + k * ROWB, ROWB, wn * TN + j * 32);
+                mma<T, MI, NJ>(af, bf, acc);
+            }
+        }
+    };
+
+    const int nsteps = (int)((mend - mbeg + GPX - 1) / GPX);
+    decode(0);
+    if (nsteps > 1) decode(1);
+    __syncthreads();
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int st = 0; st < nsteps; ++st) {
+        const int buf = st & 1;
+        if (st + 2 < nsteps) decode(st + 2);
+        if (st + 1 < nsteps) load(st + 1);
+        multiply(buf);
+        if (st + 1 < nsteps) store(buf ^ 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int col = j0 + wn * TN + j * 32 + (lane & 31);
+        const int tp = col / a.CinP, ci = col - tp * a.CinP;
+        if (col >= a.K || ci >= a.Cin) continue;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int co = co0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                if (co < a.Cout) atomicAdd(a.dw + (long)co * a.so + (long)ci * a.si + (long)tp * a.st, acc[i][j][r]);
+            }
+    }
+}
+
+// ---- weights: ABI [Cout][Cin][taps] -> [Cout][taps][CinP] (fwd) or [Cin][flipped taps][CoutP] (dgrad), padding zero
+template <typename T, bool DGRAD>
+__global__ void __launch_bounds__(256) gen_pack_kernel(const T* __restrict__ w, T* __restrict__ out, int Cout, int Cin, int KT,
+                                                       int KH, int KW, int CP, long total) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= total) return;
+    const int taps = KT * KH * KW;
+    const int c = (int)(i % CP), tap = (int)(i / CP % taps), n = (int)(i / ((long)CP * taps));
+    const int co = DGRAD ? c : n, ci = DGRAD ? n : c;
+    T v = Elem<T>::st(0.f);
+    if (c < (DGRAD ? Cout : Cin)) {
+        int src = tap;
+        if (DGRAD) {   // spatial taps are flipped and so is the temporal one
+            const int kw = tap % KW, kh = tap / KW % KH, kt = tap / (KW * KH);
+            src = ((KT - 1 - kt) * KH + (KH - 1 - kh)) * KW + (KW - 1 - kw);
+        }
+        v = w[((long)co * Cin + ci) * taps + src];
+    }
+    out[i] = v;
+}
+
+// ---- host side ----------------------------------------------------------------------------------------------------
+static int cu_count() {
+    static int n = 0;
+    if (n == 0) {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) n = v;
+        if (n <= 0) n = 256;
+    }
+    return n;
+}
+static int pad_vec(int c, int dtype) { const int v = dtype == TSM_F32 ? 4 : 8; return (c + v - 1) / v * v; }
+
+bool gen_conv_supported(const ConvP& p) {
+    if (p.pitch && p.pitch != p.Cin) return false;
+    if (p.stride > 2 || p.KH > 8 || p.KW > 8) return false;   // four parity classes, eight mask bits each way
+    if (p.KT > 1 && p.fold > 0) return false;                 // frame offsets stay within one frame either way
+    if (p.Cin > 65536 || p.Cout > 65536 || (long)p.taps() * (p.Cin + 8) > 0x3fffffffL || (long)p.taps() * (p.Cout + 8) > 0x3fffffffL) return false;
+    if (p.rows_in() > 0x3fffffffL || p.rows_out() > 0x3fffffffL) return false;
+    if ((long)p.H * p.W * p.Cin > 0x3fffffffL || (long)p.Ho * p.Wo * p.Cout > 0x3fffffffL) return false;
+    if ((p.rows_in() / 64 + 40) * ((p.Cin + 63) / 64) > 0x7fffffffL || (p.rows_out() / 64 + 40) * ((p.Cout + 63) / 64) > 0x7fffffffL) return false;
+    return true;
+}
+
+// Elements of the packed weights each direction needs; 0: the ABI order serves as it is.
+size_t gen_pack_elems(const ConvP& p, int dtype, bool dgrad) {
+    if (dgrad) return (size_t)p.Cin * p.taps() * pad_vec(p.Cout, dtype);
+    if (p.taps() == 1 && pad_vec(p.Cin, dtype) == p.Cin) return 0;
+    return (size_t)p.Cout * p.taps() * pad_vec(p.Cin, dtype);
+}
+
+int gen_pack_weights(const ConvP& p, int dtype, bool dgrad, const void* w, void* out, hipStream_t s) {
+    const long total = (long)gen_pack_elems(p, dtype, dgrad);
+    const int CP = pad_vec(dgrad ? p.Cout : p.Cin, dtype);
+    const dim3 grid((unsigned)((total + 255) / 256));
+    if (dtype == TSM_F32) {
+        if (dgrad) gen_pack_kernel<float, true><<<grid, dim3(256), 0, s>>>((const float*)w, (float*)out, p.Cout, p.Cin, p.KT, p.KH, p.KW, CP, total);
+        else gen_pack_kernel<float, false><<<grid, dim3(256), 0, s>>>((const float*)w, (float*)out, p.Cout, p.Cin, p.KT, p.KH, p.KW, CP, total);
+    } else {
+        if (dgrad) gen_pack_kernel<bf16_t, true><<<grid, dim3(256), 0, s>>>((const bf16_t*)w, (bf16_t*)out, p.Cout, p.Cin, p.KT, p.KH, p.KW, CP, total);
+        else gen_pack_kernel<bf16_t, false><<<grid, dim3(256), 0, s>>>((const bf16_t*)w, (bf16_t*)out, p.Cout, p.Cin, p.KT, p.KH, p.KW, CP, total);
+    }
+    return check_launch("gen_pack");
+}
+
+static void gen_classes(GenArgs& a, bool dgrad, int BM) {
+    if (!dgrad || a.stride == 1) {
+        a.ncls = 1; a.cstep = 1;
+        a.ph[0] = a.pw[0] = 0; a.hc[0] = a.Hd; a.wc[0] = a.Wd;
+        a.a0h[0] = a.a0w[0] = 0; a.nth[0] = a.KH; a.ntw[0] = a.KW;
+    } else {
+        const int st = a.stride;
+        a.ncls = st * st; a.cstep = st;
+        for (int c = 0; c < a.ncls; ++c) {
+            a.ph[c] = c / st; a.pw[c] = c % st;
+            a.hc[c] = (a.Hd - a.ph[c] + st - 1) / st;
+            a.wc[c] = (a.Wd - a.pw[c] + st - 1) / st;
+            a.a0h[c] = (((a.padh - a.ph[c]) % st) + st) % st;
+            a.a0w[c] = (((a.padw - a.pw[c]) % st) + st) % st;
+            a.nth[c] = a.a0h[c] < a.KH ? (a.KH - a.a0h[c] + st - 1) / st : 0;
+            a.ntw[c] = a.a0w[c] < a.KW ? (a.KW - a.a0w[c] + st - 1) / st : 0;
+            if (a.nth[c] == 0 || a.ntw[c] == 0) a.nth[c] = a.ntw[c] = 0;
+        }
+    }
+    a.mt0[0] = 0;
+    for (int c = 0; c < a.ncls; ++c) a.mt0[c + 1] = a.mt0[c] + (int)(((long)a.F * a.hc[c] * a.wc[c] + BM - 1) / BM);
+    a.mtiles = a.mt0[a.ncls];
+}
+
+// Tile by the time the fullest CU needs: rounds of tiles times tile area, the smaller tiles charged for the operand
+// bytes they read more often.
+struct GenTile { int bm, bn; };
+static GenTile gen_tile(long rows, int Cd) {
+    static const struct { int bm, bn; double cost; } opt[3] = {{128, 128, 1.0}, {128, 64, 1.06}, {64, 64, 1.15}};
+    GenTile best{64, 64};
+    double tbest = 0;
+    for (const auto& o : opt) {
+        const long tiles = ((rows + o.bm - 1) / o.bm) * ((Cd + o.bn - 1) / o.bn);
+        const long rounds = (tiles + cu_count() - 1) / cu_count();
+        const double t = (double)rounds * o.bm * o.bn * o.cost;
+        if (tbest == 0 || t < tbest) { tbest = t; best = {o.bm, o.bn}; }
+    }
+    return best;
+}
+
+template <typename T, bool DGRAD, bool RAG>
+static int gen_launch(GenArgs& a, hipStream_t s) {
+    const GenTile t = gen_tile((long)a.F * a.Hd * a.Wd, a.Cd);
+    gen_classes(a, DGRAD, t.bm);
+    a.ntiles = (a.Cd + t.bn - 1) / t.bn;
+    const dim3 grid((unsigned)((a.mtiles + 7) / 8 * 8 * a.ntiles));
+    if (t.bm == 128 && t.bn == 128) gen_igemm_kernel<T, 128, 128, 2, 2, DGRAD, RAG><<<grid, dim3(256), 0, s>>>(a);
+    else if (t.bm == 128) gen_igemm_kernel<T, 128, 64, 2, 2, DGRAD, RAG><<<grid, dim3(256), 0, s>>>(a);
+    else gen_igemm_kernel<T, 64, 64, 2, 2, DGRAD, RAG><<<grid, dim3(256), 0, s>>>(a);
+    if (sizeof(T) == 4) return check_launch(DGRAD ? "gen_dgrad_f32" : "gen_fwd_f32");
+    return check_launch(DGRAD ? "gen_dgrad_bf16" : "gen_fwd_bf16");
+}
+
+int gen_fwd_blocks(const ConvP& p) {
+    const int bm = gen_tile(p.rows_out(), p.Cout).bm;
+    return (int)((p.rows_out() + bm - 1) / bm);
+}
+
+static void gen_common(GenArgs& a, const ConvP& p) {
+    a.addend = nullptr; a.stats = nullptr;
+    a.F = p.F; a.T = p.T; a.KT = p.KT; a.KH = p.KH; a.KW = p.KW; a.stride = p.stride; a.fold = p.fold;
+}
+
+int gen_conv_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void* y, float* stats, hipStream_t s) {
+    if (p.rows_out() == 0) return TSM_OK;
+    GenArgs a;
+    gen_common(a, p);
+    a.src = x; a.wp = wp; a.dst = y; a.stats = stats;
+    a.Hs = p.H; a.Ws = p.W; a.Cs = p.Cin; a.CsP = pad_vec(p.Cin, dtype);
+    a.Hd = p.Ho; a.Wd = p.Wo; a.Cd = p.Cout;
+    a.padh = a.padw = p.pad;
+    a.Kp = p.taps() * a.CsP;
+    const bool rag = a.CsP != a.Cs || p.fold % (dtype == TSM_F32 ? 4 : 8) != 0;
+    if (dtype == TSM_F32) return rag ? gen_launch<float, false, true>(a, s) : gen_launch<float, false, false>(a, s);
+    return rag ? gen_launch<bf16_t, false, true>(a, s) : gen_launch<bf16_t, false, false>(a, s);
+}
+
+int gen_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* wd, void* dx, const void* addend, hipStream_t s) {
+    if (p.rows_in() == 0) return TSM_OK;
+    GenArgs a;
+    gen_common(a, p);
+    a.src = dy; a.wp = wd; a.dst = dx; a.addend = addend;
+    a.Hs = p.Ho; a.Ws = p.Wo; a.Cs = p.Cout; a.CsP = pad_vec(p.Cout, dtype);
+    a.Hd = p.H; a.Wd = p.W; a.Cd = p.Cin;
+    a.padh = p.KH - 1 - p.pad; a.padw = p.KW - 1 - p.pad;
+    a.Kp = p.taps() * a.CsP;
+    const bool rag = a.CsP != a.Cs;
+    if (dtype == TSM_F32) return rag ? gen_launch<float, true, true>(a, s) : gen_launch<float, true, false>(a, s);
+    return rag ? gen_launch<bf16_t, true, true>(a, s) : gen_launch<bf16_t, true, false>(a, s);
+}
+
+template <typename T, bool RAG>
+static int gen_wgrad_launch(GenWgradArgs& a, hipStream_t s) {
+    const bool big = a.Cout > 64 && a.K > 64;
+    const int bco = big ? 128 : 64, bci = big ? 128 : 64;
+    a.col_tiles = cdiv(a.K, bci);
+    const long tiles = (long)cdiv(a.Cout, bco) * a.col_tiles;
+    // two blocks per CU, and at least eight steps per block against the atomics of its tile
+    long want = 2L * cu_count() / tiles;
+    if (want < 1) want = 1;
+    long chunk = (a.M + want - 1) / want;
+    if (chunk < 8L * GPX) chunk = 8L * GPX;
+    a.chunk = (chunk + GPX - 1) / GPX * GPX;
+    const dim3 grid((unsigned)((a.M + a.chunk - 1) / a.chunk), (unsigned)tiles);
+    if (big) gen_wgrad_kernel<T, 128, 128, 2, 2, RAG><<<grid, dim3(256), 0, s>>>(a);
+    else gen_wgrad_kernel<T, 64, 64, 2, 2, RAG><<<grid, dim3(256), 0, s>>>(a);
+    return check_launch(sizeof(T) == 4 ? "gen_wgrad_f32" : "gen_wgrad_bf16");
+}
+
+// dw is added to; packed: [Cout][taps][Cin], otherwise the ABI order [Cout][Cin][taps].
+int gen_conv_wgrad(const ConvP& p, int dtype, const void* x, const void* dy, float* dw, bool packed, hipStream_t s) {
+    if (p.rows_out() == 0) return TSM_OK;
+    GenWgradArgs a;
+    a.x = x; a.dy = dy; a.dw = dw;
+    a.so = (long)p.K(); a.si = packed ? 1 : p.taps(); a.st = packed ? p.Cin : 1;
+    a.F = p.F; a.T = p.T; a.H = p.H; a.W = p.W; a.Cin = p.Cin; a.CinP = pad_vec(p.Cin, dtype);
+    a.Ho = p.Ho; a.Wo = p.Wo; a.Cout = p.Cout;
+    a.KT = p.KT; a.KH = p.KH; a.KW = p.KW; a.stride = p.stride; a.pad = p.pad; a.fold = p.fold;
+    a.M = p.rows_out();
+    a.K = p.taps() * a.CinP;
+    const int ve = dtype == TSM_F32 ? 4 : 8;
+    const bool rag = p.Cin % ve || p.Cout % ve || p.fold % ve;
+    if (dtype == TSM_F32) return rag ? gen_wgrad_launch<float, true>(a, s) : gen_wgrad_launch<float, false>(a, s);
+    return rag ? gen_wgrad_launch<bf16_t, true>(a, s) : gen_wgrad_launch<bf16_t, false>(a, s);
+}
+
+}  // namespace tsm

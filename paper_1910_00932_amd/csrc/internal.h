@@ -29,7 +29,7 @@ int shift_launch(const void* x, void* y, int N, int T, int C, int H, int W, int 
                  int dir, hipStream_t s);
 int transpose_frames(const void* in, void* out, int F, int rows, int cols, int es, hipStream_t s);
 
-// ---- direct.hip: plain kernels for any shape, fp32 or bf16 storage ---------------
+// ---- direct.hip: plain kernels for the shapes no other kernel takes, fp32 or bf16 storage ---------------
 // Weights in the ABI order [Cout][Cin][KT*KH*KW], element type T (dtype).
 int conv_direct_fwd(const ConvP& p, int dtype, const void* x, const void* w, void* y, hipStream_t s);
 // dx = S^T(conv^T(dy, w)) (+ addend if not null, same shape as dx).
@@ -37,6 +37,17 @@ int conv_direct_dgrad(const ConvP& p, int dtype, const void* dy, const void* w, 
                       hipStream_t s);
 // dw fp32 [Cout][Cin][taps]; must be zeroed by the caller unless accumulating.
 int conv_direct_wgrad(const ConvP& p, int dtype, const void* x, const void* dy, float* dw, hipStream_t s);
+
+// ---- conv_general.hip: implicit GEMM for fp32 storage and for channel counts the bf16 MFMA kernels below do not take
+bool gen_conv_supported(const ConvP& p);
+// Elements (of dtype) of the packed weights of each direction; 0: the ABI order is what the kernel reads.
+size_t gen_pack_elems(const ConvP& p, int dtype, bool dgrad);
+int gen_pack_weights(const ConvP& p, int dtype, bool dgrad, const void* w, void* out, hipStream_t s);
+int gen_fwd_blocks(const ConvP& p);   // rows of gen_conv_fwd's statistics partial buffer
+int gen_conv_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void* y, float* stats_partial, hipStream_t s);
+int gen_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* wd, void* dx, const void* addend, hipStream_t s);
+// dw fp32 is added to; packed: [Cout][taps][Cin], otherwise the ABI order.
+int gen_conv_wgrad(const ConvP& p, int dtype, const void* x, const void* dy, float* dw, bool packed, hipStream_t s);
 
 // ---- elementwise.hip -----------------------------------------------------------------
 // Per-channel reductions are deterministic and atomic-free: every block of a

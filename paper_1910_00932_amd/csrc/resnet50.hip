@@ -868,7 +868,7 @@ static int r50_step(const tsm_r50_desc* d, const void* clips, const int32_t* lab
     }
     float *rm0, *rv0;
     run_slot(64, &rm0, &rv0);
-    const int nb0f = bf ? conv_mfma_fwd_blocks(stem) : red_blocks(stem.rows_out(), 64, dtype);
+    const int nb0f = bf ? conv_mfma_fwd_blocks(stem) : conv_stats_blocks(stem, dtype, A);
     // blocks of the stem backward kernel (rows of its partial buffer): 32 or 16 pixels per block step, a few
     // steps per block
     const int nb0b = (int)std::min<long>(4096, std::max<long>(1, stem.rows_out() / 128));
@@ -1062,8 +1062,9 @@ static int r50_step(const tsm_r50_desc* d, const void* clips, const int32_t* lab
         if (bf) {
             RUN(conv_mfma_fwd(stem, (const bf16_t*)x0, wp0, (bf16_t*)y0, part0, nullptr, s));
         } else {
-            RUN(conv_direct_fwd(stem, dtype, x0, P("conv1.w"), y0, s));
-            RUN(channel_stats(dtype, y0, stem.rows_out(), 64, part0, s));
+            Arena sc(scratch_base, scratch_cap);
+            TSM_TRY(run_conv_fwd(stem, dtype, x0, P("conv1.w"), nullptr, y0, part0, sc, dry, s));
+            note(sc);
         }
         RUN(bn_finalize(part0, nb0f, stem.rows_out(), 64, P("bn1.g"), P("bn1.b"), d->bn_eps, bn0, rm0, rv0,
                         d->bn_momentum, s));
@@ -1164,8 +1165,11 @@ static int r50_step(const tsm_r50_desc* d, const void* clips, const int32_t* lab
                 stem_unpack_kernel<<<dim3(64), dim3(256), 0, s>>>(dwp0, G("conv1.w"));
                 LAUNCH_CHECK("stem_unpack");
             }
-        } else
-            RUN(conv_direct_wgrad(stem, dtype, x0, da0, G("conv1.w"), s));
+        } else {
+            Arena sc(scratch_base, scratch_cap);
+            TSM_TRY(run_conv_wgrad(stem, dtype, x0, da0, G("conv1.w"), nullptr, 1, sc, dry, s));
+            note(sc);
+        }
     }
     if (unp.n && !dry) {
         unpack_all_kernel<<<dim3(cdiv(unp.start[unp.n], 256)), dim3(256), 0, s>>>(unp, dwp_base, grads);
@@ -1380,7 +1384,9 @@ static int r50_infer(const tsm_r50_desc* d, const void* clips, const float* para
         RUN(conv_mfma_fwd(stem, (const bf16_t*)x0, wp0, (bf16_t*)y0, nullptr, nullptr, s));
     } else {
         RUN(transpose_frames(clips, x0, F, 3, S * S, 4, s));
-        RUN(conv_direct_fwd(stem, dtype, x0, P("conv1.w"), y0, s));
+        Arena sc(scratch_base, scratch_cap);
+        TSM_TRY(run_conv_fwd(stem, dtype, x0, P("conv1.w"), nullptr, y0, nullptr, sc, dry, s));
+        scratch_need = sc.used;
     }
     {
         const int cv = 64 / VEC;

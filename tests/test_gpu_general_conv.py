@@ -1,0 +1,56 @@
+"""The general implicit-GEMM convolutions (fp32 storage; bf16 storage with channel counts or shift groups that are no
+multiple of eight) against the oracle, element by element, at the sizes where they can go wrong: one element past and
+one short of a tile, vectors that straddle two shift groups or the last channel, rows that are not 16-byte aligned, every
+tile shape, clips of one frame, both strides.  Bounds: those of test_gpu_conv.py (one rounding of an fp32 sum, with a
+factor of two; 1e-4 in fp32, where sums of K products differ from fp64 by about 1e-7 * sqrt(K))."""
+import numpy as np
+import pytest
+import torch
+
+import test_gpu_conv as TC
+from oracle import tsm_oracle as O
+from paper_1910_00932_amd import binding as B
+from paper_1910_00932_amd import inputs as I
+from gpu_util import compare_act, dev_vec, empty_act, from_dev, to_dev
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # N,T,Cin,H,W,Cout,k,stride,pad,fold_div
+    (1, 1, 4, 1, 1, 4, 1, 1, 0, 0),           # the smallest call
+    (2, 4, 72, 9, 8, 200, 3, 1, 1, 8),        # groups of 9 channels: vectors straddle both group borders
+    (1, 3, 12, 7, 5, 20, 3, 2, 1, 5),         # groups of 2, channel counts that are no multiple of eight, strided
+    (1, 2, 3, 13, 11, 64, 7, 2, 3, 0),        # three channels, 7x7: the stem
+    (1, 3, 132, 5, 13, 129, 1, 1, 0, 2),      # every channel shifted, 129 results
+    (1, 1, 20, 8, 8, 60, 3, 1, 1, 4),         # one frame: both groups read zeros
+    (1, 2, 66, 8, 8, 65, 3, 1, 1, 3),         # one pixel tile of 128 exactly; unaligned rows
+    (1, 2, 68, 33, 31, 132, 1, 2, 0, 8),      # strided 1x1 (two parity classes receive nothing)
+    (4, 8, 36, 23, 29, 132, 1, 1, 0, 4),      # enough tiles for the 128 x 128 tile
+    (3, 8, 40, 41, 40, 36, 3, 1, 1, 3),       # narrow result, several hundred tiles
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES)
+def test_general_conv_parity(case, dtype):
+    TC._run(case, dtype, "nthwc")
+
+
+@pytest.mark.parametrize("case", [CASES[1], CASES[2]])
+def test_general_conv_parity_paper_order(case):
+    TC._run(case, "bf16", "ntchw")
+
+
+def test_noalloc_forward_whose_packed_weights_do_not_fit_the_fixed_scratch():
+    """1024 x 512 x 3x3 fp32 weights are 18.9 MB packed, the built-in scratch is 16 MiB: the plain kernel runs."""
+    N, T, Cin, H, Cout, k = 1, 2, 1024, 3, 512, 3
+    x, w = I.normal((N, T, Cin, H, H), 0), I.kaiming_conv((Cout, Cin, k, k), 1)
+    d = B.ConvDesc(N=N, T=T, Cin=Cin, H=H, W=H, Cout=Cout, kh=k, kw=k, stride=1, pad=1, fold_div=8, dtype=B.TSM_F32,
+                   layout=B.TSM_NTHWC)
+    assert B.tsm_conv_workspace_bytes(d) > B.NOALLOC_SCRATCH_BYTES
+    y = empty_act((N, T, Cout, H, H), "f32", "nthwc")
+    s1, s2 = (torch.empty(Cout, dtype=torch.float32, device="cuda") for _ in range(2))
+    B.tsm_conv_fwd_noalloc(d, to_dev(x, "f32", "nthwc"), dev_vec(w), y, s1, s2)
+    ref = O.conv_fwd(x.astype(np.float64), w.astype(np.float64), 1, 1, 8)
+    got = from_dev(y, "nthwc")
+    compare_act(got, ref, 1e-4, "noalloc", "f32")
+    assert np.allclose(s1.cpu().numpy(), got.sum(axis=(0, 1, 3, 4)), rtol=1e-4, atol=1e-4)
