@@ -44,11 +44,30 @@ static inline bool use_gen(const ConvP& p, int dtype, const Arena& ws) {
     return !use_mfma(p, dtype) && !ws.lean && gen_conv_supported(p);
 }
 
+// Shift groups whose border splits a 16-byte vector of channels: the forward and weight-gradient kernels, which gather
+// whole vectors, then read S(x) from the workspace, written by the stand-alone shift, instead of putting every such
+// vector together from up to three masked loads per tap.
+static bool shift_first(ConvP* p, int dtype, const Arena& ws) {
+    const int ve = dtype == TSM_F32 ? 4 : 8;
+    if (use_mfma(*p, dtype) || ws.lean || p->fold == 0 || p->fold % ve == 0 || p->Cin % ve != 0 || !gen_conv_supported(*p)) return false;
+    p->fold = 0;
+    return true;
+}
+static int shifted_copy(const ConvP& p, int dtype, const void** x, Arena& ws, bool dry, hipStream_t s) {
+    const int es = (int)dtype_size(dtype);
+    void* xs = ws.take((size_t)p.rows_in() * p.Cin * es);
+    RUN(shift_launch(*x, xs, p.F / p.T, p.T, p.Cin, p.H, p.W, p.fold, es, TSM_NTHWC, 1, s));
+    *x = xs;
+    return TSM_OK;
+}
+
 // ---- internal conv runners (channels-innermost) -----------------------------------------
 // Rows of the statistics partial buffer run_conv_fwd fills for this convolution.
-int conv_stats_blocks(const ConvP& p, int dtype, const Arena& ws) {
+int conv_stats_blocks(const ConvP& p0, int dtype, const Arena& ws) {
+    ConvP p = p0;
+    shift_first(&p, dtype, ws);
     if (use_mfma(p, dtype)) return conv_mfma_fwd_blocks(p);
-    return use_gen(p, dtype, ws) ? gen_fwd_blocks(p) : red_blocks(p.rows_out(), p.Cout, dtype);
+    return use_gen(p, dtype, ws) ? gen_fwd_blocks(p, dtype) : red_blocks(p.rows_out(), p.Cout, dtype);
 }
 
 // Weights in the order a general kernel reads: packed into the workspace, or the caller's own where they are in it.
@@ -63,8 +82,10 @@ static int gen_weights(const ConvP& p, int dtype, bool dgrad, const void* w, con
 }
 
 // stats_partial: fp32 [conv_stats_blocks(p, dtype, ws)][2*Cout] or null.
-int run_conv_fwd(const ConvP& p, int dtype, const void* x, const void* w, const bf16_t* wp, void* y,
+int run_conv_fwd(const ConvP& p0, int dtype, const void* x, const void* w, const bf16_t* wp, void* y,
                  float* stats_partial, Arena& ws, bool dry, hipStream_t s) {
+    ConvP p = p0;
+    if (shift_first(&p, dtype, ws)) TSM_TRY(shifted_copy(p0, dtype, &x, ws, dry, s));
     if (use_mfma(p, dtype)) {
         if (!wp) {
             bf16_t* pk = ws.take_n<bf16_t>((size_t)p.Cout * p.K());
@@ -83,11 +104,18 @@ int run_conv_fwd(const ConvP& p, int dtype, const void* x, const void* w, const 
     return TSM_OK;
 }
 
-int conv_dgrad_fuse_blocks(const ConvP& p, int dtype) { return use_mfma(p, dtype) ? conv_mfma_dgrad_blocks(p) : 0; }
+// fp32: the K-split kernels carry the same fused epilogue, on whole vectors of one shift group.
+static bool fuse_f32(const ConvP& p, int dtype) {
+    return dtype == TSM_F32 && gen_conv_supported(p) && ksplit_use(p, dtype, true) && p.fold % 4 == 0;
+}
+int conv_dgrad_fuse_blocks(const ConvP& p, int dtype) {
+    if (fuse_f32(p, dtype)) return ksplit_rows(p, dtype, true);
+    return use_mfma(p, dtype) ? conv_mfma_dgrad_blocks(p) : 0;
+}
 
 int run_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* w, const bf16_t* wd, void* dx,
                    const void* addend, const DgradFuse* fuse, Arena& ws, bool dry, hipStream_t s, int addend_stride) {
-    if (fuse && !use_mfma(p, dtype)) return fail(TSM_ERR_UNSUPPORTED, "dgrad: no fused path for this layer");
+    if (fuse && !use_mfma(p, dtype) && !fuse_f32(p, dtype)) return fail(TSM_ERR_UNSUPPORTED, "dgrad: no fused path for this layer");
     if (addend_stride != 1 && !use_mfma(p, dtype)) return fail(TSM_ERR_UNSUPPORTED, "dgrad: no compact addend for this layer");
     if (use_mfma(p, dtype)) {
         if (!wd) {
@@ -99,15 +127,20 @@ int run_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* w, con
     } else if (use_gen(p, dtype, ws)) {
         const void* gw;
         TSM_TRY(gen_weights(p, dtype, true, w, &gw, ws, dry, s));
-        RUN(gen_conv_dgrad(p, dtype, dy, gw, dx, addend, s));
+        if (fuse)
+            RUN(ksplit_dgrad(p, dtype, dy, gw, dx, addend, 1, fuse, s));
+        else
+            RUN(gen_conv_dgrad(p, dtype, dy, gw, dx, addend, s));
     } else {
         RUN(conv_direct_dgrad(p, dtype, dy, w, dx, addend, s));
     }
     return TSM_OK;
 }
 
-int run_conv_wgrad(const ConvP& p, int dtype, const void* x, const void* dy, float* dw, float* dwp_zeroed, int accumulate,
+int run_conv_wgrad(const ConvP& p0, int dtype, const void* x, const void* dy, float* dw, float* dwp_zeroed, int accumulate,
                    Arena& ws, bool dry, hipStream_t s) {
+    ConvP p = p0;
+    if (shift_first(&p, dtype, ws)) TSM_TRY(shifted_copy(p0, dtype, &x, ws, dry, s));
     // all kernels add with atomics; "accumulate" skips the zero fill of dw
     const size_t n = (size_t)p.Cout * p.K();
     if (use_mfma(p, dtype) && p.taps() > 1 && dwp_zeroed) {
@@ -765,6 +798,11 @@ static int block_entry(bool bwd, const tsm_block_desc* d, const void* x, const v
     const char* who = bwd ? "tsm_block_bwd" : "tsm_block_fwd";
     BlockPlan b;
     TSM_TRY(make_block_plan(d, &b, who));
+    // A single block's weight gradients and shortcut run beside its data gradients on CUs that the wider tiles leave to them:
+    // 512 -> 256 -> 1024 on 24 frames of 27 x 35 takes 432 us as it is and 456 with the K-split kernels, although the two
+    // convolutions they would take get shorter (26.5 -> 22.9, 17.4 -> 16.2 us).
+    for (StageDef& st : b.st) st.p.whole_k = true;
+    b.ds.p.whole_k = true;
     const bool tr = d->layout == TSM_NTCHW;
     if (!dry) {
         if (!prm) return fail(TSM_ERR_NULLPTR, "%s: null params", who);

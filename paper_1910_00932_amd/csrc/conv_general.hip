@@ -10,9 +10,10 @@
 // enough and tiles are chosen for how well they fill the last round.
 //
 // Against one thread per output element (1.2 TFLOP/s whatever the layer; those kernels are kept in direct.hip for strides
-// beyond 2 and filters beyond 8): fp32 train step at 4 clips of 8 x 224^2 655 -> 16.1 ms; fp32 64-channel basic block at
-// 2 clips of 8 x 14^2, forward and backward, 1077 -> 201 us; bf16 72 -> 200 channels 3x3 at 4 clips of 8 x 29^2, all
-// three directions, 17.7 ms -> 211 us.
+// beyond 2 and filters beyond 8): fp32 train step at 4 clips of 8 x 224^2 655 -> 16.1 ms; bf16 72 -> 200 channels 3x3 at
+// 4 clips of 8 x 29^2, all three directions, 17.7 ms -> 211 us.  Forward and data gradients have since moved to
+// conv_ksplit.hip (12.9 ms and 157 us) except where channel counts are no multiple of a 16-byte vector or a tensor
+// exceeds the 2 GiB of a buffer's offsets; the weight gradients are here.
 //
 // The shift is index arithmetic as in conv_mfma.hip.  A 16-byte vector of channels that straddles two shift groups is
 // put together from one masked load per group; where rows are not 16-byte aligned (channel counts that are no multiple
@@ -616,7 +617,8 @@ static int gen_launch(GenArgs& a, hipStream_t s) {
     return check_launch(DGRAD ? "gen_dgrad_bf16" : "gen_fwd_bf16");
 }
 
-int gen_fwd_blocks(const ConvP& p) {
+int gen_fwd_blocks(const ConvP& p, int dtype) {
+    if (ksplit_use(p, dtype, false)) return ksplit_rows(p, dtype, false);
     const int bm = gen_tile(p.rows_out(), p.Cout).bm;
     return (int)((p.rows_out() + bm - 1) / bm);
 }
@@ -628,6 +630,7 @@ static void gen_common(GenArgs& a, const ConvP& p) {
 
 int gen_conv_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void* y, float* stats, hipStream_t s) {
     if (p.rows_out() == 0) return TSM_OK;
+    if (ksplit_use(p, dtype, false)) return ksplit_fwd(p, dtype, x, wp, y, stats, nullptr, s);
     GenArgs a;
     gen_common(a, p);
     a.src = x; a.wp = wp; a.dst = y; a.stats = stats;
@@ -642,6 +645,7 @@ int gen_conv_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void*
 
 int gen_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* wd, void* dx, const void* addend, hipStream_t s) {
     if (p.rows_in() == 0) return TSM_OK;
+    if (ksplit_use(p, dtype, true)) return ksplit_dgrad(p, dtype, dy, wd, dx, addend, 1, nullptr, s);
     GenArgs a;
     gen_common(a, p);
     a.src = dy; a.wp = wd; a.dst = dx; a.addend = addend;

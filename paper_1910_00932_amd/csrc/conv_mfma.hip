@@ -2546,6 +2546,7 @@ static void ring_tile(const IgemmArgs& a, int* bm, int* bn) {
 // 24 (64 clips) this one saves 1.1 % of the step.  TSM_CONV3X3_C64=0 leaves these layers to the general kernel,
 // TSM_CONV3X3_C64_MIN_TILES=<n> moves the threshold (both read at every call: tests and comparisons set them).
 static bool c64_eligible(const IgemmArgs& a) {
+    if (a.Cs != 64 || a.Cd != 64 || a.KH != 3) return false;
     const char* e = getenv("TSM_CONV3X3_C64");
     const bool enabled = !(e && e[0] == '0');
     const char* t = getenv("TSM_CONV3X3_C64_MIN_TILES");
@@ -2792,13 +2793,13 @@ static int launch_stem_s(IgemmArgs& a, hipStream_t s) {
 // the grid forms.)
 static int pw_block_channels(int Cs) { return Cs <= 128 ? 256 : 128; }
 static bool pw_shape_ok(const IgemmArgs& a) {
-    const char* e = getenv("TSM_PW_KERNEL");
-    if (e && e[0] == '0') return false;
     if (!((a.Cs == 64 || a.Cs == 128 || a.Cs == 256) && a.pitch == a.Cs && a.KT == 1 && a.KH == 1 && a.KW == 1 && a.stride == 1 &&
           a.padh == 0 && a.padw == 0 && a.Hs == a.Hd && a.Ws == a.Wd))
         return false;
     const int nb = pw_block_channels(a.Cs);
     if (a.Cd < 256 || a.Cd > 1024 || a.Cd % nb != 0 || a.Cd < 2 * a.Cs) return false;     // wide results only
+    const char* e = getenv("TSM_PW_KERNEL");
+    if (e && e[0] == '0') return false;
     const long rows = (long)a.F * a.Hd * a.Wd;
     const char* t = getenv("TSM_PW_MIN_ROWS");
     const long min_rows = t ? atol(t) : 32L * 8 * num_cu() / (a.Cd / nb);
@@ -2860,6 +2861,7 @@ static int launch_pw_dgrad(IgemmArgs& a, hipStream_t s) {
 // (measured: better from 148 tiles on, worse at 98).  TSM_IGEMM_WIDE=0 (read at every call) keeps 128 columns, TSM_IGEMM_WIDE_MIN_TILES=<n> replaces the number
 // of wide tiles from which they are chosen (tests and comparisons set them).
 static bool wide_fwd_eligible(const IgemmArgs& a) {
+    if (a.Cd % 256 != 0) return false;
     const char* e = getenv("TSM_IGEMM_WIDE");
     if (e && e[0] == '0') return false;
     const char* t = getenv("TSM_IGEMM_WIDE_MIN_TILES");
@@ -2921,6 +2923,7 @@ static int dispatch_igemm(IgemmArgs& a, hipStream_t s) {
     return launch_igemm<128, 128, 2, 2, DGRAD, 1, 2>(a, DGRAD ? "igemm_dgrad_128x128" : "igemm_fwd_128x128", s);
 }
 
+static void dgrad_args(const ConvP& p, IgemmArgs& a);
 static void fwd_args(const ConvP& p, IgemmArgs& a) {
     a.F = p.F; a.T = p.T;
     a.Hs = p.H; a.Ws = p.W; a.Cs = p.Cin; a.pitch = p.pix_pitch();
@@ -2931,8 +2934,24 @@ static void fwd_args(const ConvP& p, IgemmArgs& a) {
     a.K = (int)p.K();
 }
 
+// Layers the K-split kernels take over (see ksplit_use): none that a kernel of its own may take.  A function of the
+// shape alone, so that callers size the rows of the partial buffers by it.
+static bool fwd_ksplit(const ConvP& p) {
+    if (!ksplit_use(p, TSM_BF16, false)) return false;
+    IgemmArgs a = {};
+    fwd_args(p, a);
+    return !c64_eligible(a) && !pw_shape_ok(a) && !wide_fwd_eligible(a);
+}
+static bool dgrad_ksplit(const ConvP& p) {
+    if (!ksplit_use(p, TSM_BF16, true)) return false;
+    IgemmArgs a = {};
+    dgrad_args(p, a);
+    return !c64_eligible(a) && !pw_shape_ok(a);
+}
+
 // Blocks the forward convolution with the statistics epilogue launches (= partial rows it writes).
 int conv_mfma_fwd_blocks(const ConvP& p) {
+    if (fwd_ksplit(p)) return ksplit_rows(p, TSM_BF16, false);
     const int bn = p.Cout <= 64 ? 64 : 128;
     {
         IgemmArgs a;
@@ -2949,12 +2968,14 @@ int conv_mfma_fwd_blocks(const ConvP& p) {
 }
 
 bool conv_mfma_fwd_can_fuse(const ConvP& p) {
+    if (fwd_ksplit(p)) return true;
     return ring_eligible(p.Cin, p.rows_in() * (long)p.pix_pitch() + p.Cin + (long)(p.pad * p.W + p.pad) * p.pix_pitch(), (long)p.Cout * p.K(),
                          p.pix_pitch() != p.Cin);
 }
 
 int conv_mfma_fwd(const ConvP& p, const bf16_t* x, const bf16_t* wp, bf16_t* y, float* stats, const FwdEpilogue* ep,
                   hipStream_t s) {
+    if (fwd_ksplit(p)) return ksplit_fwd(p, TSM_BF16, x, wp, y, stats, ep, s);
     IgemmArgs a;
     a.src = x; a.wp = wp; a.dst = y; a.addend = nullptr; a.add_stride = 1; a.add_ho = a.add_wo = 0; a.stats = stats;
     a.act = nullptr; a.ybn = nullptr; a.bn_mean = nullptr; a.bn_rstd = nullptr; a.act_bits = nullptr;
@@ -2978,6 +2999,7 @@ static void dgrad_args(const ConvP& p, IgemmArgs& a) {
 }
 
 int conv_mfma_dgrad_blocks(const ConvP& p) {
+    if (dgrad_ksplit(p)) return ksplit_rows(p, TSM_BF16, true);
     IgemmArgs a;
     dgrad_args(p, a);
     if (!ring_eligible(a.Cs, (long)a.F * a.Hs * a.Ws * a.pitch + a.Cs + (long)(a.padh * a.Ws + a.padw) * a.pitch, (long)a.Cd * a.K, a.pitch != a.Cs)) return 0;
@@ -2992,6 +3014,7 @@ bool conv_mfma_dgrad_compact_addend_ok(const ConvP& p) { return conv_mfma_dgrad_
 
 int conv_mfma_dgrad(const ConvP& p, const bf16_t* dy, const bf16_t* wd, bf16_t* dx, const bf16_t* addend,
                     const DgradFuse* fuse, hipStream_t s, int addend_stride) {
+    if (dgrad_ksplit(p)) return ksplit_dgrad(p, TSM_BF16, dy, wd, dx, addend, addend_stride, fuse, s);
     IgemmArgs a;
     a.src = dy; a.wp = wd; a.dst = dx; a.addend = addend; a.stats = nullptr;
     a.add_stride = 1; a.add_ho = a.add_wo = 0;

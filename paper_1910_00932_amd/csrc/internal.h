@@ -17,6 +17,8 @@ struct ConvP {
     // overlap the following pixels: a convolution whose taps along W are folded into the channel dimension
     // (MFMA kernels with Cin % 64 == 0 only; the caller guarantees that every read stays inside the tensor).
     int pitch = 0;
+    // bf16: keeps the layer on the kernels that sum the whole K range of a result in one wavefront (see ksplit_use).
+    bool whole_k = false;
     int pix_pitch() const { return pitch ? pitch : Cin; }
     long rows_in() const { return (long)F * H * W; }
     long rows_out() const { return (long)F * Ho * Wo; }
@@ -43,7 +45,7 @@ bool gen_conv_supported(const ConvP& p);
 // Elements (of dtype) of the packed weights of each direction; 0: the ABI order is what the kernel reads.
 size_t gen_pack_elems(const ConvP& p, int dtype, bool dgrad);
 int gen_pack_weights(const ConvP& p, int dtype, bool dgrad, const void* w, void* out, hipStream_t s);
-int gen_fwd_blocks(const ConvP& p);   // rows of gen_conv_fwd's statistics partial buffer
+int gen_fwd_blocks(const ConvP& p, int dtype);   // rows of gen_conv_fwd's statistics partial buffer
 int gen_conv_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void* y, float* stats_partial, hipStream_t s);
 int gen_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* wd, void* dx, const void* addend, hipStream_t s);
 // dw fp32 is added to; packed: [Cout][taps][Cin], otherwise the ABI order.
@@ -163,5 +165,15 @@ int conv_mfma_dgrad(const ConvP& p, const bf16_t* dy, const bf16_t* wd, bf16_t* 
 bool conv_mfma_wgrad_affine_ok(const ConvP& p);
 int conv_mfma_wgrad(const ConvP& p, const bf16_t* x, const bf16_t* dy, float* dw, int cin_real, bool packed,
                     hipStream_t s, const bf16_t* affine_y = nullptr, const float* affine_coef = nullptr);
+
+// ---- conv_ksplit.hip: implicit GEMM with the K range split over the wavefronts of a block -----------------------------
+// Which layers of the two sets of kernels above it takes over, and the rows of the partial buffer it then writes
+// (statistics, or the sums of a fused data gradient).  Weights are packed as for those kernels.
+bool ksplit_use(const ConvP& p, int dtype, bool dgrad);
+int ksplit_rows(const ConvP& p, int dtype, bool dgrad);
+int ksplit_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void* y, float* stats_partial, const FwdEpilogue* ep,
+               hipStream_t s);
+int ksplit_dgrad(const ConvP& p, int dtype, const void* dy, const void* wd, void* dx, const void* addend, int addend_stride,
+                 const DgradFuse* fuse, hipStream_t s);
 
 }  // namespace tsm
