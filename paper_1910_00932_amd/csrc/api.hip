@@ -94,8 +94,8 @@ int run_conv_fwd(const ConvP& p0, int dtype, const void* x, const void* w, const
         }
         RUN(conv_mfma_fwd(p, (const bf16_t*)x, wp, (bf16_t*)y, stats_partial, nullptr, s));
     } else if (use_gen(p, dtype, ws)) {
-        const void* gw;
-        TSM_TRY(gen_weights(p, dtype, false, w, &gw, ws, dry, s));
+        const void* gw = wp;
+        if (!gw) TSM_TRY(gen_weights(p, dtype, false, w, &gw, ws, dry, s));
         RUN(gen_conv_fwd(p, dtype, x, gw, y, stats_partial, s));
     } else {
         RUN(conv_direct_fwd(p, dtype, x, w, y, s));
@@ -125,8 +125,8 @@ int run_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* w, con
         }
         RUN(conv_mfma_dgrad(p, (const bf16_t*)dy, wd, (bf16_t*)dx, (const bf16_t*)addend, fuse, s, addend_stride));
     } else if (use_gen(p, dtype, ws)) {
-        const void* gw;
-        TSM_TRY(gen_weights(p, dtype, true, w, &gw, ws, dry, s));
+        const void* gw = wd;
+        if (!gw) TSM_TRY(gen_weights(p, dtype, true, w, &gw, ws, dry, s));
         if (fuse)
             RUN(ksplit_dgrad(p, dtype, dy, gw, dx, addend, 1, fuse, s));
         else
@@ -143,12 +143,16 @@ int run_conv_wgrad(const ConvP& p0, int dtype, const void* x, const void* dy, fl
     if (shift_first(&p, dtype, ws)) TSM_TRY(shifted_copy(p0, dtype, &x, ws, dry, s));
     // all kernels add with atomics; "accumulate" skips the zero fill of dw
     const size_t n = (size_t)p.Cout * p.K();
-    if (use_mfma(p, dtype) && p.taps() > 1 && dwp_zeroed) {
-        // the caller owns a zeroed packed buffer and permutes it into dw later (one fill / one permutation per step)
-        RUN(conv_mfma_wgrad(p, (const bf16_t*)x, (const bf16_t*)dy, dwp_zeroed, p.Cin, true, s));
+    const bool gen = use_gen(p, dtype, ws);
+    if (p.taps() > 1 && dwp_zeroed && (use_mfma(p, dtype) || (gen && !accumulate))) {
+        // the caller owns a zeroed packed buffer; accumulating, it permutes it into dw later (one permutation per step)
+        if (gen)
+            RUN(gen_conv_wgrad(p, dtype, x, dy, dwp_zeroed, true, s));
+        else
+            RUN(conv_mfma_wgrad(p, (const bf16_t*)x, (const bf16_t*)dy, dwp_zeroed, p.Cin, true, s));
+        if (!accumulate) RUN(unpack_wgrad(dwp_zeroed, dw, p.Cout, p.Cin, p.taps(), p.Cin, 0, s));
         return TSM_OK;
     }
-    const bool gen = use_gen(p, dtype, ws);
     if ((gen || use_mfma(p, dtype)) && p.taps() > 1) {
         // several taps: accumulate in the packed order (contiguous atomics), then permute into dw
         float* dwp = ws.take_n<float>(n);
@@ -168,6 +172,19 @@ int run_conv_wgrad(const ConvP& p0, int dtype, const void* x, const void* dy, fl
     else
         RUN(conv_direct_wgrad(p, dtype, x, dy, dw, s));
     return TSM_OK;
+}
+
+// Adds the packing of a stand-alone block's weights to its preparation; null where the kernel reads them as they are.
+static void* prep_pack(BlockPrep& prep, const ConvP& p0, int dtype, bool dgrad, const void* w, Arena& ws) {
+    ConvP p = p0;
+    if (!dgrad) shift_first(&p, dtype, ws);
+    size_t n = 0;
+    if (use_mfma(p, dtype)) n = (size_t)p.Cout * p.K();
+    else if (use_gen(p, dtype, ws)) n = gen_pack_elems(p, dtype, dgrad);
+    if (n == 0) return nullptr;
+    void* out = ws.take(n * dtype_size(dtype));
+    prep.pack(p, (int)(n / ((size_t)(dgrad ? p.Cin : p.Cout) * p.taps())), dgrad, w, out);
+    return out ? out : (void*)16;   // (dry run: only the flag matters)
 }
 
 // ---- conv entry points -------------------------------------------------------------------
@@ -505,6 +522,7 @@ static int block_infer_entry(const tsm_block_desc* d, const void* x, const tsm_b
     void* ytmp = ws.take(out_bytes);
     void* scbuf = ws.take(out_bytes);
     InferParams ip{};
+    BlockPrep prep;
     const StageDef* sds[4] = {&b.st[0], &b.st[1], b.nst == 3 ? &b.st[2] : nullptr, b.proj ? &b.ds : nullptr};
     const float* mean[4] = {dry ? nullptr : st->m1, dry ? nullptr : st->m2, dry ? nullptr : st->m3, dry ? nullptr : st->md};
     const float* var[4] = {dry ? nullptr : st->v1, dry ? nullptr : st->v2, dry ? nullptr : st->v3, dry ? nullptr : st->vd};
@@ -513,15 +531,12 @@ static int block_infer_entry(const tsm_block_desc* d, const void* x, const tsm_b
         const ConvP& p = sds[i]->p;
         float* sc = ws.take_n<float>(p.Cout);
         float* sh = ws.take_n<float>(p.Cout);
-        RUN(bn_eval_vec(sds[i]->g, sds[i]->b, mean[i], var[i], d->bn_eps, p.Cout, sc, sh, s));
+        prep.affine(sds[i]->g, sds[i]->b, mean[i], var[i], sc, sh, p.Cout);
         ip.sc[i] = sc;
         ip.sh[i] = sh;
-        if (use_mfma(p, d->dtype)) {
-            bf16_t* pk = ws.take_n<bf16_t>((size_t)p.Cout * p.K());
-            RUN(pack_weights_fwd(d->dtype, sds[i]->w, pk, p.Cout, p.Cin, p.taps(), p.Cin, s));
-            ip.wp[i] = pk;
-        }
+        ip.wp[i] = (const bf16_t*)prep_pack(prep, p, d->dtype, false, sds[i]->w, ws);
     }
+    RUN(block_prep(d->dtype, prep, d->bn_eps, s));
     const void* xi = x;
     void* oi = out;
     if (tr) {
@@ -599,7 +614,7 @@ static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const vo
     float* partL = ws.take_n<float>((size_t)nbL * 2 * pl.Cout);
     float* partd = ws.take_n<float>((size_t)nbL * 2 * pl.Cout);
     float* coefL = ws.take_n<float>(3 * (size_t)pl.Cout);
-    const int acc_flag = b.grads_prezeroed ? 1 : 0;
+    auto acc_flag = [&](const StageDef& st) { return b.grads_prezeroed && !(b.unpack_here && st.dwp) ? 1 : 0; };
     if (chained) {
         dzL = const_cast<void*>(dout);
         partL = const_cast<float*>(b.dout_part);
@@ -667,7 +682,7 @@ static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const vo
     for (int i = L; i >= 1; --i) {
         StageDef& st = b.st[i];
         const ConvP& pp = b.st[i - 1].p;  // producer of this stage's input
-        TSM_TRY(wgrad_beside(ss, &forked, st.p, b.dtype, b.z[i - 1], g, st.dw, st.dwp, acc_flag, ws, dry, s));
+        TSM_TRY(wgrad_beside(ss, &forked, st.p, b.dtype, b.z[i - 1], g, st.dw, st.dwp, acc_flag(st), ws, dry, s));
         if (i == L && b.proj) TSM_TRY(shortcut_dgrad());
         void* dzin = ws.take((size_t)pp.rows_out() * pp.Cout * es);
         // the ReLU mask and the BatchNorm reductions of the producing stage ride in the data gradient's
@@ -689,10 +704,10 @@ static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const vo
         RUN(bn_bwd_apply(b.dtype, dzin, b.y[i - 1], pp.rows_out(), pp.Cout, coef, dzin, s));
         g = dzin;
     }
-    TSM_TRY(wgrad_beside(ss, &forked, b.st[0].p, b.dtype, x, g, b.st[0].dw, b.st[0].dwp, acc_flag, ws, dry, s));
+    TSM_TRY(wgrad_beside(ss, &forked, b.st[0].p, b.dtype, x, g, b.st[0].dw, b.st[0].dwp, acc_flag(b.st[0]), ws, dry, s));
     if (b.proj) {
         StageDef& st = b.ds;
-        TSM_TRY(wgrad_beside(ss, &forked, st.p, b.dtype, x, dyd, st.dw, st.dwp, acc_flag, ws, dry, s));
+        TSM_TRY(wgrad_beside(ss, &forked, st.p, b.dtype, x, dyd, st.dw, st.dwp, acc_flag(st), ws, dry, s));
         if (branch_open && hipStreamWaitEvent(s, ss->branch, 0) != hipSuccess)
             return fail(TSM_ERR_LAUNCH, "block backward: cannot wait for the side stream");
     }
@@ -832,6 +847,11 @@ static int block_entry(bool bwd, const tsm_block_desc* d, const void* x, const v
             xi = b.x_copy;
             oi = b.out_copy;
         }
+        BlockPrep prep;
+        auto pack = [&](StageDef& st) { st.wp = (const bf16_t*)prep_pack(prep, st.p, d->dtype, false, st.w, ws); };
+        for (int i = 0; i < b.nst; ++i) pack(b.st[i]);
+        if (b.proj) pack(b.ds);
+        RUN(block_prep(d->dtype, prep, 0.f, s));
         TSM_TRY(block_fwd_impl(b, xi, oi, ws, dry, s));
         if (tr) RUN(transpose_frames(oi, out, pl.F, pl.Ho * pl.Wo, pl.Cout, es, s));
     } else {
@@ -845,6 +865,25 @@ static int block_entry(bool bwd, const tsm_block_desc* d, const void* x, const v
             di = dt;
             dxi = ws.take((size_t)p0.rows_in() * p0.Cin * es);
         }
+        BlockPrep prep;
+        auto ready = [&](StageDef& st) {
+            ConvP p = st.p;
+            // (a strided projection's data gradient runs on its output grid, with the same weights)
+            st.wd = (const bf16_t*)prep_pack(prep, p, d->dtype, true, st.w, ws);
+            shift_first(&p, d->dtype, ws);
+            const long n = (long)p.Cout * p.K();
+            if (p.taps() > 1 && (use_mfma(p, d->dtype) || use_gen(p, d->dtype, ws))) {
+                st.dwp = ws.take_n<float>((size_t)n);
+                prep.fill(st.dwp, n);
+                if (dry) st.dwp = (float*)16;
+            } else {
+                prep.fill(st.dw, n);
+            }
+        };
+        for (int i = 0; i < b.nst; ++i) ready(b.st[i]);
+        if (b.proj) ready(b.ds);
+        b.grads_prezeroed = b.unpack_here = true;
+        RUN(block_prep(d->dtype, prep, 0.f, s));
         TSM_TRY(block_bwd_impl(b, xi, oi, di, dxi, ws, dry, s));
         if (tr) RUN(transpose_frames(dxi, dx, p0.F, p0.H * p0.W, p0.Cin, es, s));
     }

@@ -25,6 +25,7 @@ struct BlockPlan {
     int dtype;
     float eps, bn_momentum;
     bool grads_prezeroed;  // the caller zeroed every dw: weight gradients are added without a fill
+    bool unpack_here;      // (with grads_prezeroed) a dwp is permuted into its dw, which need not be zero, right away
     // Chaining inside a network (both optional).  dout_part: the gradient handed to block_bwd_impl is already
     // masked with out > 0 and the BatchNorm sums of the last stage are in dout_part, dout_nb rows (the
     // producer was a fused data gradient).  dx_fuse: applied to the data gradient that produces dx.

@@ -238,24 +238,6 @@ int bn_finalize(const float* partial, int nblocks, long rows, int C, const float
     return check_launch("bn_finalize");
 }
 
-// Inference-mode BatchNorm as an affine map: scale = gamma / sqrt(var + eps), shift = beta - mean * scale.
-__global__ void __launch_bounds__(256) bn_eval_vec_kernel(const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                          const float* __restrict__ mean, const float* __restrict__ var,
-                                                          float eps, int C, float* __restrict__ scale,
-                                                          float* __restrict__ shift) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= C) return;
-    const float sc = gamma[c] / sqrtf(var[c] + eps);
-    scale[c] = sc;
-    shift[c] = fmaf(-mean[c], sc, beta[c]);
-}
-
-int bn_eval_vec(const float* gamma, const float* beta, const float* mean, const float* var, float eps, int C,
-                float* scale, float* shift, hipStream_t s) {
-    bn_eval_vec_kernel<<<dim3(cdiv(C, 256)), dim3(256), 0, s>>>(gamma, beta, mean, var, eps, C, scale, shift);
-    return check_launch("bn_eval_vec");
-}
-
 __global__ void __launch_bounds__(SP_C * SP_R) stats_to_float_kernel(const float* __restrict__ partial, int nblocks, int C, float* sum, float* sumsq) {
     const int c = blockIdx.x * SP_C + threadIdx.x;
     double s1, s2;
@@ -631,6 +613,64 @@ int pack_weights_dgrad(int dtype, const void* w, bf16_t* out, int Cout, int Cin,
     else
         pack_dgrad_kernel<bf16_t><<<dim3(cdiv(n, 256)), dim3(256), 0, s>>>((const bf16_t*)w, out, Cout, Cin, KT, KH, KW);
     return check_launch("pack_weights_dgrad");
+}
+
+// A block's weights are a few megabytes: what a launch of its own costs each of them is the launch (serving one res4 block
+// of 8 clips: three maps and three packings in six launches of 80 us, 15 us of it in front of the first convolution).
+static constexpr int PREP_PER_BLOCK = 1024;
+template <typename T>
+__global__ void __launch_bounds__(256) block_prep_kernel(BlockPrep t, float eps) {
+    if (blockIdx.x >= t.blocks) {   // one thread block per BatchNorm behind the items
+        const BlockPrep::Bn& b = t.bn[blockIdx.x - t.blocks];
+        for (int c = threadIdx.x; c < b.C; c += 256) {
+            const float sc = b.gamma[c] / sqrtf(b.var[c] + eps);
+            b.scale[c] = sc;
+            b.shift[c] = fmaf(-b.mean[c], sc, b.beta[c]);
+        }
+        return;
+    }
+    int l = 0;
+    while (l + 1 < t.nitem && blockIdx.x >= t.item[l + 1].first) ++l;
+    const BlockPrep::Item& it = t.item[l];
+    const long i0 = (long)(blockIdx.x - it.first) * PREP_PER_BLOCK + threadIdx.x;
+    const int taps = it.KT * it.KH * it.KW;
+#pragma unroll
+    for (int u = 0; u < PREP_PER_BLOCK / 256; ++u) {
+        const long i = i0 + u * 256;
+        if (i >= it.total) return;
+        if (it.in == nullptr) {
+            ((uint32_t*)it.out)[i] = 0u;
+            continue;
+        }
+        const unsigned row = (unsigned)(i / it.CP);
+        const int c = (int)(i - (long)row * it.CP), tap = (int)(row % (unsigned)taps), n = (int)(row / (unsigned)taps);
+        const int co = it.dgrad ? c : n, ci = it.dgrad ? n : c;
+        T v = Elem<T>::st(0.f);
+        if (c < (it.dgrad ? it.Cout : it.Cin)) v = ((const T*)it.in)[((long)co * it.Cin + ci) * taps + (it.dgrad ? taps - 1 - tap : tap)];
+        ((T*)it.out)[i] = v;
+    }
+}
+
+void BlockPrep::pack(const ConvP& p, int CP, bool dgrad, const void* w, void* out) {
+    Item& it = item[nitem++];
+    it = Item{w, out, (long)(dgrad ? p.Cin : p.Cout) * p.taps() * CP, p.Cout, p.Cin, p.KT, p.KH, p.KW, CP, dgrad ? 1 : 0, blocks};
+    blocks += (unsigned)((it.total + PREP_PER_BLOCK - 1) / PREP_PER_BLOCK);
+}
+void BlockPrep::fill(void* out, long words) {
+    Item& it = item[nitem++];
+    it = Item{nullptr, out, words, 0, 0, 1, 1, 1, 1, 0, blocks};
+    blocks += (unsigned)((words + PREP_PER_BLOCK - 1) / PREP_PER_BLOCK);
+}
+void BlockPrep::affine(const float* gamma, const float* beta, const float* mean, const float* var, float* scale, float* shift, int C) {
+    bn[nbn++] = Bn{gamma, beta, mean, var, scale, shift, C};
+}
+
+int block_prep(int dtype, const BlockPrep& t, float eps, hipStream_t s) {
+    const unsigned grid = t.blocks + (unsigned)t.nbn;
+    if (grid == 0) return TSM_OK;
+    if (dtype == TSM_F32) block_prep_kernel<float><<<dim3(grid), dim3(256), 0, s>>>(t, eps);
+    else block_prep_kernel<bf16_t><<<dim3(grid), dim3(256), 0, s>>>(t, eps);
+    return check_launch("block_prep");
 }
 
 __global__ void __launch_bounds__(256) unpack_wgrad_kernel(const float* __restrict__ packed, float* __restrict__ dw,

@@ -67,9 +67,6 @@ struct BnVec {           // per-channel fp32 vectors of one BatchNorm, each [C]
 int bn_finalize(const float* partial, int nblocks, long rows, int C, const float* gamma, const float* beta,
                 float eps, BnVec out, float* run_mean, float* run_var, float momentum, hipStream_t s);
 int stats_to_float(const float* partial, int nblocks, int C, float* sum, float* sumsq, hipStream_t s);
-// scale = gamma / sqrt(var + eps), shift = beta - mean * scale (BatchNorm with known statistics)
-int bn_eval_vec(const float* gamma, const float* beta, const float* mean, const float* var, float eps, int C,
-                float* scale, float* shift, hipStream_t s);
 // z = relu(scale*y + shift)
 int bn_relu_apply(int dtype, const void* y, long rows, int C, const float* scale, const float* shift, void* z,
                   hipStream_t s);
@@ -103,6 +100,31 @@ int pack_weights_fwd(int dtype, const void* w, bf16_t* out, int Cout, int Cin, i
 // ABI [Cout][Cin][KT][KH][KW] -> bf16 [Cin][flipped taps][Cout]
 int pack_weights_dgrad(int dtype, const void* w, bf16_t* out, int Cout, int Cin, int KT, int KH, int KW,
                        hipStream_t s);
+// What one stand-alone block has to prepare before its convolutions, in one launch: weights into the order a kernel
+// reads, gradient buffers set to zero, known BatchNorm statistics as
+// affine maps (scale = gamma / sqrt(var + eps), shift = beta - mean * scale).
+struct BlockPrep {
+    struct Item {
+        const void* in;      // pack: weights, ABI order [Cout][Cin][KT][KH][KW]; fill: null
+        void* out;           // pack: [Cout][taps][CP] or, dgrad, [Cin][flipped taps][CP] (channels beyond the last: zero)
+        long total;          // elements of `out` (fill: 4-byte words)
+        int Cout, Cin, KT, KH, KW, CP, dgrad;
+        unsigned first;      // first thread block of the item
+    };
+    struct Bn {
+        const float *gamma, *beta, *mean, *var;
+        float *scale, *shift;
+        int C;
+    };
+    Item item[8];
+    Bn bn[4];
+    int nitem = 0, nbn = 0;
+    unsigned blocks = 0;
+    void pack(const ConvP& p, int CP, bool dgrad, const void* w, void* out);
+    void fill(void* out, long words);
+    void affine(const float* gamma, const float* beta, const float* mean, const float* var, float* scale, float* shift, int C);
+};
+int block_prep(int dtype, const BlockPrep& t, float eps, hipStream_t s);
 // fp32 [Cout][taps][CinP] -> fp32 [Cout][Cin][taps] (+= if accumulate)
 int unpack_wgrad(const float* packed, float* dw, int Cout, int Cin, int taps, int CinP, int accumulate,
                  hipStream_t s);
