@@ -67,6 +67,8 @@ def igemm_class(kind, cd, cs, rows, taps=1, stride=1, affine=False):
             return "igemm_fwd_pw"             # the short-K 1x1 forward kernel (affine epilogue: K = 64 and 256 only)
         if kind == "fwd" and not affine and cd % 256 == 0 and r == "256" and -(-rows // 256) * (cd // 256) * 2 >= 256:
             return "igemm_fwd_256x256"        # wide results: 256-column tiles from half a round on
+        if not (r == "256" and taps == 1 and stride == 1 and pw_layer(cs, cd, rows)) and -(-rows // 64) * -(-cd // 64) <= 2 * 256:
+            return "ksplit_%s_bf16" % kind    # at most two 64 x 64 tiles per CU: the K range split over the wavefronts
         # 64 columns per tile for narrow outputs, and where even 128x128 tiles leave a quarter of the CUs idle
         narrow = cd <= 64 or (r == "r128" and -(-rows // 128) * -(-cd // 128) * 4 < 256 * 3)
         return "igemm_%s_%sx%s" % (kind, r, "64" if narrow else "128")
