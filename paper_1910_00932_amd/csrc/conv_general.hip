@@ -18,6 +18,7 @@
 // The shift is index arithmetic as in conv_mfma.hip.  A 16-byte vector of channels that straddles two shift groups is
 // put together from one masked load per group; where rows are not 16-byte aligned (channel counts that are no multiple
 // of the vector) it is loaded element by element.
+#include <algorithm>
 #include "internal.h"
 
 namespace tsm {
@@ -389,7 +390,7 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
     // buffer and receive zeros, so that no load stands under a condition; the buffer of x starts at the most negative tap
     // origin.
     constexpr uint32_t OOB = 0x80000000u;
-    const uint32_t bias = RAG ? 0u : (uint32_t)((a.pad * a.W + a.pad) * a.Cin) * (uint32_t)sizeof(T);
+    const uint32_t bias = RAG ? 0u : (uint32_t)(((long)a.pad * a.W + a.pad) * a.Cin * (long)sizeof(T));
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.x - bias), 0,
                                                                         (int)((uint32_t)(a.F * (long)a.H * a.W * a.Cin * (long)sizeof(T)) + bias), 0x00020000);
     const __amdgpu_buffer_rsrc_t rdy = __builtin_amdgcn_make_buffer_rsrc((void*)a.dy, 0, (int)(uint32_t)(a.M * a.Cout * (long)sizeof(T)), 0x00020000);
@@ -560,6 +561,7 @@ bool gen_conv_supported(const ConvP& p) {
     if (p.Cin > 65536 || p.Cout > 65536 || (long)p.taps() * (p.Cin + 8) > 0x3fffffffL || (long)p.taps() * (p.Cout + 8) > 0x3fffffffL) return false;
     if (p.rows_in() > 0x3fffffffL || p.rows_out() > 0x3fffffffL) return false;
     if ((long)p.H * p.W * p.Cin > 0x3fffffffL || (long)p.Ho * p.Wo * p.Cout > 0x3fffffffL) return false;
+    if (((long)p.KH * p.W + p.KW) * p.Cin > 0x3fffffffL || ((long)p.KH * p.Wo + p.KW) * p.Cout > 0x3fffffffL) return false;   // offset of a tap
     if ((p.rows_in() / 64 + 40) * ((p.Cin + 63) / 64) > 0x7fffffffL || (p.rows_out() / 64 + 40) * ((p.Cout + 63) / 64) > 0x7fffffffL) return false;
     return true;
 }
@@ -710,8 +712,9 @@ int gen_conv_wgrad(const ConvP& p, int dtype, const void* x, const void* dy, flo
     a.K = p.taps() * a.CinP;
     const int ve = dtype == TSM_F32 ? 4 : 8;
     // (a buffer load's offset stays below 2 GiB)
-    const long es = (long)dtype_size(dtype), limit = 0x7ff00000L, edge = ((long)p.KH * p.W + p.KW) * p.Cin * es;
-    const bool rag = p.Cin % ve || p.Cout % ve || p.fold % ve || p.rows_in() * p.Cin * es + 2 * edge >= limit || p.rows_out() * p.Cout * es >= limit;
+    const long es = (long)dtype_size(dtype), limit = 0x7ff00000L;
+    const long edge = std::max(2 * ((long)p.KH * p.W + p.KW), (long)p.pad * p.W + p.pad) * p.Cin * es;   // taps behind the last pixel, padding before the first
+    const bool rag = p.Cin % ve || p.Cout % ve || p.fold % ve || p.rows_in() * p.Cin * es + edge >= limit || p.rows_out() * p.Cout * es >= limit;
     if (dtype == TSM_F32) return rag ? gen_wgrad_launch<float, true>(a, s) : gen_wgrad_launch<float, false>(a, s);
     return rag ? gen_wgrad_launch<bf16_t, true>(a, s) : gen_wgrad_launch<bf16_t, false>(a, s);
 }

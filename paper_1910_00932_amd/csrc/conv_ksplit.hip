@@ -527,9 +527,12 @@ static bool ks_supported(const ConvP& p, int dtype, bool dgrad) {
     if (p.Cin % ve || p.Cout % ve || p.stride > 2 || p.KH > 8 || p.KW > 8) return false;
     if (p.KT > 1 && p.fold > 0) return false;
     if (!dgrad && p.fold % ve) return false;           // a vector's channels come from one frame
-    const long cs = dgrad ? p.Cout : p.Cin, cd = dgrad ? p.Cin : p.Cout;
-    const long src = (dgrad ? p.rows_out() : p.rows_in()) * cs * es, pad = ((long)p.KH * (dgrad ? p.Wo : p.W) + p.KW) * cs * es;
-    if (src + 2 * pad >= limit || (long)p.taps() * cs * cd * es >= limit) return false;
+    // offsets run from the padding in front of the first pixel (the bias of ks_geometry) to the last tap behind the last one
+    const long cs = dgrad ? p.Cout : p.Cin, cd = dgrad ? p.Cin : p.Cout, ws = dgrad ? p.Wo : p.W;
+    const long padh = dgrad ? p.KH - 1 - p.pad : p.pad, padw = dgrad ? p.KW - 1 - p.pad : p.pad;
+    const long src = (dgrad ? p.rows_out() : p.rows_in()) * cs * es, span = ((long)p.KH * ws + p.KW) * cs * es;
+    const long bias = (std::max(padh, 0L) * ws + std::max(padw, 0L)) * cs * es;
+    if (src + 2 * span >= limit || src + bias >= limit || (long)p.taps() * cs * cd * es >= limit) return false;
     if (p.rows_in() > 0x3fffffffL || p.rows_out() > 0x3fffffffL) return false;
     return p.rows_in() > 0 && p.rows_out() > 0;
 }

@@ -136,6 +136,21 @@ def test_workspace_plan_switches_kernels_at_2_gib():
     assert rows_above == 2 * rows_below and rows_below % 8 == 0
 
 
+def test_workspace_plan_counts_the_padding_towards_2_gib():
+    """Byte offsets start at the padding in front of the tensor: a 1x1 layer of 1.998 GiB with a padding of 20 pixels passes
+    2 GiB with it and has to run on the kernel with 64-bit addresses (128-row tiles, one statistics row each) instead of the
+    K-split kernel (64-row tiles), which takes the same tensor without padding."""
+    def plan(pad, tile):
+        d = B.ConvDesc(N=167, T=1, Cin=1024, H=56, W=56, Cout=8, kh=1, kw=1, stride=1, pad=pad, fold_div=0,
+                       dtype=B.TSM_F32, layout=B.TSM_NTHWC)
+        rows = -(-167 * (56 + 2 * pad) ** 2 // tile)
+        return B.tsm_conv_workspace_bytes(d), -(-rows * 2 * 8 * 4 // 256) * 256
+    need, expected = plan(0, 64)
+    assert need == expected
+    need, expected = plan(20, 128)
+    assert need == expected
+
+
 def test_block_infer_argument_errors():
     L = B.lib()
     a = 4096

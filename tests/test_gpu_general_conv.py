@@ -54,3 +54,32 @@ def test_noalloc_forward_whose_packed_weights_do_not_fit_the_fixed_scratch():
     got = from_dev(y, "nthwc")
     compare_act(got, ref, 1e-4, "noalloc", "f32")
     assert np.allclose(s1.cpu().numpy(), got.sum(axis=(0, 1, 3, 4)), rtol=1e-4, atol=1e-4)
+
+
+def test_padding_that_takes_the_offsets_past_2_gib():
+    """A 1x1 layer of 1.998 GiB with a padding of 20 pixels: what lies in the padding is zero in the result and adds nothing to
+    the weight gradient.  The frames are drawn on the device; fp64 products of sampled frames and of all of them."""
+    N, C, H, pad, Co = 167, 1024, 56, 20, 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(0)
+    x = torch.randn((N, 1, H, H, C), generator=g, device="cuda")
+    dy = torch.randn((N, 1, H + 2 * pad, H + 2 * pad, Co), generator=g, device="cuda")
+    w = torch.randn((Co, C, 1, 1), generator=g, device="cuda")
+    d = B.ConvDesc(N=N, T=1, Cin=C, H=H, W=H, Cout=Co, kh=1, kw=1, stride=1, pad=pad, fold_div=0, dtype=B.TSM_F32,
+                   layout=B.TSM_NTHWC)
+    ws = torch.empty(B.tsm_conv_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    y, dw = torch.empty_like(dy), torch.empty((Co, C, 1, 1), device="cuda")
+    B.tsm_conv_fwd(d, x, w, y, None, None, ws)
+    B.tsm_conv_wgrad(d, x, dy, dw, 0, ws)
+    inside = slice(pad, pad + H)
+    w64 = w.reshape(Co, C).double()
+    for n in (0, 1, N // 2, N - 1):
+        ref = x[n, 0].double() @ w64.t()
+        assert torch.linalg.norm(y[n, 0, inside, inside].double() - ref) < 1e-5 * torch.linalg.norm(ref)
+    y[:, :, inside, inside] = 0
+    assert torch.count_nonzero(y) == 0
+    ref = torch.zeros((Co, C), dtype=torch.float64, device="cuda")
+    for n in range(N):
+        ref += dy[n, 0, inside, inside].reshape(-1, Co).double().t() @ x[n, 0].reshape(-1, C).double()
+    # (fp32 sums over chunks of 48096 products: sqrt(48096) * 2^-24 = 1.3e-5, with a factor of three)
+    assert torch.linalg.norm(dw.reshape(Co, C).double() - ref) < 4e-5 * torch.linalg.norm(ref)
