@@ -73,6 +73,11 @@
  *  - dtype: TSM_F32 (fp32 storage and arithmetic) or TSM_BF16 (bf16 storage,
  *    bf16 MFMA products, fp32 accumulation; all statistics, weight gradients,
  *    the loss and the optimiser state stay fp32).
+ *  - Infinite and NaN operands: a tap outside the frame or the clip adds nothing in
+ *    TSM_F32 layers and in TSM_BF16 layers whose channel counts or shift groups
+ *    are no multiples of eight; the other TSM_BF16 layers multiply the operand
+ *    with a zero there, so that an infinite weight (or, in a weight gradient, an
+ *    infinite gradient) is NaN at the border.
  *  - Device pointers must be 16-byte aligned (TSM_ERR_ALIGN otherwise).
  *  - fold_div: 0 disables the shift (plain per-frame 2-D convolution);
  *    fold_div >= 2 moves fold = C / fold_div (integer division) channels each

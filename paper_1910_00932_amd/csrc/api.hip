@@ -50,6 +50,7 @@ static inline bool use_gen(const ConvP& p, int dtype, const Arena& ws) {
 static bool shift_first(ConvP* p, int dtype, const Arena& ws) {
     const int ve = dtype == TSM_F32 ? 4 : 8;
     if (use_mfma(*p, dtype) || ws.lean || p->fold == 0 || p->fold % ve == 0 || p->Cin % ve != 0 || !gen_conv_supported(*p)) return false;
+    p->shifted = p->fold;
     p->fold = 0;
     return true;
 }

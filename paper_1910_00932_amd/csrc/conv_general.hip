@@ -12,14 +12,15 @@
 // Against one thread per output element (1.2 TFLOP/s whatever the layer; those kernels are kept in direct.hip for strides
 // beyond 2 and filters beyond 8): fp32 train step at 4 clips of 8 x 224^2 655 -> 16.1 ms; bf16 72 -> 200 channels 3x3 at
 // 4 clips of 8 x 29^2, all three directions, 17.7 ms -> 211 us.  Forward and data gradients have since moved to
-// conv_ksplit.hip (12.9 ms and 157 us) except where channel counts are no multiple of a 16-byte vector or a tensor
-// exceeds the 2 GiB of a buffer's offsets; the weight gradients are here.
+// conv_ksplit.hip (12.9 ms and 157 us) except where channel counts are no multiple of a 16-byte vector, a tensor
+// exceeds the 2 GiB of a buffer's offsets or a large bf16 layer reads a shifted copy; the weight gradients are here.
 //
 // The shift is index arithmetic as in conv_mfma.hip.  A 16-byte vector of channels that straddles two shift groups is
 // put together from one masked load per group; where rows are not 16-byte aligned (channel counts that are no multiple
 // of the vector) it is loaded element by element.
 #include <algorithm>
 #include "internal.h"
+#include "taps_inside.h"
 
 namespace tsm {
 
@@ -44,6 +45,7 @@ struct GenArgs {
     int Hd, Wd, Cd;
     int KT, KH, KW, stride, padh, padw;
     int fold;              // fwd: shift of source channels; dgrad: adjoint shift of destination channels
+    int shifted;           // fwd: fold of a source that is S(x) already
     int Kp;                // taps * CsP
     int ntiles, mtiles;
     // parity classes of destination pixels (see IgemmArgs in conv_mfma.hip)
@@ -121,6 +123,31 @@ __device__ __forceinline__ void mma(const u32x4* a, const u32x4* b, f32x16 (&acc
                 for (int j = 0; j < NJ; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i][e]), __uint_as_float(b[j][e]), acc[i][j], 0, 0, 0);
     }
+}
+
+// The accumulators of a lane that hold NaN, and a new value for one of them.
+template <int MI, int NJ>
+__device__ __forceinline__ uint64_t nan_mask(const f32x16 (&acc)[MI][NJ]) {
+    static_assert(MI * NJ * 16 <= 64, "one bit each");
+    uint64_t m = 0;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (acc[i][j][r] != acc[i][j][r]) m |= 1ull << ((i * NJ + j) * 16 + r);
+    return m;
+}
+template <int MI, int NJ>
+__device__ __forceinline__ void set_at(f32x16 (&acc)[MI][NJ], int at, float v) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[i][j][r] = at == (i * NJ + j) * 16 + r ? v : acc[i][j][r];
 }
 
 struct GenRow {
@@ -263,6 +290,16 @@ __global__ void __launch_bounds__(256, 2) gen_igemm_kernel(GenArgs a) {
         __syncthreads();
     }
 
+    uint64_t nan = nan_mask(acc);   // (see taps_inside.h)
+    while (__builtin_expect(nan != 0, 0)) {
+        const int at = __ffsll((long long)nan) - 1, i = at / (NJ * 16), j = at / 16 % NJ, r = at % 16;
+        nan &= nan - 1;
+        const GenRow row = s_row[wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)];
+        const int col = n0 + wn * TN + j * 32 + (lane & 31);
+        if (row.dst >= 0 && col < a.Cd)
+            set_at(acc, at, sum_taps_inside<T, DGRAD>(a, cls, (const T*)a.src + row.off, row.mask, (const T*)a.wp + (long)col * a.Kp, a.CsP));
+    }
+
     // ---- epilogue: lane = channel lane % 32, register r = row 8*(r/4) + 4*(lane/32) + r%4 of the 32x32 block; a
     // half-wavefront stores 32 consecutive channels of one pixel
     float* s_part = (float*)smem;   // [2][WM*2][BN]
@@ -332,6 +369,8 @@ struct GenWgradArgs {
     int si, st;
     int F, T, H, W, Cin, CinP, Ho, Wo, Cout;
     int KT, KH, KW, stride, pad, fold;
+    int shifted;           // fold of an x that is S(x) already
+    int inside_only;       // pixels whose tap lies outside add nothing whatever dy is (see taps_inside.h)
     long M, chunk;
     int K;                 // taps * CinP: columns of D, padded per tap
     int col_tiles;
@@ -506,6 +545,26 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
         if (st + 1 < nsteps) store(buf ^ 1);
         __syncthreads();
     }
+    uint64_t nan = a.inside_only ? nan_mask(acc) : 0ull;
+    while (__builtin_expect(nan != 0, 0)) {
+        const int at = __ffsll((long long)nan) - 1, i = at / (NJ * 16), j = at / 16 % NJ, r = at % 16;
+        nan &= nan - 1;
+        const int col = j0 + wn * TN + j * 32 + (lane & 31), co = co0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int tp = col / a.CinP, ci = col - tp * a.CinP;
+        if (col >= a.K || ci >= a.Cin || co >= a.Cout) continue;
+        const int w_ = tp % a.KW, h_ = tp / a.KW % a.KH, dk = tp / (a.KW * a.KH) - a.KT / 2;
+        const int d = dk + tap_group_dt(ci, a.fold + a.shifted);   // (one of them is zero)
+        float v = 0.f;
+#pragma unroll 1
+        for (long m = mbeg; m < mend && v == v; ++m) {
+            const int f = (int)(m / hw), pix = (int)(m - (long)f * hw), t = f % a.T;
+            const int ih = pix / a.Wo * a.stride - a.pad + h_, iw = pix % a.Wo * a.stride - a.pad + w_;
+            if (ih < 0 || ih >= a.H || iw < 0 || iw >= a.W || t + d < 0 || t + d >= a.T) continue;
+            v = fmaf(Elem<T>::ld(((const T*)a.dy)[m * a.Cout + co]),
+                     Elem<T>::ld(((const T*)a.x)[(((long)f + (a.shifted ? dk : d)) * a.H * a.W + (long)ih * a.W + iw) * a.Cin + ci]), v);
+        }
+        set_at(acc, at, v);
+    }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int col = j0 + wn * TN + j * 32 + (lane & 31);
@@ -648,7 +707,7 @@ int gen_fwd_blocks(const ConvP& p, int dtype) {
 
 static void gen_common(GenArgs& a, const ConvP& p) {
     a.addend = nullptr; a.stats = nullptr;
-    a.F = p.F; a.T = p.T; a.KT = p.KT; a.KH = p.KH; a.KW = p.KW; a.stride = p.stride; a.fold = p.fold;
+    a.F = p.F; a.T = p.T; a.KT = p.KT; a.KH = p.KH; a.KW = p.KW; a.stride = p.stride; a.fold = p.fold; a.shifted = p.shifted;
 }
 
 int gen_conv_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void* y, float* stats, hipStream_t s) {
@@ -708,6 +767,7 @@ int gen_conv_wgrad(const ConvP& p, int dtype, const void* x, const void* dy, flo
     a.F = p.F; a.T = p.T; a.H = p.H; a.W = p.W; a.Cin = p.Cin; a.CinP = pad_vec(p.Cin, dtype);
     a.Ho = p.Ho; a.Wo = p.Wo; a.Cout = p.Cout;
     a.KT = p.KT; a.KH = p.KH; a.KW = p.KW; a.stride = p.stride; a.pad = p.pad; a.fold = p.fold;
+    a.shifted = p.shifted; a.inside_only = dtype == TSM_F32 || !mfma_conv_supported(p);
     a.M = p.rows_out();
     a.K = p.taps() * a.CinP;
     const int ve = dtype == TSM_F32 ? 4 : 8;

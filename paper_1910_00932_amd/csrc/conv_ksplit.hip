@@ -12,6 +12,7 @@
 // latency, are what is left (392 x 4608 -> 512 in 32 x 32 tiles reads 590 KB per CU).
 #include <algorithm>
 #include "internal.h"
+#include "taps_inside.h"
 
 namespace tsm {
 
@@ -44,6 +45,8 @@ struct KsArgs {
     int KT, KH, KW;
     int stride, padh, padw;
     int fold;              // fwd: shift of source channels; dgrad: adjoint shift of destination channels
+    int shifted;           // fwd: fold of a source that is S(x) already
+    int inside_only;       // taps outside add nothing whatever they are multiplied with (see taps_inside.h)
     uint32_t wrow;         // bytes of one weight row
     uint32_t src_bytes, w_bytes, bias_bytes;
     int ntiles, mtiles, by_n;
@@ -94,7 +97,8 @@ template <typename T> __device__ __forceinline__ u32x4 pack(const float* f) {
 }
 
 // One tile of 32*MI pixels x 32*NJ channels per block; wavefront w multiplies the K chunks (128 bytes of every tile row)
-// w, w + KS, w + 2*KS, ... of it.  RAG: source channels that are no multiple of a chunk (they are one of the vector).
+// w, w + KS, w + 2*KS, ... of it.  RAG: source channels that are no multiple of a chunk (they are one of the vector), and bf16
+// layers with inside_only.
 template <typename T, int MI, int NJ, int KS, bool DGRAD, bool RAG>
 __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
     constexpr int NT = KS * 64;
@@ -103,6 +107,7 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
     constexpr int STAGE = (TM + TN) * 128;          // bytes per wavefront
     constexpr int PA = TM / 8, PB = TN / 8;         // 16-byte pieces per lane and chunk
     constexpr int SL = TN / 4;                      // 16-byte slots per row of a partial tile
+    constexpr bool CHECK = ES == 4 || RAG;          // takes layers with inside_only
     static_assert(TM * TN * 4 <= STAGE, "a partial tile takes the place of its wavefront's operands");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     KsRow* s_row = (KsRow*)(smem + KS * STAGE);
@@ -337,6 +342,42 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
                 }
     }
     __syncthreads();
+    auto add_up = [&](int v, float* f) {
+        const int row = v * RPS + r0;
+#pragma unroll
+        for (int q = 0; q < VE; ++q) f[q] = 0.f;
+        for (int w = 0; w < nact; ++w) {
+            const unsigned char* p = smem + w * STAGE + row * (TN * 4);
+#pragma unroll
+            for (int h = 0; h < VE / 4; ++h) {
+                const f32x4 x = *(const f32x4*)(p + (((vcol * (VE / 4) + h) ^ (row & (SL - 1))) * 16));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) f[4 * h + q] += x[q];
+            }
+        }
+    };
+    float sum[CHECK ? NV : 1][VE];
+    if constexpr (CHECK) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) add_up(v, sum[v]);
+    }
+    if constexpr (CHECK) if (a.inside_only && colok) {
+        uint32_t nan = 0;
+        static_assert(NV * VE <= 32, "one bit each");
+#pragma unroll
+        for (int e = 0; e < NV * VE; e += 2)
+            if (__builtin_isunordered(sum[e / VE][e % VE], sum[e / VE][e % VE + 1])) nan |= 3u << e;
+        while (__builtin_expect(nan != 0, 0)) {
+            const int at = __ffs((int)nan) - 1, c = col + at % VE;
+            nan &= nan - 1;
+            const KsRow r = s_row[at / VE * RPS + r0];
+            if (r.dst < 0) continue;
+            const float f = sum_taps_inside<T, DGRAD>(a, cls, (const T*)((const char*)a.src + ((long)r.off - (long)a.bias_bytes)), r.mask,
+                                                      (const T*)((const char*)a.wp + (size_t)c * a.wrow), a.Cs);
+#pragma unroll
+            for (int e = 0; e < NV * VE; ++e) sum[e / VE][e % VE] = e == at ? f : sum[e / VE][e % VE];
+        }
+    }
     T* const dst = (T*)a.dst;
     // value (rounded once) -> addend -> ReLU mask and BatchNorm sums -> store
     auto finish = [&](long m, float* f, const u32x4& adv, const u32x4& acv, const u32x4& yyv) {
@@ -366,19 +407,13 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
     for (int v = 0; v < NV; ++v) {
         const int row = v * RPS + r0;
         float f[VE];
-#pragma unroll
-        for (int q = 0; q < VE; ++q) f[q] = 0.f;
-        for (int w = 0; w < nact; ++w) {
-            const unsigned char* p = smem + w * STAGE + row * (TN * 4);
-#pragma unroll
-            for (int h = 0; h < VE / 4; ++h) {
-                const f32x4 x = *(const f32x4*)(p + (((vcol * (VE / 4) + h) ^ (row & (SL - 1))) * 16));
-#pragma unroll
-                for (int q = 0; q < 4; ++q) f[4 * h + q] += x[q];
-            }
+        if constexpr (CHECK) {
+            unpack<T>(pack<T>(sum[v]), f);
+        } else {
+            add_up(v, f);
+            const u32x4 o = pack<T>(f);
+            unpack<T>(o, f);
         }
-        const u32x4 o = pack<T>(f);
-        unpack<T>(o, f);
         if constexpr (!DGRAD) {
             if (mr[v] < 0) continue;
             if (a.stats) {
@@ -506,6 +541,7 @@ static int ks_classes(KsArgs& a, bool dgrad, int BM) {
 static void ks_geometry(KsArgs& a, const ConvP& p, int dtype, bool dgrad) {
     const long es = (long)dtype_size(dtype);
     a.F = p.F; a.T = p.T; a.KT = p.KT; a.KH = p.KH; a.KW = p.KW; a.stride = p.stride; a.fold = p.fold;
+    a.shifted = p.shifted; a.inside_only = dtype == TSM_F32 || !mfma_conv_supported(p);
     if (!dgrad) {
         a.Hs = p.H; a.Ws = p.W; a.Cs = p.Cin; a.Hd = p.Ho; a.Wd = p.Wo; a.Cd = p.Cout;
         a.padh = a.padw = p.pad;
@@ -588,7 +624,7 @@ static KsTile ks_tile(const ConvP& p, int dtype, bool dgrad) {
 
 template <typename T, bool DGRAD>
 static int ks_dispatch(KsArgs& a, KsTile t, hipStream_t s) {
-    const bool rag = a.Cs % (128 / (int)sizeof(T)) != 0;
+    const bool rag = a.Cs % (128 / (int)sizeof(T)) != 0 || (sizeof(T) == 2 && a.inside_only);
 #define KS_CASE(BM, BN, KS_) \
     if (t.bm == BM && t.bn == BN && t.ks == KS_) return rag ? ks_launch<T, BM / 32, BN / 32, KS_, DGRAD, true>(a, s) : ks_launch<T, BM / 32, BN / 32, KS_, DGRAD, false>(a, s)
     KS_CASE(64, 64, 4);
@@ -603,12 +639,13 @@ static int ks_dispatch(KsArgs& a, KsTile t, hipStream_t s) {
 // fp32 layers, and bf16 layers that conv_mfma.hip does not take, run here whenever they can: the alternative is the block-
 // wide schedule of conv_general.hip (fp32 6272 x 2304 -> 256: 129 us there, 83 here; 25088 x 1152 -> 128: 106, 82; bf16
 // data gradient 26912 x 1800 -> 72 with split shift groups: 56, 36).  bf16 layers that it does take change over where
-// there are at most two 64 x 64 tiles per CU.  Measured on both sides of the line, us there -> here: 6272 x 2304 -> 256 (392
+// there are at most two 64 x 64 tiles per CU, and so do forward layers that read a shifted copy (26912 x 648 -> 200, 1684 tiles:
+// its three directions together 132.1 us with the general kernel, 140.0 with this one).  Measured on both sides of the line, us there -> here: 6272 x 2304 -> 256 (392
 // tiles) 25.4 -> 20.7, 6272 x 1024 -> 256 (392) 16.4 -> 14.0, 392 x 4608 -> 512 (56) 39 -> 13, 25088 x 64 -> 64 (392) 8.6 -> 7.4;
 // 12544 x 1024 -> 256 (784) 18.9 -> 22.4, 6272 x 128 -> 512 (784) 9.5 -> 13.5, 25088 x 64 -> 256 (1568) 12.2 -> 15.
 bool ksplit_use(const ConvP& p, int dtype, bool dgrad) {
     if (!ks_supported(p, dtype, dgrad)) return false;
-    if (dtype == TSM_F32 || !mfma_conv_supported(p)) return true;
+    if (dtype == TSM_F32 || (!mfma_conv_supported(p) && (dgrad || !p.shifted))) return true;
     if (p.whole_k) return false;
     return ks_tiles(p, dtype, dgrad) <= 2L * ks_cus();
 }

@@ -1888,7 +1888,7 @@ static int num_cu() {
 
 bool mfma_conv_supported(const ConvP& p) {
     if (p.Cin % 8 || p.Cout % 8) return false;
-    if (p.fold % 8) return false;
+    if (p.fold % 8 || p.shifted) return false;
     if (p.Cin > 8192 || p.Cout > 8192) return false;
     if (p.stride > 2) return false;   // the dgrad kernel enumerates at most four parity classes
     if (p.KH > 8 || p.KW > 8) return false;        // tap-validity bit masks hold eight rows / columns

@@ -17,6 +17,9 @@ struct ConvP {
     // overlap the following pixels: a convolution whose taps along W are folded into the channel dimension
     // (MFMA kernels with Cin % 64 == 0 only; the caller guarantees that every read stays inside the tensor).
     int pitch = 0;
+    // Fold of a layer whose input is S(x) already, written by the stand-alone shift (fold is 0 then): what the shift left
+    // empty at the ends of a clip is still outside.
+    int shifted = 0;
     // bf16: keeps the layer on the kernels that sum the whole K range of a result in one wavefront (see ksplit_use).
     bool whole_k = false;
     int pix_pitch() const { return pitch ? pitch : Cin; }
