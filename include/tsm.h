@@ -27,7 +27,13 @@
  *    what is computed.  For comparisons the environment can take choices away:
  *    TSM_IGEMM_RING=0 / TSM_WGRAD_TR=0 (read once per process) fall back to the
  *    kernels for channel counts that are not multiples of 64 wherever those can
- *    run; TSM_CONV3X3_C64=0 and TSM_STEM_KERNEL=0 (read at every call) leave the
+ *    run; TSM_KSPLIT=0 (read at every call) takes away the kernels that split the
+ *    K range of a tile over the wavefronts of a block -- fp32 layers and bf16 layers
+ *    with at most two 64 x 64 tiles per compute unit, TSM_KSPLIT_MAX_TILES=<n>
+ *    replaces that number -- and TSM_KSPLIT=1 gives them the layers of
+ *    tsm_block_fwd / tsm_block_bwd as well, which otherwise keep to one wavefront
+ *    per result; TSM_IGEMM_RING=0, TSM_IGEMM_BM and TSM_IGEMM_NARROW=0 keep bf16 layers
+ *    off them too; TSM_CONV3X3_C64=0 and TSM_STEM_KERNEL=0 (read at every call) leave the
  *    layers that have a kernel of their own to the general one (TSM_STEM_PW=0,
  *    read at every call, keeps the stem on the block-wide one of its two
  *    kernels), and

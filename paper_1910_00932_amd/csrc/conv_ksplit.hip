@@ -10,6 +10,7 @@
 // is that the two wavefronts of a SIMD are never in phase (92 TFLOP/s at 6272 x 2304 -> 256, 57 with a block-wide barrier
 // per step).  Two chunks in flight per wavefront instead of one change nothing on the small layers: bytes per CU, not
 // latency, are what is left (392 x 4608 -> 512 in 32 x 32 tiles reads 590 KB per CU).
+#include <stdlib.h>
 #include <algorithm>
 #include "internal.h"
 #include "taps_inside.h"
@@ -643,11 +644,16 @@ static int ks_dispatch(KsArgs& a, KsTile t, hipStream_t s) {
 // its three directions together 132.1 us with the general kernel, 140.0 with this one).  Measured on both sides of the line, us there -> here: 6272 x 2304 -> 256 (392
 // tiles) 25.4 -> 20.7, 6272 x 1024 -> 256 (392) 16.4 -> 14.0, 392 x 4608 -> 512 (56) 39 -> 13, 25088 x 64 -> 64 (392) 8.6 -> 7.4;
 // 12544 x 1024 -> 256 (784) 18.9 -> 22.4, 6272 x 128 -> 512 (784) 9.5 -> 13.5, 25088 x 64 -> 256 (1568) 12.2 -> 15.
+// TSM_KSPLIT=0 leaves every layer to the other kernels, TSM_KSPLIT=1 takes the layers with whole_k as well, and
+// TSM_KSPLIT_MAX_TILES=<n> moves the line (all read at every call: tests and comparisons set them).
 bool ksplit_use(const ConvP& p, int dtype, bool dgrad) {
     if (!ks_supported(p, dtype, dgrad)) return false;
+    const char* e = getenv("TSM_KSPLIT");
+    if (e && e[0] == '0') return false;
     if (dtype == TSM_F32 || (!mfma_conv_supported(p) && (dgrad || !p.shifted))) return true;
-    if (p.whole_k) return false;
-    return ks_tiles(p, dtype, dgrad) <= 2L * ks_cus();
+    if (p.whole_k && !(e && e[0] == '1')) return false;
+    const char* m = getenv("TSM_KSPLIT_MAX_TILES");
+    return ks_tiles(p, dtype, dgrad) <= (m ? atol(m) : 2L * ks_cus());
 }
 
 int ksplit_rows(const ConvP& p, int dtype, bool dgrad) {

@@ -2491,25 +2491,32 @@ static int launch_igemm_ring(IgemmArgs& a, const char* name, hipStream_t s) {
 // per CU: 128x64 tiles for narrow outputs (<= 64 channels), 128x128 otherwise.
 // `needed`: the layer has a pixel pitch other than its channel count (the stem in space-to-depth form), which only
 // this kernel handles, so the comparison switch does not apply to it.
+static bool switched_on(const char* name) {
+    const char* e = getenv(name);
+    return !(e && e[0] == '0');
+}
+static bool ring_enabled() {   // TSM_IGEMM_RING=0 keeps the register-prefetch kernels wherever they can run (for comparisons)
+    static const bool on = switched_on("TSM_IGEMM_RING");
+    return on;
+}
 static bool ring_eligible(int Cs, long src_elems, long w_elems, bool needed) {
-    static int enabled = -1;   // TSM_IGEMM_RING=0 keeps the register-prefetch kernels wherever they can run (for comparisons)
-    if (enabled < 0) {
-        const char* e = getenv("TSM_IGEMM_RING");
-        enabled = (e && e[0] == '0') ? 0 : 1;
-    }
+    const bool enabled = ring_enabled();
     const long limit = 0x7ff00000L;   // bytes, leaves room for the padding bias in front of the tensor
     return (enabled || needed) && Cs % BK == 0 && src_elems * 2 < limit && w_elems * 2 < limit;
 }
 
 // Rows per tile of the ring kernel: 256, or 128 when 256-row tiles would leave a good part of the CUs without
 // a tile (small batches in the last stages).
-static int ring_rows(long rows, int Cd) {
-    static int forced = -1;   // TSM_IGEMM_BM=128|256 fixes the choice (for comparisons)
-    if (forced < 0) {
+static int forced_rows() {   // TSM_IGEMM_BM=128|256 fixes the choice (for comparisons)
+    static const int rows = [] {
         const char* e = getenv("TSM_IGEMM_BM");
-        forced = e ? atoi(e) : 0;
-    }
-    if (forced == 128 || forced == 256) return forced;
+        const int v = e ? atoi(e) : 0;
+        return v == 128 || v == 256 ? v : 0;
+    }();
+    return rows;
+}
+static int ring_rows(long rows, int Cd) {
+    if (forced_rows()) return forced_rows();
     const long ntiles = (Cd + 127) / 128;
     const long tiles256 = ((rows + 255) / 256) * (Cd <= 64 ? 1 : ntiles);
     return tiles256 * 4 < (long)num_cu() * 3 ? 128 : 256;
@@ -2518,14 +2525,13 @@ static int ring_rows(long rows, int Cd) {
 // Columns per tile of the ring kernel: 128, or 64 for outputs of at most 64 channels and where even 128-row tiles
 // with 128 columns would leave a good part of the CUs without a tile (the last stage at the paper's batch of 8
 // clips: 25 row tiles x 4 column tiles for 256 CUs).  TSM_IGEMM_NARROW=0 keeps 128 columns (for comparisons).
+static bool narrow_enabled() {
+    static const bool on = switched_on("TSM_IGEMM_NARROW");
+    return on;
+}
 static int ring_cols(long rows, int Cd) {
     if (Cd <= 64) return 64;
-    static int enabled = -1;
-    if (enabled < 0) {
-        const char* e = getenv("TSM_IGEMM_NARROW");
-        enabled = (e && e[0] == '0') ? 0 : 1;
-    }
-    if (!enabled || ring_rows(rows, Cd) != 128) return 128;
+    if (!narrow_enabled() || ring_rows(rows, Cd) != 128) return 128;
     const long tiles = ((rows + 127) / 128) * ((Cd + 127) / 128);
     return tiles * 4 < (long)num_cu() * 3 ? 64 : 128;
 }
@@ -2934,16 +2940,18 @@ static void fwd_args(const ConvP& p, IgemmArgs& a) {
     a.K = (int)p.K();
 }
 
-// Layers the K-split kernels take over (see ksplit_use): none that a kernel of its own may take.  A function of the
-// shape alone, so that callers size the rows of the partial buffers by it.
+// Layers the K-split kernels take over (see ksplit_use): none that a kernel of its own may take, and none at all where a switch
+// asks for a kernel or a tile of the general set.  A function of the shape and the switches, so that callers size the rows
+// of the partial buffers by it.
+static bool general_tile_asked_for() { return !ring_enabled() || forced_rows() || !narrow_enabled(); }
 static bool fwd_ksplit(const ConvP& p) {
-    if (!ksplit_use(p, TSM_BF16, false)) return false;
+    if (general_tile_asked_for() || !ksplit_use(p, TSM_BF16, false)) return false;
     IgemmArgs a = {};
     fwd_args(p, a);
     return !c64_eligible(a) && !pw_shape_ok(a) && !wide_fwd_eligible(a);
 }
 static bool dgrad_ksplit(const ConvP& p) {
-    if (!ksplit_use(p, TSM_BF16, true)) return false;
+    if (general_tile_asked_for() || !ksplit_use(p, TSM_BF16, true)) return false;
     IgemmArgs a = {};
     dgrad_args(p, a);
     return !c64_eligible(a) && !pw_shape_ok(a);
@@ -3014,6 +3022,13 @@ bool conv_mfma_dgrad_compact_addend_ok(const ConvP& p) { return conv_mfma_dgrad_
 
 int conv_mfma_dgrad(const ConvP& p, const bf16_t* dy, const bf16_t* wd, bf16_t* dx, const bf16_t* addend,
                     const DgradFuse* fuse, hipStream_t s, int addend_stride) {
+    static const bool bits_on = switched_on("TSM_MASK_BITS");   // TSM_MASK_BITS=0 keeps the activation as the mask source (for comparisons)
+    DgradFuse from_act;
+    if (fuse && !bits_on) {
+        from_act = *fuse;
+        from_act.act_bits = nullptr;
+        fuse = &from_act;
+    }
     if (dgrad_ksplit(p)) return ksplit_dgrad(p, TSM_BF16, dy, wd, dx, addend, addend_stride, fuse, s);
     IgemmArgs a;
     a.src = dy; a.wp = wd; a.dst = dx; a.addend = addend; a.stats = nullptr;
@@ -3029,12 +3044,7 @@ int conv_mfma_dgrad(const ConvP& p, const bf16_t* dy, const bf16_t* wd, bf16_t* 
     if (fuse) {
         // (the general kernel reads the decision bits where it has them; the 64-channel kernel and tiles without the
         // variant read `act`)
-        static int bits_on = -1;   // TSM_MASK_BITS=0 keeps the activation as the mask source (for comparisons)
-        if (bits_on < 0) {
-            const char* e = getenv("TSM_MASK_BITS");
-            bits_on = (e && e[0] == '0') ? 0 : 1;
-        }
-        if (bits_on && p.Cin % 8 == 0) a.act_bits = fuse->act_bits;
+        if (p.Cin % 8 == 0) a.act_bits = fuse->act_bits;
         if (conv_mfma_dgrad_blocks(p) == 0) return fail(TSM_ERR_UNSUPPORTED, "dgrad: this layer's kernel cannot fuse the BatchNorm reductions");
         // (y == nullptr: only the ReLU mask of `act` is applied, no sums)
         a.act = fuse->act; a.ybn = fuse->y; a.bn_mean = fuse->mean; a.bn_rstd = fuse->rstd; a.stats = fuse->y ? fuse->partial : nullptr;

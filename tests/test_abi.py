@@ -3,6 +3,8 @@ symbol declared in include/tsm.h, and rejects bad arguments before launching."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -149,6 +151,39 @@ def test_workspace_plan_counts_the_padding_towards_2_gib():
     assert need == expected
     need, expected = plan(20, 128)
     assert need == expected
+
+
+PLAN_CHILD = """
+import os
+from paper_1910_00932_amd import binding as B
+def rows(dtype):   # (sizes for which the forward pass, packed weights and rows, needs the largest workspace)
+    k = 1 if dtype else 3
+    d = B.ConvDesc(N=1, T=8, Cin=512, H=7, W=7, Cout=512, kh=k, kw=k, stride=1, pad=k // 2, fold_div=0, dtype=dtype,
+                   layout=B.TSM_NTHWC)
+    return (B.tsm_conv_workspace_bytes(d) - 512 * 512 * (2 if dtype else 36)) // (2 * 512 * 4)
+print(rows(B.TSM_BF16), rows(B.TSM_F32))
+os.environ["TSM_KSPLIT"] = "0"
+print(rows(B.TSM_BF16), rows(B.TSM_F32))
+os.environ["TSM_KSPLIT"] = ""
+os.environ["TSM_KSPLIT_MAX_TILES"] = "55"
+print(rows(B.TSM_BF16), rows(B.TSM_F32))
+"""
+
+
+@pytest.mark.parametrize("switch,general", [(None, 32), ("TSM_IGEMM_RING", 32), ("TSM_IGEMM_BM", 32), ("TSM_IGEMM_NARROW", 32)])
+def test_switches_take_small_layers_off_the_k_split_kernels(switch, general):
+    """392 pixels x 512 channels, 56 tiles of 64 x 64: 13 rows of partial sums (tiles of 32 pixels) on the K-split kernels, one
+    per block on the general ones (8 x 4 blocks and more), one per 64-row tile in fp32.  The three switches that fix a kernel or
+    a tile of the general set, read once per process, take the bf16 layer there; TSM_KSPLIT takes both there."""
+    env = {k: v for k, v in os.environ.items() if not k.startswith("TSM_")}
+    if switch:
+        env[switch] = "128" if switch == "TSM_IGEMM_BM" else "0"
+    r = subprocess.run([sys.executable, "-c", PLAN_CHILD], cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    default, off, line = [tuple(int(v) for v in l.split()) for l in r.stdout.split("\n") if l]
+    assert default[1] == 13 and off[1] == 7 and line[1] == 13
+    assert default[0] == 13 if switch is None else default[0] >= general
+    assert off[0] >= general and line[0] == off[0]
 
 
 def test_block_infer_argument_errors():
