@@ -138,13 +138,14 @@ int run_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* w, con
     return TSM_OK;
 }
 
-// Weight gradients with ragged channel counts: conv_mfma.hip's kernel for them transposes in registers on the way to LDS,
-// the general one reads its operands transposed out of it.  From some 16k pixels on the latter is faster (us: 26912 pixels
-// 72 -> 200 3x3 72.6 -> 46.2, 115200 pixels 160 -> 128 3x3 144.7 -> 112.1, 102400 pixels 120 -> 64 1x1 45.0 -> 43.3);
-// below, the former's shorter start is (3136 pixels 96 -> 96, 16.2 and 17.9; 324 pixels 40 -> 40, 9.3 and 11.6).
+// Weight gradients of several taps with ragged channel counts: conv_mfma.hip's kernel for them transposes in registers on the
+// way to LDS, the general one reads its operands transposed out of it.  From some 16k pixels on the latter is faster (us: 26912
+// pixels 72 -> 200 3x3 72.6 -> 46.2, 115200 pixels 160 -> 128 3x3 144.7 -> 112.1); below, the former's shorter start is
+// (3136 pixels 96 -> 96, 16.2 and 17.9; 324 pixels 40 -> 40, 9.3 and 11.6).  A single tap leaves the two level (102400 pixels
+// 120 -> 64 1x1 45.0 and 43.3) and stays with the former.
 static bool wgrad_gen(const ConvP& p, int dtype, const Arena& ws) {
     if (use_gen(p, dtype, ws)) return true;
-    return dtype == TSM_BF16 && !ws.lean && !p.pitch && (p.Cin % 64 || p.Cout % 64) && p.rows_out() >= 16384 && gen_conv_supported(p);
+    return dtype == TSM_BF16 && p.taps() > 1 && !ws.lean && !p.pitch && (p.Cin % 64 || p.Cout % 64) && p.rows_out() >= 16384 && gen_conv_supported(p);
 }
 
 int run_conv_wgrad(const ConvP& p0, int dtype, const void* x, const void* dy, float* dw, float* dwp_zeroed, int accumulate,

@@ -40,6 +40,18 @@ def test_general_conv_parity_paper_order(case):
     TC._run(case, "bf16", "ntchw")
 
 
+@pytest.mark.parametrize("case,kernel", [
+    ((2, 8, 24, 32, 32, 40, 3, 1, 1, 0), "gen_wgrad_bf16"),     # 16384 pixels
+    ((2, 8, 24, 31, 33, 40, 3, 1, 1, 0), "wgrad_64x64"),        # 16368
+    ((2, 8, 24, 33, 34, 40, 1, 1, 0, 0), "wgrad_64x64"),        # 17952, one tap
+])
+def test_weight_gradient_of_ragged_bf16_layers_on_both_sides_of_the_line(case, kernel):
+    B.tsm_profile_begin()
+    TC._run(case, "bf16", "nthwc")
+    classes = B.tsm_profile_end()
+    assert {k for k in classes if "wgrad" in k and not k.startswith("unpack")} == {kernel}, sorted(classes)
+
+
 def test_noalloc_forward_whose_packed_weights_do_not_fit_the_fixed_scratch():
     """1024 x 512 x 3x3 fp32 weights are 18.9 MB packed, the built-in scratch is 16 MiB: the plain kernel runs."""
     N, T, Cin, H, Cout, k = 1, 2, 1024, 3, 512, 3
