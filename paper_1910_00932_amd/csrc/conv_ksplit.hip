@@ -36,7 +36,7 @@ struct KsArgs {
     const float* bn_mean;
     const float* bn_rstd;
     const uint8_t* act_bits;
-    const float* ep_scale; // fwd: affine epilogue (nullable), as in IgemmArgs
+    const float* ep_scale; // fwd, bf16: affine epilogue (nullable), as in IgemmArgs
     const float* ep_shift;
     const void* ep_res;
     int ep_relu;
@@ -282,7 +282,7 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
     const int nact = nch < KS ? nch : KS;
     const bool fuse_mask = DGRAD && (a.act_bits != nullptr || a.act != nullptr);
     const bool fuse_bn = fuse_mask && a.ybn != nullptr;
-    const bool affine = !DGRAD && a.ep_scale != nullptr;
+    const bool affine = !DGRAD && ES == 2 && a.ep_scale != nullptr;
     const int dt = DGRAD ? ks_group_dt(col, a.fold) : 0;
     const bool straddle = DGRAD && ks_group_dt(col + VE - 1, a.fold) != dt;
     // what the epilogue reads is requested before the partial tiles are exchanged; rows that are not stored read zeros
@@ -666,6 +666,7 @@ int ksplit_fwd(const ConvP& p, int dtype, const void* x, const void* wp, void* y
     KsArgs a = {};
     ks_geometry(a, p, dtype, false);
     a.src = x; a.wp = wp; a.dst = y; a.stats = stats; a.add_stride = 1;
+    if (ep && dtype != TSM_BF16) return fail(TSM_ERR_UNSUPPORTED, "ksplit: the affine epilogue is for bf16 layers");
     if (ep) { a.ep_scale = ep->scale; a.ep_shift = ep->shift; a.ep_res = ep->res; a.ep_relu = ep->relu; }
     const KsTile t = ks_tile(p, dtype, false);
     return dtype == TSM_F32 ? ks_dispatch<float, false>(a, t, s) : ks_dispatch<bf16_t, false>(a, t, s);
