@@ -595,15 +595,16 @@ static int ks_launch(KsArgs& a, hipStream_t s) {
     return check_launch(DGRAD ? "ksplit_dgrad_bf16" : "ksplit_fwd_bf16");
 }
 
-// 64 x 64 tiles of a direction that have something to multiply (a strided 1x1 layer's data gradient has parity classes
-// without taps).
-static long ks_tiles(const ConvP& p, int dtype, bool dgrad) {
+// 64 x 64 tiles of a direction that have something to multiply; *idle: of those that only store zeros or an addend (a strided
+// 1x1 layer's data gradient has parity classes without taps).
+static long ks_tiles(const ConvP& p, int dtype, bool dgrad, long* idle = nullptr) {
     KsArgs a;
     ks_geometry(a, p, dtype, dgrad);
     ks_classes(a, dgrad, 64);
     long mt = 0;
     for (int c = 0; c < a.ncls; ++c)
         if (a.nth[c] > 0) mt += a.mt0[c + 1] - a.mt0[c];
+    if (idle) *idle = (a.mt0[a.ncls] - mt) * ((a.Cd + 63) / 64);
     return mt * ((a.Cd + 63) / 64);
 }
 
@@ -644,6 +645,9 @@ static int ks_dispatch(KsArgs& a, KsTile t, hipStream_t s) {
 // its three directions together 132.1 us with the general kernel, 140.0 with this one).  Measured on both sides of the line, us there -> here: 6272 x 2304 -> 256 (392
 // tiles) 25.4 -> 20.7, 6272 x 1024 -> 256 (392) 16.4 -> 14.0, 392 x 4608 -> 512 (56) 39 -> 13, 25088 x 64 -> 64 (392) 8.6 -> 7.4;
 // 12544 x 1024 -> 256 (784) 18.9 -> 22.4, 6272 x 128 -> 512 (784) 9.5 -> 13.5, 25088 x 64 -> 256 (1568) 12.2 -> 15.
+// Data gradients with idle tiles (strided 1x1 layers): more of those than CUs cost more than the split saves unless K is long.
+// Us there -> here, K and tiles in all: 128 224 10.6 -> 10.7, 64 392 10.9 -> 13.3, 128 416 10.7 -> 13.7, 512 400 13.5 -> 15.9,
+// 256 448 11.7 -> 15.6; 1024 400 16.9 -> 15.0, 2048 800 33.7 -> 26.1.
 // TSM_KSPLIT=0 leaves every layer to the other kernels, TSM_KSPLIT=1 takes the layers with whole_k as well, and
 // TSM_KSPLIT_MAX_TILES=<n> moves the line (all read at every call: tests and comparisons set them).
 bool ksplit_use(const ConvP& p, int dtype, bool dgrad) {
@@ -653,7 +657,10 @@ bool ksplit_use(const ConvP& p, int dtype, bool dgrad) {
     if (dtype == TSM_F32 || (!mfma_conv_supported(p) && (dgrad || !p.shifted))) return true;
     if (p.whole_k && !(e && e[0] == '1')) return false;
     const char* m = getenv("TSM_KSPLIT_MAX_TILES");
-    return ks_tiles(p, dtype, dgrad) <= (m ? atol(m) : 2L * ks_cus());
+    long idle = 0;
+    const long tiles = ks_tiles(p, dtype, dgrad, &idle);
+    if (idle > 0 && tiles + idle > ks_cus() && p.Cout < 1024) return false;
+    return tiles <= (m ? atol(m) : 2L * ks_cus());
 }
 
 int ksplit_rows(const ConvP& p, int dtype, bool dgrad) {

@@ -19,6 +19,12 @@ from paper_1910_00932_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(autouse=True)
+def _off_the_plain_kernels(monkeypatch):
+    monkeypatch.setenv("TSM_PLAIN_CONV", "0")
+
+
 CASES = [  # N,T,Cin,H,W,Cout,k,stride,pad,fold_div
     (1, 1, 64, 1, 1, 64, 1, 1, 0, 0),          # one pixel, one chunk: seven of eight wavefronts have nothing to add
     (1, 2, 512, 5, 5, 64, 3, 1, 1, 8),         # 32 x 32 tiles, nine chunks per wavefront
@@ -49,6 +55,18 @@ def test_ksplit_parity(case, dtype):
         assert not both & set(classes), sorted(classes)
     else:
         assert both <= set(classes), sorted(classes)
+
+
+@pytest.mark.parametrize("case,split", [  # strided 1x1: three parity classes of dx receive nothing
+    ((8, 8, 512, 7, 7, 128, 1, 2, 0, 8), False),    # 400 tiles for 256 CUs, 128 products
+    ((2, 8, 512, 7, 7, 128, 1, 2, 0, 8), True),     # 104 tiles
+    ((4, 8, 256, 14, 14, 1024, 1, 2, 0, 8), True),  # 400 tiles, 1024 products
+])
+def test_strided_one_tap_data_gradients_on_both_sides_of_the_line(case, split):
+    B.tsm_profile_begin()
+    TC._run(case, "bf16", "nthwc")
+    classes = B.tsm_profile_end()
+    assert ("ksplit_dgrad_bf16" in classes) == split, sorted(classes)
 
 
 def test_ksplit_with_two_wavefronts_per_tile_in_bf16():
