@@ -33,7 +33,9 @@
  *    replaces that number -- and TSM_KSPLIT=1 gives them the layers of
  *    tsm_block_fwd / tsm_block_bwd as well, which otherwise keep to one wavefront
  *    per result; TSM_IGEMM_RING=0, TSM_IGEMM_BM and TSM_IGEMM_NARROW=0 keep bf16 layers
- *    off them too; TSM_CONV3X3_C64=0 and TSM_STEM_KERNEL=0 (read at every call) leave the
+ *    off them too; TSM_PLAIN_CONV=0 (read at every call) keeps the smallest fp32 and
+ *    ragged calls of tsm_conv_* off the plain kernels, which save them launches;
+ *    TSM_CONV3X3_C64=0 and TSM_STEM_KERNEL=0 (read at every call) leave the
  *    layers that have a kernel of their own to the general one (TSM_STEM_PW=0,
  *    read at every call, keeps the stem on the block-wide one of its two
  *    kernels), and

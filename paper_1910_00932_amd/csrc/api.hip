@@ -201,6 +201,41 @@ static void* prep_pack(BlockPrep& prep, const ConvP& p0, int dtype, bool dgrad, 
 // ---- conv entry points -------------------------------------------------------------------
 enum { CONV_FWD = 0, CONV_DGRAD = 1, CONV_WGRAD = 2 };
 
+// Single convolutions too small for the general kernels' packing, shifted copy, permutation and barriers: a few launches against
+// one of a plain kernel, which wins while the serial sum of its threads is short and all of them together have little to
+// do.  Measured, us, plain and general kernels:
+//   forward        5 -> 7 3x3, 8 frames of 28 x 28 10.7, 12.2; 12 -> 20 1x1 bf16, 32 frames 9.0, 14.5
+//                  32 -> 32 1x1, 8 frames 17.9, 7.3; 20 -> 12 3x3, 4 frames of 7 x 7 31, 10
+//   data gradient  16 -> 16 1x1, 8 frames of 28 x 28 7.5, 10.2; 5 -> 7 3x3, 32 frames 10.7, 19.2
+//                  32 -> 8 3x3, 8 frames 19.1, 10.3; 128 -> 128 1x1, 4 frames of 7 x 7 15.0, 10.0
+//   weight grad.   20 -> 12 3x3, 4 frames of 7 x 7 12.2, 15.4; 128 -> 128 1x1 12.8, 26.6
+//                  20 -> 12 3x3, 8 frames of 14 x 14 35, 17; 128 -> 128 1x1 38, 30
+// With statistics the general kernels, which take them in their epilogue, win at every size.  TSM_PLAIN_CONV=0 (read at every
+// call) keeps these layers on the general kernels.
+static bool plain_conv(int which, const ConvP& p, int dtype, bool stats) {
+    if (use_mfma(p, dtype) || (which == CONV_FWD && stats)) return false;
+    const int ve = dtype == TSM_F32 ? 4 : 8;
+    const bool ragged = p.Cin % ve || p.Cout % ve, f32 = dtype == TSM_F32;   // ragged: element-wise loads in the general kernels
+    auto inside = [&](int in, int out, int k) {   // (tap, position) pairs inside the frame, one dimension
+        long n = 0;
+        for (int o = 0; o < out; ++o) n += std::max(0, std::min(k, in + p.pad - o * p.stride) - std::max(0, p.pad - o * p.stride));
+        return (double)n;
+    };
+    if ((double)p.rows_out() * p.Cin * p.Cout > 16e6) return false;           // (one tap is too much already)
+    const double pairs = inside(p.H, p.Ho, p.KH) * inside(p.W, p.Wo, p.KW);   // of one frame
+    const double macs = pairs * p.F * p.Cin * p.Cout;                         // products of all sums
+    bool plain;
+    if (which == CONV_FWD)
+        plain = pairs / ((double)p.Ho * p.Wo) * p.Cin <= (f32 && !ragged ? 32 : 56) && macs <= (ragged ? 8e6 : f32 ? 2e6 : 4e6);
+    else if (which == CONV_DGRAD)
+        plain = pairs / ((double)p.H * p.W) * p.Cout <= (ragged ? 160 : 64) && macs <= (f32 || ragged ? 13e6 : 6.5e6);
+    else
+        plain = (double)p.Ho * p.Wo * ((p.F + 63) / 64) <= 64 && macs <= 4e6;
+    if (!plain) return false;
+    const char* e = getenv("TSM_PLAIN_CONV");
+    return !(e && e[0] == '0');
+}
+
 static int conv_entry(int which, const tsm_conv_desc* d, const void* a0, const void* a1, void* out, float* ch_sum,
                       float* ch_sumsq, int accumulate, void* wsp, size_t ws_bytes, bool dry, hipStream_t s,
                       size_t* need, bool lean = false) {
@@ -215,7 +250,7 @@ static int conv_entry(int which, const tsm_conv_desc* d, const void* a0, const v
         if (ws_bytes > 0 && !wsp) return fail(TSM_ERR_NULLPTR, "%s: null workspace", who);
     }
     Arena ws(dry ? nullptr : wsp, dry ? (size_t)-1 : ws_bytes);
-    ws.lean = lean;
+    ws.lean = lean = lean || plain_conv(which, p, d->dtype, ch_sum != nullptr);
     if (!dry) {  // size check first, with a dry pass of the same plan
         size_t req = 0;
         TSM_TRY(conv_entry(which, d, a0, a1, out, ch_sum, ch_sumsq, accumulate, nullptr, 0, true, s, &req, lean));
@@ -910,9 +945,11 @@ extern "C" {
 
 size_t tsm_conv_workspace_bytes(const tsm_conv_desc* d) {
     size_t best = 0;
-    for (int which = 0; which < 3; ++which) {
+    float stats;   // (the kernel of a small forward pass depends on whether statistics are asked for; never written)
+    for (int which = 0; which < 4; ++which) {
+        float* sums = which == 3 ? &stats : nullptr;
         size_t need = 0;
-        if (conv_entry(which, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, true, nullptr, &need) != TSM_OK) return 0;
+        if (conv_entry(which == 3 ? CONV_FWD : which, d, nullptr, nullptr, nullptr, sums, sums, 0, nullptr, 0, true, nullptr, &need) != TSM_OK) return 0;
         if (need > best) best = need;
     }
     return best;
@@ -965,10 +1002,10 @@ int tsm_conv_fwd_noalloc(const tsm_conv_desc* d, const void* x, const void* w, v
                          void* stream) {
     size_t need = 0;
     bool lean = false;
-    TSM_TRY(conv_entry(CONV_FWD, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, true, nullptr, &need));
+    TSM_TRY(conv_entry(CONV_FWD, d, nullptr, nullptr, nullptr, ch_sum, ch_sumsq, 0, nullptr, 0, true, nullptr, &need));
     if (need > (size_t)TSM_NOALLOC_SCRATCH_BYTES) {
         lean = true;
-        TSM_TRY(conv_entry(CONV_FWD, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0, true, nullptr, &need, lean));
+        TSM_TRY(conv_entry(CONV_FWD, d, nullptr, nullptr, nullptr, ch_sum, ch_sumsq, 0, nullptr, 0, true, nullptr, &need, lean));
     }
     if (need > (size_t)TSM_NOALLOC_SCRATCH_BYTES)
         return fail(TSM_ERR_WORKSPACE, "tsm_conv_fwd_noalloc: this convolution needs %zu bytes of scratch, the built-in buffer holds %zu",

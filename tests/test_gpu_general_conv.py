@@ -15,6 +15,12 @@ from gpu_util import compare_act, dev_vec, empty_act, from_dev, to_dev
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(autouse=True)
+def _off_the_plain_kernels(monkeypatch):
+    monkeypatch.setenv("TSM_PLAIN_CONV", "0")
+
+
 CASES = [  # N,T,Cin,H,W,Cout,k,stride,pad,fold_div
     (1, 1, 4, 1, 1, 4, 1, 1, 0, 0),           # the smallest call
     (2, 4, 72, 9, 8, 200, 3, 1, 1, 8),        # groups of 9 channels: vectors straddle both group borders
@@ -38,6 +44,49 @@ def test_general_conv_parity(case, dtype):
 @pytest.mark.parametrize("case", [CASES[1], CASES[2]])
 def test_general_conv_parity_paper_order(case):
     TC._run(case, "bf16", "ntchw")
+
+
+SMALL = [  # case, dtype, directions of (fwd, dgrad, wgrad) that run on the plain kernels
+    ((1, 1, 4, 1, 1, 4, 1, 1, 0, 0), "f32", (1, 1, 1)),
+    ((1, 2, 5, 9, 8, 7, 3, 1, 1, 4), "bf16", (1, 1, 0)),        # 38 and 53 products per sum on average; 72 pixels per thread
+    ((1, 3, 12, 8, 8, 20, 3, 2, 1, 5), "bf16", (0, 1, 1)),      # 91 and 38
+    ((1, 1, 21, 6, 6, 25, 3, 1, 1, 0), "bf16", (0, 0, 1)),      # 149 and 178
+    ((1, 2, 24, 8, 8, 16, 1, 1, 0, 8), "bf16", (1, 1, 1)),      # split shift groups
+    ((2, 8, 48, 8, 9, 64, 1, 1, 0, 0), "f32", (0, 1, 0)),       # 3.5 million products
+    ((1, 2, 32, 8, 8, 72, 1, 1, 0, 0), "f32", (1, 0, 1)),
+]
+
+
+@pytest.mark.parametrize("case,dtype,plain", SMALL)
+@pytest.mark.parametrize("layout", ["nthwc", "ntchw"])
+def test_small_calls_on_both_sides_of_the_plain_kernels_line(case, dtype, plain, layout, monkeypatch):
+    """The library's own choice against the general kernels, which the oracle holds above: a result differs by its rounding and
+    by the order of its sum.  (Bounds: one rounding each in bf16; K products in fp32, 1e-5.)"""
+    N, T, Cin, H, W, Cout, k, s, p, fd = case
+    Ho, Wo = (H + 2 * p - k) // s + 1, (W + 2 * p - k) // s + 1
+    x, w = I.normal((N, T, Cin, H, W), 0, dtype), I.kaiming_conv((Cout, Cin, k, k), 1, dtype)
+    dy = I.normal((N, T, Cout, Ho, Wo), 3, dtype)
+    d = B.ConvDesc(N=N, T=T, Cin=Cin, H=H, W=W, Cout=Cout, kh=k, kw=k, stride=s, pad=p, fold_div=fd,
+                   dtype=B.TSM_F32 if dtype == "f32" else B.TSM_BF16, layout=B.TSM_NTHWC if layout == "nthwc" else B.TSM_NTCHW)
+    xd, wd, dyd = to_dev(x, dtype, layout), dev_vec(w, dtype), to_dev(dy, dtype, layout)
+    got = {}
+    for choice in ("1", "0"):
+        monkeypatch.setenv("TSM_PLAIN_CONV", choice)
+        ws = torch.empty(B.tsm_conv_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+        y, dx = empty_act((N, T, Cout, Ho, Wo), dtype, layout), empty_act((N, T, Cin, H, W), dtype, layout)
+        dw = torch.empty((Cout, Cin, k, k), device="cuda")
+        ran = []
+        for call in (lambda: B.tsm_conv_fwd(d, xd, wd, y, None, None, ws), lambda: B.tsm_conv_dgrad(d, dyd, wd, dx, ws),
+                     lambda: B.tsm_conv_wgrad(d, xd, dyd, dw, 0, ws)):
+            B.tsm_profile_begin()
+            call()
+            ran.append(int(any(c.startswith("conv_direct") for c in B.tsm_profile_end())))
+        assert tuple(ran) == (plain if choice == "1" else (0, 0, 0)), ran
+        got[choice] = y, dx, dw
+    for a, b, rel in zip(got["1"], got["0"], (2.0 ** -7 if dtype == "bf16" else 1e-5,) * 2 + (1e-5,)):
+        a, b = a.double(), b.double()
+        assert (a - b).abs().max() <= rel * (b.abs() + b.square().mean().sqrt()).max()
+        assert torch.linalg.norm(a - b) <= rel * torch.linalg.norm(b)
 
 
 @pytest.mark.parametrize("case,kernel", [

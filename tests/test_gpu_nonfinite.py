@@ -12,6 +12,12 @@ from gpu_util import CDT, dev_vec, empty_act, from_dev, to_dev, workspace
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(autouse=True)
+def _off_the_plain_kernels(monkeypatch):
+    monkeypatch.setenv("TSM_PLAIN_CONV", "0")
+
+
 CASES = [  # N,T,Cin,H,W,Cout,k,stride,pad,fold_div,dtype
     (1, 2, 8, 9, 7, 12, 3, 1, 1, 0, "f32"),        # K-split, chunks that cross taps
     (2, 3, 64, 5, 6, 36, 3, 1, 1, 8, "f32"),       # K-split, whole chunks, shifted
