@@ -144,3 +144,74 @@ def test_padding_that_takes_the_offsets_past_2_gib():
         ref += dy[n, 0, inside, inside].reshape(-1, Co).double().t() @ x[n, 0].reshape(-1, C).double()
     # (fp32 sums over chunks of 48096 products: sqrt(48096) * 2^-24 = 1.3e-5, with a factor of three)
     assert torch.linalg.norm(dw.reshape(Co, C).double() - ref) < 4e-5 * torch.linalg.norm(ref)
+
+
+def _shifted(x, fold):   # [N, T, H, W, C] on the device
+    s = torch.zeros_like(x)
+    s[:, :-1, ..., :fold] = x[:, 1:, ..., :fold]
+    s[:, 1:, ..., fold:2 * fold] = x[:, :-1, ..., fold:2 * fold]
+    s[..., 2 * fold:] = x[..., 2 * fold:]
+    return s
+
+
+def _weight_gradient(x, dy, k, fold):
+    """In 64 bits on the device, clip by clip."""
+    ref = torch.zeros((dy.shape[-1], x.shape[-1], k, k), dtype=torch.float64, device="cuda")
+    H, W, p = x.shape[2], x.shape[3], k // 2
+    for n in range(x.shape[0]):
+        xs = torch.nn.functional.pad(_shifted(x[n:n + 1].double(), fold)[0], (0, 0, p, p, p, p))
+        g = dy[n].double().reshape(-1, dy.shape[-1]).t().contiguous()
+        for kh in range(k):
+            for kw in range(k):
+                ref[:, :, kh, kw] += g @ xs[:, kh:kh + H, kw:kw + W].reshape(-1, x.shape[-1])
+    return ref
+
+
+def test_fp32_layers_of_2_gib_and_more():
+    """A shifted 1x1 fp32 layer of 90 clips of 8 x 112 x 112 x 64 (2.3 GB): beyond the K-split kernels' offsets, on the general
+    kernels with whole vectors forward and in the data gradient, on the ragged one in the weight gradient.  Sampled clips
+    against the oracle: the first, the last and the one that holds byte offset 2^31."""
+    N, T, C, H = 90, 8, 64, 112
+    g = torch.Generator(device="cuda")
+    g.manual_seed(0)
+    x = torch.randn((N, T, H, H, C), generator=g, device="cuda")
+    assert x.numel() * 4 >= 0x7ff00000
+    w = I.kaiming_conv((C, C, 1, 1), 1)
+    d = B.ConvDesc(N=N, T=T, Cin=C, H=H, W=H, Cout=C, kh=1, kw=1, stride=1, pad=0, fold_div=8, dtype=B.TSM_F32,
+                   layout=B.TSM_NTHWC)
+    ws = torch.empty(B.tsm_conv_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    y, dx, dw = torch.empty_like(x), torch.empty_like(x), torch.empty((C, C, 1, 1), device="cuda")
+    B.tsm_profile_begin()
+    B.tsm_conv_fwd(d, x, dev_vec(w), y, None, None, ws)
+    B.tsm_conv_dgrad(d, y, dev_vec(w), dx, ws)
+    B.tsm_conv_wgrad(d, x, y, dw, 0, ws)
+    classes = B.tsm_profile_end()
+    assert {"gen_fwd_f32", "gen_dgrad_f32", "gen_wgrad_f32"} <= set(classes), sorted(classes)
+    for n in (0, (1 << 31) // (T * H * H * C * 4), N - 1):
+        xo, yg = from_dev(x[n:n + 1], "nthwc"), from_dev(y[n:n + 1], "nthwc")
+        compare_act(yg, O.conv_fwd(xo, w.astype(np.float64), 1, 0, 8), 1e-4, "fwd clip %d" % n, "f32")
+        compare_act(from_dev(dx[n:n + 1], "nthwc"), O.conv_dgrad(yg, w.astype(np.float64), H, H, 1, 0, 8), 1e-4, "dgrad clip %d" % n, "f32")
+    ref = _weight_gradient(x, y, 1, C // 8)
+    # (fp32 sums over 512 chunks of 17640 products, sqrt(17640) * 2^-24 = 8e-6, and over the chunks; factor of four)
+    assert torch.linalg.norm(dw.double() - ref) < 4e-5 * torch.linalg.norm(ref)
+
+
+def test_ragged_bf16_weight_gradient_of_2_gib_and_more():
+    """72 -> 8 channels 3x3 on 150 clips of 8 x 112 x 112 (2.2 GB): whole vectors, but 64-bit addresses."""
+    N, T, C, Co, H = 150, 8, 72, 8, 112
+    g = torch.Generator(device="cuda")
+    g.manual_seed(0)
+    x = torch.randn((N, T, H, H, C), generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randn((N, T, H, H, Co), generator=g, device="cuda").to(torch.bfloat16)
+    assert x.numel() * 2 >= 0x7ff00000
+    d = B.ConvDesc(N=N, T=T, Cin=C, H=H, W=H, Cout=Co, kh=3, kw=3, stride=1, pad=1, fold_div=9, dtype=B.TSM_BF16,
+                   layout=B.TSM_NTHWC)
+    ws = torch.empty(B.tsm_conv_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    dw = torch.empty((Co, C, 3, 3), device="cuda")
+    B.tsm_profile_begin()
+    B.tsm_conv_wgrad(d, x, dy, dw, 0, ws)
+    classes = B.tsm_profile_end()
+    assert "gen_wgrad_bf16" in classes, sorted(classes)
+    ref = _weight_gradient(x, dy, 3, 8)
+    # (15 million exact products per sum in 46 chunks: sqrt(327k) * 2^-24 = 3.4e-5, with a factor of three)
+    assert torch.linalg.norm(dw.double() - ref) < 1e-4 * torch.linalg.norm(ref)
