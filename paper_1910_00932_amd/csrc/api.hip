@@ -859,9 +859,13 @@ static int block_entry(bool bwd, const tsm_block_desc* d, const void* x, const v
     const char* who = bwd ? "tsm_block_bwd" : "tsm_block_fwd";
     BlockPlan b;
     TSM_TRY(make_block_plan(d, &b, who));
-    // A single block's weight gradients and shortcut run beside its data gradients on CUs that the wider tiles leave to them:
-    // 512 -> 256 -> 1024 on 24 frames of 27 x 35 takes 432 us as it is and 456 with the K-split kernels, although the two
-    // convolutions they would take get shorter (26.5 -> 22.9, 17.4 -> 16.2 us).
+    // A single bf16 block keeps to one wavefront per result at every size.  Where its weight gradients and shortcut fill the CUs
+    // beside its data gradients the K-split kernels are slower (us without and with them: 512 -> 256 -> 1024 on 24 frames of
+    // 27 x 35, stride 2, 385 and 400; 512 -> 128 -> 512 on 16 of 28 x 28 213 and 216).  Small blocks would gain (2048 -> 512 -> 2048 on
+    // 8 of 7 x 7 284 and 200, 1024 -> 256 -> 1024 on 8 of 14 x 14 219 and 194, its temporal twin 245 and 207), at the price of other
+    // roundings to 16 bits: ReLU decisions at zero fall the other way and move gradients by up to 7e-3 (a temporal block 1.2e-2).
+    // Neither result is the nearer one: against 64 bits both are off by 6.3e-2 and 6.6e-2 in dx on two temporal blocks, against
+    // 64 bits with storage in 16 by 3.8e-3 and 3.0e-3 without, 3.7e-3 and 7.2e-3 with them.  (TSM_KSPLIT=1 gives them these layers.)
     for (StageDef& st : b.st) st.p.whole_k = true;
     b.ds.p.whole_k = true;
     const bool tr = d->layout == TSM_NTCHW;

@@ -5,9 +5,10 @@
 // LDS, and only the instruction that multiplies a 16-byte fragment pair differs -- v_mfma_f32_32x32x16_bf16, or four
 // v_mfma_f32_32x32x2_f32 (fp32 products and sums: no precision is given up against a scalar fmaf loop).
 //
-// What bounds them: fp32 runs at the fp32 matrix rate (157 TFLOP/s, 64 cycles per instruction and 4 KB of LDS
-// fragments per 4096 of those cycles: neither LDS nor memory comes close), so plain register prefetch and two stages are
-// enough and tiles are chosen for how well they fill the last round.
+// What bounds them: in fp32 the matrix cores' fp32 rate (157 TFLOP/s; 64 cycles per instruction and 4 KB of LDS fragments per 4096
+// of those cycles: neither LDS nor memory comes close), of which a barrier per step that stops all four wavefronts at
+// once leaves 57 TFLOP/s (6272 x 2304 -> 256; conv_ksplit.hip, without that barrier, 92).  Tiles are chosen for how well they
+// fill the last round.
 //
 // Against one thread per output element (1.2 TFLOP/s whatever the layer; those kernels are kept in direct.hip for strides
 // beyond 2 and filters beyond 8): fp32 train step at 4 clips of 8 x 224^2 655 -> 16.1 ms; bf16 72 -> 200 channels 3x3 at

@@ -6,9 +6,9 @@
 // 64 CUs: 39 us, 0.5 us per step of 64).  Here the wavefronts of a block take every KS-th chunk of 128 bytes of K each,
 // with LDS of their own, so that no barrier stands in the loop and eight chunks are in flight per CU; their partial tiles
 // meet in LDS once at the end (fp32, added in a fixed order).  One tile per block, no persistence: what fills the chip at
-// small sizes is tiles of 32 or 64 rows.  fp32 layers are bound by the fp32 matrix rate at every size; there the point
-// is that the two wavefronts of a SIMD are never in phase (92 TFLOP/s at 6272 x 2304 -> 256, 57 with a block-wide barrier
-// per step).  Two chunks in flight per wavefront instead of one change nothing on the small layers: bytes per CU, not
+// small sizes is tiles of 32 or 64 rows.  fp32 layers have the fp32 matrix rate of 157 TFLOP/s as their bound at every size;
+// there the point is that the two wavefronts of a SIMD are never in phase (92 TFLOP/s at 6272 x 2304 -> 256, 57 with a block-wide
+// barrier per step).  Two chunks in flight per wavefront instead of one change nothing on the small layers: bytes per CU, not
 // latency, are what is left (392 x 4608 -> 512 in 32 x 32 tiles reads 590 KB per CU).
 #include <stdlib.h>
 #include <algorithm>

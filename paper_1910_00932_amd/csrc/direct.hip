@@ -1,6 +1,7 @@
 // Plain one-thread-per-output convolution kernels, channels-innermost frames.
 // They accept any shape and either storage type (fp32 accumulation) and serve
-// the fp32 configurations and every shape the MFMA kernels do not take.
+// strides beyond 2 and filters beyond 8, the forward pass on a fixed scratch
+// that packed weights do not fit, and the smallest fp32 and ragged calls.
 // Same definitions as the fast path: y = conv(S(x)), dx = S^T(conv^T(dy)),
 // dw = sum dy (x) S(x) (paper section 2: shift + per-frame 2-D convolution).
 #include "internal.h"

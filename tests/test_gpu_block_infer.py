@@ -1,7 +1,7 @@
 """tsm_block_infer (forward pass of one block, BatchNorm with running statistics) against the oracle's
 bottleneck_infer: the kernel that runs the 3x3 and the last 1x1 convolution of a bottleneck in one launch, with the
 tensor between them kept on the chip, element by element on ragged shapes, strides and both shortcut kinds; the
-same blocks on one kernel per convolution; the plain fp32 path."""
+same blocks on one kernel per convolution; the fp32 path."""
 import numpy as np
 import pytest
 import torch

@@ -1,7 +1,9 @@
 """Parity of the HIP shift-fused convolution, its data gradient (adjoint shift)
-and weight gradient with the fp64 oracle, element by element, for the plain fp32
-kernels and the bf16 MFMA kernels, in both memory orders.  Sizes span several
-128-row tiles with ragged tails; tolerances are the spec ones (relative L2
+and weight gradient with the fp64 oracle, element by element, in both storage
+types and both memory orders, on the kernels the library picks: the sizes of the
+first list are small enough for the K-split kernels (and for the plain ones in the
+smallest fp32 and ragged gradients); test_gpu_ksplit.py runs it on the kernels for
+larger layers as well.  Sizes span several 128-row tiles with ragged tails; tolerances are the spec ones (relative L2
 1e-4 for fp32, 2e-2 for bf16)."""
 import numpy as np
 import pytest
@@ -23,11 +25,11 @@ CASES = [  # N,T,Cin,H,W,Cout,k,stride,pad,fold_div
     (1, 4, 128, 13, 13, 128, 3, 2, 1, 0),   # strided 3x3
     (1, 2, 256, 9, 9, 512, 1, 2, 0, 0),     # strided projection
     (2, 3, 24, 5, 6, 40, 3, 1, 1, 3),       # ragged channels, fold = 8
-    (1, 2, 20, 5, 5, 12, 3, 1, 1, 8),       # channels not multiple of 8 -> plain kernels
+    (1, 2, 20, 5, 5, 12, 3, 1, 1, 8),       # channels not multiple of 8: general forward kernel
     (1, 1, 16, 6, 6, 16, 1, 1, 0, 4),       # T = 1: both shifted groups read zeros
-    (1, 1, 64, 6, 6, 64, 3, 1, 1, 0),       # fewer pixels than one 256-row tile (most blocks of the grid idle)
-    (1, 4, 64, 10, 10, 64, 1, 1, 0, 8),     # 64 -> 64 1x1 with shift: 256x64 tile, 64x64 weight-gradient tile
-    (2, 2, 128, 9, 9, 320, 1, 1, 0, 0),     # output channels not a multiple of the 128-column tile
+    (1, 1, 64, 6, 6, 64, 3, 1, 1, 0),       # fewer pixels than one tile of any kernel for large layers
+    (1, 4, 64, 10, 10, 64, 1, 1, 0, 8),     # 64 -> 64 1x1 with shift: 64x64 weight-gradient tile
+    (2, 2, 128, 9, 9, 320, 1, 1, 0, 0),     # output channels not a multiple of a 128-column tile
     (1, 2, 192, 7, 7, 64, 3, 1, 1, 8),      # three 64-channel steps per tap, shift inside the first step only
 ]
 

@@ -45,7 +45,7 @@ def run_infer(N, T, S, dtype, flat, clips, state, K=400, fold_div=8):
 
 
 def test_infer_fp32_against_oracle():
-    """fp32 storage, plain kernels: every layer's wiring, BatchNorm slots and the head, to 1e-4."""
+    """fp32 storage: every layer's wiring, BatchNorm slots and the head, to 1e-4."""
     N, T, S = 2, 4, 64
     table, flat, clips, P, state = setup(N, T, S, "f32")
     got = run_infer(N, T, S, "f32", flat, clips, state)

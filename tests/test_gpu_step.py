@@ -104,7 +104,7 @@ def test_param_table_matches_the_oracles():
 
 
 def test_step_fp32_against_oracle():
-    """The whole step in fp32 storage (same host code, plain kernels) against the fp64 oracle: pins the
+    """The whole step in fp32 storage (same host code, the fp32 kernels) against the fp64 oracle: pins the
     wiring of stem, pooling, 16 blocks, head, loss, all 161 gradients and the update.
     Forward quantities are held to 1e-4.  Gradients of a ReLU network are discontinuous in the
     forward values: the fp32 forward differs from fp64 by about 1e-5, which flips the mask of the few
