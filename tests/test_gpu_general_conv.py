@@ -215,3 +215,20 @@ def test_ragged_bf16_weight_gradient_of_2_gib_and_more():
     ref = _weight_gradient(x, dy, 3, 8)
     # (15 million exact products per sum in 46 chunks: sqrt(327k) * 2^-24 = 3.4e-5, with a factor of three)
     assert torch.linalg.norm(dw.double() - ref) < 1e-4 * torch.linalg.norm(ref)
+
+
+def test_fp32_weight_gradient_sums_in_two_levels():
+    """512 -> 512 channels 3x3 on 32 frames of 7 x 7, whose chunks are 523 pixels: within 3 * 2^-24 of 64 bits (1.1e-7 measured;
+    2.6e-7 as one chain of 523, 1.3e-7 as a sum per frame)."""
+    N, T, C, H = 4, 8, 512, 7
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    x = torch.randn((N, T, H, H, C), generator=g, device="cuda").relu()
+    dy = torch.randn((N, T, H, H, C), generator=g, device="cuda")
+    d = B.ConvDesc(N=N, T=T, Cin=C, H=H, W=H, Cout=C, kh=3, kw=3, stride=1, pad=1, fold_div=8, dtype=B.TSM_F32,
+                   layout=B.TSM_NTHWC)
+    ws = torch.empty(B.tsm_conv_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    dw = torch.empty((C, C, 3, 3), device="cuda")
+    B.tsm_conv_wgrad(d, x, dy, dw, 0, ws)
+    ref = _weight_gradient(x, dy, 3, C // 8)
+    assert torch.linalg.norm(dw.double() - ref) < 3 * 2.0 ** -24 * torch.linalg.norm(ref)
