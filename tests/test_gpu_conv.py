@@ -3,8 +3,8 @@ and weight gradient with the fp64 oracle, element by element, in both storage
 types and both memory orders, on the kernels the library picks: the sizes of the
 first list are small enough for the K-split kernels (and for the plain ones in the
 smallest fp32 and ragged gradients); test_gpu_ksplit.py runs it on the kernels for
-larger layers as well.  Sizes span several 128-row tiles with ragged tails; tolerances are the spec ones (relative L2
-1e-4 for fp32, 2e-2 for bf16)."""
+larger layers as well.  Sizes span several 128-row tiles with ragged tails; tolerances are 1e-4
+(fp32) and 2e-2 (bf16) relative L2."""
 import numpy as np
 import pytest
 import torch
