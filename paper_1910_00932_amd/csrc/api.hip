@@ -420,39 +420,57 @@ static int wgrad_join(SideStream* ss, bool forked, hipStream_t s) {
     return TSM_OK;
 }
 
-// The projection shortcut (convolution + BatchNorm statistics) depends on the block input only: it runs on the side
-// stream beside the first convolution, which reads the same tensor, and is joined in front of the block's tail.
-static int block_fwd_stages(BlockPlan& b, const void* x, Arena& ws, bool dry, hipStream_t s) {
+// A stage's BatchNorm whose sums lie in `nrows` partial rows, going forward.
+static BnSums fwd_sums(const StageDef& st, const BnVec& v, const float* partial, int nrows) {
+    return BnSums{partial, nrows, st.g, st.b, v, st.run_mean, st.run_var, nullptr, nullptr};
+}
+static BnSums bwd_sums(const StageDef& st, const BnVec& v, const float* partial, int nrows) {
+    return BnSums{partial, nrows, st.g, nullptr, v, nullptr, nullptr, st.dg, st.db};
+}
+
+// One convolution with the sums of its BatchNorm; finalize: the sums become the BatchNorm's vectors in a launch of their own.
+static int conv_sums(BlockPlan& b, StageDef& st, const BnVec& v, const void* x, void* y, bool finalize, BnSums* sums, Arena& ws,
+                     bool dry, hipStream_t s) {
+    const int nb = conv_stats_blocks(st.p, b.dtype, ws);
+    float* part = ws.take_n<float>((size_t)nb * 2 * st.p.Cout);
+    TSM_TRY(run_conv_fwd(st.p, b.dtype, x, st.w, st.wp, y, part, ws, dry, s));
+    *sums = fwd_sums(st, v, part, nb);
+    if (finalize)
+        RUN(bn_finalize(part, nb, st.p.rows_out(), st.p.Cout, st.g, st.b, b.eps, v, st.run_mean, st.run_var, b.bn_momentum, s));
+    return TSM_OK;
+}
+
+static bool fold_stage(const BlockPlan& b, const StageDef& st, const Arena& ws) {
+    return bn_fold_use(b.dtype, conv_stats_blocks(st.p, b.dtype, ws), st.p.rows_out(), st.p.Cout);
+}
+
+// The convolutions of the residual branch.  The last one's BatchNorm is the tail's: with fold_tail its sums are left for it.
+static int block_fwd_stages(BlockPlan& b, const void* x, bool fold_tail, BnSums* last, Arena& ws, bool dry, hipStream_t s) {
     const void* cur = x;
     for (int i = 0; i < b.nst; ++i) {
         StageDef& st = b.st[i];
-        const int nb = conv_stats_blocks(st.p, b.dtype, ws);
-        float* part = ws.take_n<float>((size_t)nb * 2 * st.p.Cout);
-        TSM_TRY(run_conv_fwd(st.p, b.dtype, cur, st.w, st.wp, b.y[i], part, ws, dry, s));
-        RUN(bn_finalize(part, nb, st.p.rows_out(), st.p.Cout, st.g, st.b, b.eps, b.bn[i], st.run_mean, st.run_var,
-                        b.bn_momentum, s));
+        const bool fold = i + 1 < b.nst ? fold_stage(b, st, ws) : fold_tail;
+        TSM_TRY(conv_sums(b, st, b.bn[i], cur, b.y[i], !fold, last, ws, dry, s));
         if (i + 1 < b.nst) {
-            RUN(bn_relu_apply(b.dtype, b.y[i], st.p.rows_out(), st.p.Cout, b.bn[i].scale, b.bn[i].shift, b.z[i], s));
+            if (fold)
+                RUN(bn_fold_relu(b.dtype, *last, b.eps, b.bn_momentum, b.y[i], st.p.rows_out(), st.p.Cout, b.z[i], s));
+            else
+                RUN(bn_relu_apply(b.dtype, b.y[i], st.p.rows_out(), st.p.Cout, b.bn[i].scale, b.bn[i].shift, b.z[i], s));
             cur = b.z[i];
         }
     }
     return TSM_OK;
 }
 
-static int block_fwd_shortcut(BlockPlan& b, const void* x, Arena& ws, bool dry, hipStream_t s) {
-    StageDef& st = b.ds;
-    const int nb = conv_stats_blocks(st.p, b.dtype, ws);
-    float* part = ws.take_n<float>((size_t)nb * 2 * st.p.Cout);
-    TSM_TRY(run_conv_fwd(st.p, b.dtype, x, st.w, st.wp, b.yd, part, ws, dry, s));
-    RUN(bn_finalize(part, nb, st.p.rows_out(), st.p.Cout, st.g, st.b, b.eps, b.bnd, st.run_mean, st.run_var,
-                    b.bn_momentum, s));
-    return TSM_OK;
-}
-
+// The projection shortcut (convolution + BatchNorm statistics) depends on the block input only: it runs on the side
+// stream beside the first convolution, which reads the same tensor, and is joined in front of the block's tail.
 int block_fwd_impl(BlockPlan& b, const void* x, void* out, Arena& ws, bool dry, hipStream_t s) {
     SideStream* const ss = (dry || !b.proj || !shortcut_branch_enabled()) ? nullptr : side_stream();
     bool forked = false;
     int rc = TSM_OK;
+    const int L = b.nst - 1;
+    const bool fold_tail = fold_stage(b, b.st[L], ws) && (!b.proj || fold_stage(b, b.ds, ws));
+    BnSums sums, sums_d;
     if (b.proj) {
         hipStream_t sd = s;
         if (ss) {
@@ -461,14 +479,18 @@ int block_fwd_impl(BlockPlan& b, const void* x, void* out, Arena& ws, bool dry, 
             forked = true;
             sd = ss->stream;
         }
-        rc = block_fwd_shortcut(b, x, ws, dry, sd);
+        rc = conv_sums(b, b.ds, b.bnd, x, b.yd, !fold_tail, &sums_d, ws, dry, sd);
     }
-    if (rc == TSM_OK) rc = block_fwd_stages(b, x, ws, dry, s);
+    if (rc == TSM_OK) rc = block_fwd_stages(b, x, fold_tail, &sums, ws, dry, s);
     const int rj = wgrad_join(ss, forked, s);      // on every path: a caller's stream capture must not keep an open branch
     if (rc != TSM_OK) return rc;
     if (rj != TSM_OK) return rj;
-    const int L = b.nst - 1;
     const ConvP& pl = b.st[L].p;
+    if (fold_tail) {
+        RUN(bn_fold_tail(b.dtype, sums, b.proj ? &sums_d : nullptr, b.eps, b.bn_momentum, b.y[L], b.proj ? b.yd : x, pl.rows_out(), pl.Cout,
+                         out, b.out_bits, s));
+        return TSM_OK;
+    }
     RUN(block_tail_fwd(b.dtype, b.y[L], pl.rows_out(), pl.Cout, b.bn[L].scale, b.bn[L].shift, b.proj ? b.yd : x,
                        b.proj ? b.bnd.scale : nullptr, b.proj ? b.bnd.shift : nullptr, out, s, b.out_bits));
     return TSM_OK;
@@ -675,15 +697,24 @@ static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const vo
                                b.proj ? b.yd : nullptr, b.proj ? b.bnd.mean : nullptr, b.proj ? b.bnd.rstd : nullptr,
                                b.proj ? partd : nullptr, s));
     }
-    RUN(bn_bwd_coeffs(partL, nbL, pl.rows_out(), pl.Cout, b.bn[L].mean, b.bn[L].rstd, b.st[L].g, coefL, b.st[L].dg,
-                      b.st[L].db, s));
+    const bool foldL = bn_fold_use(b.dtype, nbL, pl.rows_out(), pl.Cout);
+    const BnSums sumsL = bwd_sums(b.st[L], b.bn[L], partL, nbL);
+    if (!foldL)
+        RUN(bn_bwd_coeffs(partL, nbL, pl.rows_out(), pl.Cout, b.bn[L].mean, b.bn[L].rstd, b.st[L].g, coefL, b.st[L].dg,
+                          b.st[L].db, s));
     // a projection shortcut's BatchNorm takes the same upstream gradient: both are applied from one read of it
     void* dyd = nullptr;
     if (b.proj) {
         dyd = ws.take(out_bytes);
         float* coefd = ws.take_n<float>(3 * (size_t)pl.Cout);
-        RUN(bn_bwd_coeffs(partd, nbL, pl.rows_out(), pl.Cout, b.bnd.mean, b.bnd.rstd, b.ds.g, coefd, b.ds.dg, b.ds.db, s));
-        RUN(bn_bwd_apply2(b.dtype, dzL, b.y[L], coefL, dyL, b.yd, coefd, dyd, pl.rows_out(), pl.Cout, s));
+        if (foldL) {
+            RUN(bn_fold_bwd2(b.dtype, sumsL, bwd_sums(b.ds, b.bnd, partd, nbL), dzL, b.y[L], dyL, b.yd, dyd, pl.rows_out(), pl.Cout, s));
+        } else {
+            RUN(bn_bwd_coeffs(partd, nbL, pl.rows_out(), pl.Cout, b.bnd.mean, b.bnd.rstd, b.ds.g, coefd, b.ds.dg, b.ds.db, s));
+            RUN(bn_bwd_apply2(b.dtype, dzL, b.y[L], coefL, dyL, b.yd, coefd, dyd, pl.rows_out(), pl.Cout, s));
+        }
+    } else if (foldL) {
+        RUN(bn_fold_bwd(b.dtype, sumsL, dzL, b.y[L], pl.rows_out(), pl.Cout, dyL, s));
     } else {
         RUN(bn_bwd_apply(b.dtype, dzL, b.y[L], pl.rows_out(), pl.Cout, coefL, dyL, s));
     }
@@ -745,9 +776,13 @@ static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const vo
             RUN(relu_bn_bwd_reduce(b.dtype, dzin, b.z[i - 1], b.y[i - 1], pp.rows_out(), pp.Cout, b.bn[i - 1].mean,
                                    b.bn[i - 1].rstd, dzin, part, nullptr, nullptr, nullptr, nullptr, s));
         }
-        RUN(bn_bwd_coeffs(part, nb, pp.rows_out(), pp.Cout, b.bn[i - 1].mean, b.bn[i - 1].rstd, b.st[i - 1].g, coef,
-                          b.st[i - 1].dg, b.st[i - 1].db, s));
-        RUN(bn_bwd_apply(b.dtype, dzin, b.y[i - 1], pp.rows_out(), pp.Cout, coef, dzin, s));
+        if (bn_fold_use(b.dtype, nb, pp.rows_out(), pp.Cout)) {
+            RUN(bn_fold_bwd(b.dtype, bwd_sums(b.st[i - 1], b.bn[i - 1], part, nb), dzin, b.y[i - 1], pp.rows_out(), pp.Cout, dzin, s));
+        } else {
+            RUN(bn_bwd_coeffs(part, nb, pp.rows_out(), pp.Cout, b.bn[i - 1].mean, b.bn[i - 1].rstd, b.st[i - 1].g, coef,
+                              b.st[i - 1].dg, b.st[i - 1].db, s));
+            RUN(bn_bwd_apply(b.dtype, dzin, b.y[i - 1], pp.rows_out(), pp.Cout, coef, dzin, s));
+        }
         g = dzin;
     }
     TSM_TRY(wgrad_beside(ss, &forked, b.st[0].p, b.dtype, x, g, b.st[0].dw, b.st[0].dwp, acc_flag(b.st[0]), ws, dry, s));

@@ -206,6 +206,25 @@ __device__ __forceinline__ void sum_partials(const float* __restrict__ partial, 
 }
 
 // ---- partial statistics -> per-channel vectors ------------------------------------------------------
+struct BnMoments { float mean, rstd; double var; };
+__device__ __forceinline__ BnMoments bn_moments(double s1, double s2, double inv_m, float eps) {
+    const double mean = s1 * inv_m;
+    double var = s2 * inv_m - mean * mean;
+    if (var < 0) var = 0;
+    return {(float)mean, (float)(1.0 / sqrt(var + (double)eps)), var};
+}
+__device__ __forceinline__ void bn_store(const BnVec& o, float* run_mean, float* run_var, int c, const BnMoments& m, float scale,
+                                         float shift, double unbias, float momentum) {
+    o.mean[c] = m.mean;
+    o.rstd[c] = m.rstd;
+    o.scale[c] = scale;
+    o.shift[c] = shift;
+    if (run_mean) {
+        run_mean[c] = (1.f - momentum) * run_mean[c] + momentum * m.mean;
+        run_var[c] = (1.f - momentum) * run_var[c] + momentum * (float)(m.var * unbias);
+    }
+}
+
 __global__ void __launch_bounds__(SP_C * SP_R) bn_finalize_kernel(const float* __restrict__ partial, int nblocks, double inv_m, double unbias, int C,
                                    const float* __restrict__ gamma, const float* __restrict__ beta, float eps,
                                    BnVec o, float* run_mean, float* run_var, float momentum) {
@@ -213,20 +232,10 @@ __global__ void __launch_bounds__(SP_C * SP_R) bn_finalize_kernel(const float* _
     double s1, s2;
     sum_partials(partial, nblocks, C, c, &s1, &s2);
     if (c >= C || threadIdx.y != 0) return;
-    const double mean = s1 * inv_m;
-    double var = s2 * inv_m - mean * mean;
-    if (var < 0) var = 0;
-    const float rstd = (float)(1.0 / sqrt(var + (double)eps));
+    const BnMoments m = bn_moments(s1, s2, inv_m, eps);
     const float g = gamma ? gamma[c] : 1.f;
     const float b = beta ? beta[c] : 0.f;
-    o.mean[c] = (float)mean;
-    o.rstd[c] = rstd;
-    o.scale[c] = g * rstd;
-    o.shift[c] = b - (float)mean * g * rstd;
-    if (run_mean) {
-        run_mean[c] = (1.f - momentum) * run_mean[c] + momentum * (float)mean;
-        run_var[c] = (1.f - momentum) * run_var[c] + momentum * (float)(var * unbias);
-    }
+    bn_store(o, run_mean, run_var, c, m, g * m.rstd, b - m.mean * g * m.rstd, unbias, momentum);
 }
 
 int bn_finalize(const float* partial, int nblocks, long rows, int C, const float* gamma, const float* beta, float eps,
@@ -431,6 +440,12 @@ int relu_bn_bwd_reduce(int dtype, const void* dout, const void* act, const void*
 // dy = gamma*rstd*(dz - S1/m - yhat*S2/m), yhat = (y-mean)*rstd, rewritten as dy = a*dz + b*y + c with
 //   a = gamma*rstd,  b = -gamma*rstd^2*S2/m,  c = gamma*rstd*(mean*rstd*S2/m - S1/m);
 // dbeta = S1, dgamma = S2.
+struct BnCoef { float a, b, c; };
+__device__ __forceinline__ BnCoef bn_coef(double s1, double s2, double inv_m, float g, float mu, float rs) {
+    const float m1 = (float)(s1 * inv_m), m2 = (float)(s2 * inv_m);
+    return {g * rs, -g * rs * rs * m2, g * rs * (mu * rs * m2 - m1)};
+}
+
 __global__ void __launch_bounds__(SP_C * SP_R) bn_bwd_coeffs_kernel(const float* __restrict__ partial, int nblocks, double inv_m, int C,
                                      const float* __restrict__ mean, const float* __restrict__ rstd,
                                      const float* __restrict__ gamma, float* __restrict__ coef,
@@ -439,12 +454,10 @@ __global__ void __launch_bounds__(SP_C * SP_R) bn_bwd_coeffs_kernel(const float*
     double s1, s2;
     sum_partials(partial, nblocks, C, c, &s1, &s2);
     if (c >= C || threadIdx.y != 0) return;
-    const float g = gamma ? gamma[c] : 1.f;
-    const float rs = rstd[c], mu = mean[c];
-    const float m1 = (float)(s1 * inv_m), m2 = (float)(s2 * inv_m);
-    coef[c] = g * rs;
-    coef[C + c] = -g * rs * rs * m2;
-    coef[2 * C + c] = g * rs * (mu * rs * m2 - m1);
+    const BnCoef k = bn_coef(s1, s2, inv_m, gamma ? gamma[c] : 1.f, mean[c], rstd[c]);
+    coef[c] = k.a;
+    coef[C + c] = k.b;
+    coef[2 * C + c] = k.c;
     if (dbeta) dbeta[c] = (float)s1;
     if (dgamma) dgamma[c] = (float)s2;
 }
@@ -550,6 +563,217 @@ int bn_bwd_apply(int dtype, const void* dz, const void* y, long rows, int C, con
                       : bn_bwd_apply_tv<float, 1>((const float*)dz, (const float*)y, rows, C, coef, (float*)dy, s);
     return v == 8 ? bn_bwd_apply_tv<bf16_t, 8>((const bf16_t*)dz, (const bf16_t*)y, rows, C, coef, (bf16_t*)dy, s)
                   : bn_bwd_apply_tv<bf16_t, 1>((const bf16_t*)dz, (const bf16_t*)y, rows, C, coef, (bf16_t*)dy, s);
+}
+
+// ---- BatchNorm's sums finished inside the pass that needs them ---------------------------------------------------------
+// Between two convolutions stand the sums of the first's partial rows (bn_finalize, bn_bwd_coeffs: a launch of pure latency)
+// and the elementwise pass that waits for them.  Where the rows are few, every block of the elementwise pass adds them up
+// itself for its slab of 128 bytes of channels, in fp64 and in one fixed order (so all blocks hold the same coefficients),
+// after it has requested its first rows; the first block of a slab leaves the vectors behind that later kernels read.  Latency is
+// what bounds it: 4.5 us at 6400 x 128 bf16 where the two launches took 3.8 and 2.8.
+static constexpr int FOLD_TX = 8, FOLD_TY = 32, FOLD_UR = 4;   // threads along a row and rows; rows per thread in flight
+static constexpr int FOLD_NT = FOLD_TX * FOLD_TY;
+enum { FOLD_RELU, FOLD_TAIL, FOLD_TAIL_PROJ, FOLD_BWD, FOLD_BWD2 };
+
+struct FoldArgs {
+    BnSums bn[2];
+    double inv_m, unbias;
+    float eps, momentum;
+    long rows;
+    int C;
+    const void *in0, *in1, *in2;   // RELU: y; TAIL: y, shortcut; BWD: dz, y; BWD2: dz, y1, y2
+    void *out0, *out1;
+    uint8_t* bits;
+    bool stream;
+};
+
+// Totals of the slab's channels c0 .. c0 + CS: s_tot[0..CS) first, s_tot[CS..2*CS) second sums.  Ends with a barrier.
+template <int CS>
+__device__ __forceinline__ void fold_sums(const float* partial, int nrows, int C, int c0, double (*s_red)[2 * CS], double* s_tot) {
+    constexpr int Q = 2 * CS / 4, RL = FOLD_NT / Q, U = 16;   // 16-byte pieces of a row, rows read side by side, in flight
+    const int tid = threadIdx.x, q = tid % Q, rl = tid / Q;
+    const float* p = partial + (q / (CS / 4)) * C + c0 + (q % (CS / 4)) * 4;
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int r0 = rl; r0 < nrows; r0 += U * RL) {
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {   // rows beyond the end re-read the last one and count as zero: no branch around the loads
+            const int r = r0 + u * RL;
+            v[u] = *(const float4*)(p + (size_t)(r < nrows ? r : nrows - 1) * 2 * C);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = r0 + u * RL < nrows;
+            t[0] += in ? (double)v[u].x : 0.0;
+            t[1] += in ? (double)v[u].y : 0.0;
+            t[2] += in ? (double)v[u].z : 0.0;
+            t[3] += in ? (double)v[u].w : 0.0;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s_red[rl][q * 4 + k] = t[k];
+    __syncthreads();
+    if (tid < 2 * CS) {
+        double v = 0.0;
+#pragma unroll
+        for (int l = 0; l < RL; ++l) v += s_red[l][tid];
+        s_tot[tid] = v;
+    }
+    __syncthreads();
+}
+
+template <typename T, int V, int MODE>
+__global__ void __launch_bounds__(FOLD_NT) bn_fold_kernel(FoldArgs a) {
+    constexpr int CS = FOLD_TX * V;
+    constexpr bool FWD = MODE <= FOLD_TAIL_PROJ;
+    constexpr int NBN = MODE == FOLD_TAIL_PROJ || MODE == FOLD_BWD2 ? 2 : 1;
+    constexpr int NIN = MODE == FOLD_RELU ? 1 : MODE == FOLD_BWD2 ? 3 : 2;
+    __shared__ double s_red[FOLD_NT / (CS / 2)][2 * CS], s_tot[2 * CS];
+    __shared__ float s_co[NBN][3][CS];
+    typedef Pack<T, V> P;
+    const int tid = threadIdx.x, tx = tid % FOLD_TX, ty = tid / FOLD_TX;
+    const int c0 = blockIdx.y * CS, C = a.C;
+    const void* const src[3] = {a.in0, a.in1, a.in2};
+    const long step = (long)gridDim.x * (FOLD_TY * FOLD_UR);
+    long r0 = (long)blockIdx.x * (FOLD_TY * FOLD_UR) + ty;
+    P in[NIN][FOLD_UR];
+    auto load = [&](long r0) {
+#pragma unroll
+        for (int u = 0; u < FOLD_UR; ++u) {   // (rows beyond the end read the last one and are not stored)
+            const long r = r0 + u * FOLD_TY;
+            const long off = (r < a.rows ? r : a.rows - 1) * C + c0 + tx * V;
+#pragma unroll
+            for (int k = 0; k < NIN; ++k) in[k][u] = *(const P*)((const T*)src[k] + off);
+        }
+    };
+    load(r0);
+#pragma unroll
+    for (int n = 0; n < NBN; ++n) {
+        const BnSums& b = a.bn[n];
+        fold_sums<CS>(b.partial, b.nrows, C, c0, s_red, s_tot);
+        if (tid < CS) {
+            const int c = c0 + tid;
+            const double s1 = s_tot[tid], s2 = s_tot[CS + tid];
+            const bool first = blockIdx.x == 0;
+            if (FWD) {
+                const BnMoments m = bn_moments(s1, s2, a.inv_m, a.eps);
+                const float g = b.gamma ? b.gamma[c] : 1.f, be = b.beta ? b.beta[c] : 0.f;
+                const float sc = g * m.rstd, sh = be - m.mean * g * m.rstd;
+                s_co[n][0][tid] = sc;
+                s_co[n][1][tid] = sh;
+                if (first) bn_store(b.vec, b.run_mean, b.run_var, c, m, sc, sh, a.unbias, a.momentum);
+            } else {
+                const BnCoef k = bn_coef(s1, s2, a.inv_m, b.gamma ? b.gamma[c] : 1.f, b.vec.mean[c], b.vec.rstd[c]);
+                s_co[n][0][tid] = k.a;
+                s_co[n][1][tid] = k.b;
+                s_co[n][2][tid] = k.c;
+                if (first && b.dbeta) b.dbeta[c] = (float)s1;
+                if (first && b.dgamma) b.dgamma[c] = (float)s2;
+            }
+        }
+        __syncthreads();
+    }
+    float co[NBN][3][V];
+#pragma unroll
+    for (int n = 0; n < NBN; ++n)
+#pragma unroll
+        for (int k = 0; k < (FWD ? 2 : 3); ++k)
+#pragma unroll
+            for (int j = 0; j < V; ++j) co[n][k][j] = s_co[n][k][tx * V + j];
+    for (; r0 < a.rows + ty; r0 += step) {   // (every thread of a block makes the same number of turns)
+        P o0[FOLD_UR], o1[MODE == FOLD_BWD2 ? FOLD_UR : 1];
+        unsigned m[FOLD_UR];
+#pragma unroll
+        for (int u = 0; u < FOLD_UR; ++u) {
+            m[u] = 0;
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                const float x0 = Elem<T>::ld(in[0][u].v[j]);
+                if constexpr (MODE == FOLD_RELU) {
+                    const float v = fmaf(x0, co[0][0][j], co[0][1][j]);
+                    o0[u].v[j] = Elem<T>::st(v > 0.f ? v : 0.f);
+                } else if constexpr (FWD) {
+                    float rr = Elem<T>::ld(in[1][u].v[j]);
+                    if (MODE == FOLD_TAIL_PROJ) rr = fmaf(rr, co[NBN - 1][0][j], co[NBN - 1][1][j]);
+                    const float v = fmaf(x0, co[0][0][j], co[0][1][j]) + rr;
+                    o0[u].v[j] = Elem<T>::st(v > 0.f ? v : 0.f);
+                    m[u] |= (Elem<T>::ld(o0[u].v[j]) > 0.f ? 1u : 0u) << j;
+                } else {
+                    o0[u].v[j] = Elem<T>::st(fmaf(co[0][0][j], x0, fmaf(co[0][1][j], Elem<T>::ld(in[1][u].v[j]), co[0][2][j])));
+                    if constexpr (MODE == FOLD_BWD2)
+                        o1[u].v[j] = Elem<T>::st(fmaf(co[1][0][j], x0, fmaf(co[1][1][j], Elem<T>::ld(in[2][u].v[j]), co[1][2][j])));
+                }
+            }
+        }
+        const long rn = r0 + step;
+        if (rn - ty < a.rows) load(rn);
+#pragma unroll
+        for (int u = 0; u < FOLD_UR; ++u) {
+            const long r = r0 + u * FOLD_TY;
+            if (r >= a.rows) continue;
+            const long off = r * C + c0 + tx * V;
+            store_pack<T, V>((T*)a.out0 + off, o0[u], FWD && a.stream);
+            if constexpr (MODE == FOLD_BWD2) *(P*)((T*)a.out1 + off) = o1[u];
+            if constexpr (V == 8 && (MODE == FOLD_TAIL || MODE == FOLD_TAIL_PROJ))
+                if (a.bits) a.bits[off / 8] = (uint8_t)m[u];
+        }
+    }
+}
+
+// Up to FOLD_ROWS partial rows a block's own sums cost less than the launch they replace (4 - 5 us each, 106 of them per step).
+// Train step of 2 clips of 160 x 160, four micro-batches, us by the line's place: no folding 11837, 64 rows 11554, 128 11488, 256
+// 11582, 512 11667; 8 clips of 224 x 224 6657, 6659, 6649, 6731, 6744 (256 rows of 64 channels are 128 KB per block).
+static constexpr int FOLD_ROWS = 128, FOLD_BLOCKS = 512;
+bool bn_fold_use(int dtype, int nrows, long rows, int C) {
+    return C % (FOLD_TX * (dtype == TSM_F32 ? 4 : 8)) == 0 && rows > 0 && nrows > 0 && nrows <= FOLD_ROWS;
+}
+
+template <typename T, int V, int MODE>
+static int fold_launch(FoldArgs& a, hipStream_t s, const char* what) {
+    const int slabs = a.C / (FOLD_TX * V);
+    long gx = (a.rows + FOLD_TY * FOLD_UR - 1) / (FOLD_TY * FOLD_UR);
+    const long most = FOLD_BLOCKS / slabs > 1 ? FOLD_BLOCKS / slabs : 1;
+    if (gx > most) gx = most;
+    bn_fold_kernel<T, V, MODE><<<dim3((unsigned)gx, (unsigned)slabs), dim3(FOLD_NT), 0, s>>>(a);
+    return check_launch(what);
+}
+
+static FoldArgs fold_args(const BnSums& b0, const BnSums* b1, long rows, int C, int dtype) {
+    FoldArgs a = {};
+    a.bn[0] = b0;
+    if (b1) a.bn[1] = *b1;
+    a.rows = rows; a.C = C;
+    a.inv_m = 1.0 / (double)rows;
+    a.unbias = rows > 1 ? (double)rows / (double)(rows - 1) : 1.0;
+    a.stream = stream_result(rows, C, dtype);
+    return a;
+}
+
+int bn_fold_relu(int dtype, const BnSums& b, float eps, float momentum, const void* y, long rows, int C, void* z, hipStream_t s) {
+    FoldArgs a = fold_args(b, nullptr, rows, C, dtype);
+    a.eps = eps; a.momentum = momentum; a.in0 = y; a.out0 = z; a.stream = false;
+    return dtype == TSM_F32 ? fold_launch<float, 4, FOLD_RELU>(a, s, "bn_fold_relu") : fold_launch<bf16_t, 8, FOLD_RELU>(a, s, "bn_fold_relu");
+}
+
+int bn_fold_tail(int dtype, const BnSums& b, const BnSums* bd, float eps, float momentum, const void* y, const void* shortcut,
+                 long rows, int C, void* out, uint8_t* out_bits, hipStream_t s) {
+    FoldArgs a = fold_args(b, bd, rows, C, dtype);
+    a.eps = eps; a.momentum = momentum; a.in0 = y; a.in1 = shortcut; a.out0 = out; a.bits = out_bits;
+    if (dtype == TSM_F32) return bd ? fold_launch<float, 4, FOLD_TAIL_PROJ>(a, s, "bn_fold_tail") : fold_launch<float, 4, FOLD_TAIL>(a, s, "bn_fold_tail");
+    return bd ? fold_launch<bf16_t, 8, FOLD_TAIL_PROJ>(a, s, "bn_fold_tail") : fold_launch<bf16_t, 8, FOLD_TAIL>(a, s, "bn_fold_tail");
+}
+
+int bn_fold_bwd(int dtype, const BnSums& b, const void* dz, const void* y, long rows, int C, void* dy, hipStream_t s) {
+    FoldArgs a = fold_args(b, nullptr, rows, C, dtype);
+    a.in0 = dz; a.in1 = y; a.out0 = dy;
+    return dtype == TSM_F32 ? fold_launch<float, 4, FOLD_BWD>(a, s, "bn_fold_bwd") : fold_launch<bf16_t, 8, FOLD_BWD>(a, s, "bn_fold_bwd");
+}
+
+int bn_fold_bwd2(int dtype, const BnSums& b1, const BnSums& b2, const void* dz, const void* y1, void* dy1, const void* y2, void* dy2,
+                 long rows, int C, hipStream_t s) {
+    FoldArgs a = fold_args(b1, &b2, rows, C, dtype);
+    a.in0 = dz; a.in1 = y1; a.in2 = y2; a.out0 = dy1; a.out1 = dy2;
+    return dtype == TSM_F32 ? fold_launch<float, 4, FOLD_BWD2>(a, s, "bn_fold_bwd") : fold_launch<bf16_t, 8, FOLD_BWD2>(a, s, "bn_fold_bwd");
 }
 
 // ---- out = a + b ------------------------------------------------------------------------------

@@ -95,6 +95,24 @@ int bn_bwd_apply(int dtype, const void* dz, const void* y, long rows, int C, con
 // (y2, coef2).  No buffer may alias another.
 int bn_bwd_apply2(int dtype, const void* dz, const void* y1, const float* coef1, void* dy1, const void* y2,
                   const float* coef2, void* dy2, long rows, int C, hipStream_t s);
+// The same passes with the sums finished in them: bn_finalize + bn_relu_apply / block_tail_fwd (bd: the projection's
+// BatchNorm, whose raw output `shortcut` then is), bn_bwd_coeffs + bn_bwd_apply / bn_bwd_apply2, in one launch each.
+struct BnSums {
+    const float* partial;               // [nrows][2*C]
+    int nrows;
+    const float *gamma, *beta;
+    BnVec vec;                          // forward: written; backward: mean and rstd are read
+    float *run_mean, *run_var;          // forward, nullable
+    float *dgamma, *dbeta;              // backward, nullable
+};
+// Whether a pass over [rows][C] finishes the sums of nrows partial rows itself.
+bool bn_fold_use(int dtype, int nrows, long rows, int C);
+int bn_fold_relu(int dtype, const BnSums& b, float eps, float momentum, const void* y, long rows, int C, void* z, hipStream_t s);
+int bn_fold_tail(int dtype, const BnSums& b, const BnSums* bd, float eps, float momentum, const void* y, const void* shortcut,
+                 long rows, int C, void* out, uint8_t* out_bits, hipStream_t s);
+int bn_fold_bwd(int dtype, const BnSums& b, const void* dz, const void* y, long rows, int C, void* dy, hipStream_t s);
+int bn_fold_bwd2(int dtype, const BnSums& b1, const BnSums& b2, const void* dz, const void* y1, void* dy1, const void* y2, void* dy2,
+                 long rows, int C, hipStream_t s);
 // out = a + b
 int add_tensors(int dtype, const void* a, const void* b, void* out, size_t n, hipStream_t s);
 // dtype conversion / repacking of weights
