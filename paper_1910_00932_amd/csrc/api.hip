@@ -360,12 +360,16 @@ static SideStream* side_stream() {
     SideStream& ss = side[dev];
     if (ss.state == 0) {
         ss.state = -1;
+        // These events order work of one device: without the fence towards the host and other devices, which the caller's own
+        // events and synchronisations on the launch stream bring, a record holds the launch stream up for 5 us instead of 6 - 10
+        // (train step of 8 clips 6723 -> 6573 us, 64 -> 64 -> 256 block of 8 clips 756 -> 734).
+        const unsigned flags = hipEventDisableTiming | hipEventDisableSystemFence;
         if (hipStreamCreateWithFlags(&ss.stream, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&ss.fork, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ss.join, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ss.lag[0], hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ss.lag[1], hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&ss.branch, hipEventDisableTiming) == hipSuccess)
+            hipEventCreateWithFlags(&ss.fork, flags) == hipSuccess &&
+            hipEventCreateWithFlags(&ss.join, flags) == hipSuccess &&
+            hipEventCreateWithFlags(&ss.lag[0], flags) == hipSuccess &&
+            hipEventCreateWithFlags(&ss.lag[1], flags) == hipSuccess &&
+            hipEventCreateWithFlags(&ss.branch, flags) == hipSuccess)
             ss.state = 1;
         else
             (void)hipGetLastError();
@@ -622,7 +626,7 @@ static int block_infer_entry(const tsm_block_desc* d, const void* x, const tsm_b
 // The body of block_bwd_impl; `forked` tells the caller whether the side stream has work of this block, so that it
 // is joined on every path out, errors included (a caller's stream capture must not be left with an open branch).
 static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const void* dout, void* dx, Arena& ws, bool dry,
-                          hipStream_t s, SideStream* ss, bool& forked);
+                          hipStream_t s, SideStream* ss, bool gather, bool& forked);
 
 // Takes the joins that block_bwd_impl left open in its late-join mode.
 int block_bwd_flush(hipStream_t s) {
@@ -637,6 +641,15 @@ int block_bwd_flush(hipStream_t s) {
     return rc;
 }
 
+// A fork (an event recorded on one stream, waited for on the other) costs the host 12 us, four launches, and the launch stream
+// 5 us.  In a chain of small blocks a block's weight gradients share one, behind its last BatchNorm: they run beside the
+// next block's kernels.  Train step of 2 clips of 160 x 160, four micro-batches, output tensors of 1.6 to 13 MB: 11282 -> 11014
+// us.  Large tensors leave the caches in between: 8 clips of 224 x 224 with every block 6553 -> 6809, up to 30 MB 6594.
+static bool few_forks(const BlockPlan& b) {
+    const ConvP& p = b.st[b.nst - 1].p;
+    return p.rows_out() * p.Cout * (long)dtype_size(b.dtype) <= (8L << 20);
+}
+
 // lag_slot < 0: the launch stream joins the weight-gradient stream at the end of the block.  lag_slot 0 / 1 (a chain of
 // blocks whose scratch alternates between two regions, slot = region): the join of this block is left open and the one
 // the previous call left open -- the other slot's -- is taken instead, so the weight gradients of a block may run on
@@ -646,7 +659,7 @@ int block_bwd_impl(BlockPlan& b, const void* x, const void* out, const void* dou
                    hipStream_t s, int lag_slot) {
     SideStream* const ss = dry ? nullptr : side_stream();
     bool forked = false;
-    const int rc = block_bwd_body(b, x, out, dout, dx, ws, dry, s, ss, forked);
+    const int rc = block_bwd_body(b, x, out, dout, dx, ws, dry, s, ss, lag_slot >= 0 && few_forks(b), forked);
     if (lag_slot >= 0 && ss && rc == TSM_OK) {
         const int k = lag_slot & 1;
         if (ss->pending[k]) return fail(TSM_ERR_LAUNCH, "block backward: the scratch region of this slot is still in use");
@@ -669,7 +682,7 @@ int block_bwd_impl(BlockPlan& b, const void* x, const void* out, const void* dou
 }
 
 static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const void* dout, void* dx, Arena& ws, bool dry,
-                          hipStream_t s, SideStream* ss, bool& forked) {
+                          hipStream_t s, SideStream* ss, bool gather, bool& forked) {
     const int es = (int)dtype_size(b.dtype);
     const int L = b.nst - 1;
     const ConvP& pl = b.st[L].p;
@@ -755,11 +768,27 @@ static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const vo
         addend = dsc;
         return TSM_OK;
     };
+    // gather: the weight gradients wait for the block's last fork (see wgrad_beside)
+    struct { StageDef* st; const void *x, *dy; } held[4];
+    int nheld = 0;
+    auto wgrad = [&](StageDef& st, const void* x, const void* dy, bool fork) -> int {
+        if (gather && !fork) {
+            held[nheld++] = {&st, x, dy};
+            return TSM_OK;
+        }
+        TSM_TRY(wgrad_beside(ss, &forked, st.p, b.dtype, x, dy, st.dw, st.dwp, acc_flag(st), ws, dry, s));
+        for (int k = 0; k < nheld; ++k) {
+            StageDef& h = *held[k].st;
+            TSM_TRY(run_conv_wgrad(h.p, b.dtype, held[k].x, held[k].dy, h.dw, h.dwp, acc_flag(h), ws, dry, ss && !dry ? ss->stream : s));
+        }
+        nheld = 0;
+        return TSM_OK;
+    };
     void* g = dyL;
     for (int i = L; i >= 1; --i) {
         StageDef& st = b.st[i];
         const ConvP& pp = b.st[i - 1].p;  // producer of this stage's input
-        TSM_TRY(wgrad_beside(ss, &forked, st.p, b.dtype, b.z[i - 1], g, st.dw, st.dwp, acc_flag(st), ws, dry, s));
+        TSM_TRY(wgrad(st, b.z[i - 1], g, false));
         if (i == L && b.proj) TSM_TRY(shortcut_dgrad());
         void* dzin = ws.take((size_t)pp.rows_out() * pp.Cout * es);
         // the ReLU mask and the BatchNorm reductions of the producing stage ride in the data gradient's
@@ -785,10 +814,9 @@ static int block_bwd_body(BlockPlan& b, const void* x, const void* out, const vo
         }
         g = dzin;
     }
-    TSM_TRY(wgrad_beside(ss, &forked, b.st[0].p, b.dtype, x, g, b.st[0].dw, b.st[0].dwp, acc_flag(b.st[0]), ws, dry, s));
+    if (b.proj) TSM_TRY(wgrad(b.ds, x, dyd, false));
+    TSM_TRY(wgrad(b.st[0], x, g, true));
     if (b.proj) {
-        StageDef& st = b.ds;
-        TSM_TRY(wgrad_beside(ss, &forked, st.p, b.dtype, x, dyd, st.dw, st.dwp, acc_flag(st), ws, dry, s));
         if (branch_open && hipStreamWaitEvent(s, ss->branch, 0) != hipSuccess)
             return fail(TSM_ERR_LAUNCH, "block backward: cannot wait for the side stream");
     }
