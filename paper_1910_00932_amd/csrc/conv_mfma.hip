@@ -13,8 +13,8 @@
 //   wgrad      D[Cout x Cin] (per tap) = sum over pixels of dy^T * gathered x
 //
 // v_mfma_f32_32x32x16_bf16, operands staged through LDS, fp32 accumulation.  Kernels:
-//   igemm_ring_kernel  fwd/dgrad, source channels % 64 == 0: 256 x {128,64} tile, eight wavefronts,
-//                      buffer-load gathers, loads and LDS stores spread over the MFMA groups
+//   igemm_ring_kernel  fwd/dgrad, source channels % 64 == 0: {256,128} x {256,128,64} tile, eight wavefronts,
+//                      buffer-load gathers, straight into LDS or through registers, spread over the MFMA groups
 //   conv3x3_c64_kernel fwd/dgrad, 3x3 stride 1, 64 -> 64 channels, many tiles: weights and the tile's input patch
 //                      resident in LDS, no barrier inside a tile's main loop
 //   stem_s2d_kernel    fwd of the stem in space-to-depth form, many tiles: the same scheme for its 4-row window
@@ -464,16 +464,53 @@ __global__ void __launch_bounds__(256, MINB) igemm_kernel(IgemmArgs a) {
 //    instead of 64-bit pointer arithmetic.  Lanes that fall on padding pass an offset beyond the buffer and
 //    receive zeros from the bounds check.  The buffer starts `bias` bytes before the tensor so that the offset
 //    of a row's tap origin, which may lie in the padding in front of the first frame, is never negative.
-//  * LDS holds two stages.  A stage is the A rows [BM][64] followed by the B rows [BN][64], 128 bytes per row
+//  * LDS holds two to four stages.  A stage is the A rows [BM][64] followed by the B rows [BN][64], 128 bytes per row
 //    without padding; position p (16 bytes) of row r holds the row's K vector p ^ ((r >> 1) & 7), which spreads
-//    the 16-byte fragment reads of 16 consecutive rows over 16 different bank groups.  While step g is
-//    multiplied out of one stage, step g+1 moves from registers into the other and step g+2 is loaded into the
-//    registers, a few loads and stores after every group of MFMAs.  The stream of K steps runs across tile
-//    boundaries, so a tile's first two steps are on the chip before the previous tile's epilogue starts.
+//    the 16-byte fragment reads of 16 consecutive rows over 16 different bank groups; thread t's piece of a pass lies at
+//    16 * t, so a load can leave it there without a register in between.  The stream of K steps runs across tile
+//    boundaries, so a tile's first steps are on the chip before the previous tile's epilogue starts.
+//  * 128-column tiles and small 64-column results load straight into LDS (three or four stages: two or three steps in flight
+//    behind the one at work): what bounds their steps is the LDS, 128 KB of fragment reads and 48 KB of operands per 64 K of a
+//    256 x 128 tile at 128 bytes a clock against 1024 clocks of MFMAs, and the loads' way through registers put its
+//    instructions and waits on top.  Us with registers -> without: 12544 x 2304 -> 256 35.0 -> 31.2
+//    (475 TFLOP/s), 25088 x 2304 -> 256 47.8 -> 42.8, 50176 x 1152 -> 128 30.0 -> 27.9, 25088 x 4608 -> 512 (128 x 128) 58.7 -> 51.7,
+//    200704 x 576 -> 64 45.0 -> 41.6; data gradients 100352 x 2304 -> 256 166 -> 154, stride 2 100352 x 4608 -> 512 169 -> 147.
+//    256-column tiles (two 64 KB stages: one step in flight) and streamed 64-column results keep a step in registers: 100352
+//    x 1024 -> 256 66 with, 73 without; 1605632 x 256 -> 64 191, 203.  Four wavefronts of 128 x 64 instead of eight of 64 x 64,
+//    a quarter less to read from LDS, wait on themselves: 25088 x 2304 -> 256 50.0.
 static constexpr uint32_t OOB_OFFSET = 0x80000000u;   // buffers are smaller than 2 GiB
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+}
+
+constexpr bool ring_direct(int BM, int BN, bool stream) { return BN == 128 || BM == 128 || (BN == 64 && !stream); }
+constexpr int ring_stages(int BM, int BN, bool stream) { return !ring_direct(BM, BN, stream) ? 2 : BM == 128 && BN == 64 ? 4 : 3; }
+constexpr bool ring_alias(int BM, int BN) { return BN == 256 || (BM == 256 && BN == 128); }
+constexpr size_t ring_smem(int BM, int BN, int WM, int WN, bool stream) {
+    const size_t stage = (size_t)(BM + BN) * BK * 2, cst = (size_t)WM * 32 * (BN + 8) * 2;
+    const size_t part = (size_t)2 * WM * WN * BN * 4;
+    const bool alias = ring_alias(BM, BN);
+    return ring_stages(BM, BN, stream) * stage + (alias ? 0 : cst) + (alias && cst + part <= stage ? 0 : part) + (size_t)2 * BM * sizeof(RowInfo) + (size_t)2 * BM * sizeof(int);
+}
+
+// Waits until at most VM of this wavefront's memory operations (loads into LDS among them) and none of its LDS accesses are
+// outstanding; block_barrier: a barrier that waits for nothing else.
+template <int VM> __device__ __forceinline__ void wait_vm_lds() {
+    static_assert(VM >= 0 && VM <= 63, "six bits");
+    __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (0 << 8) | ((VM >> 4) << 14));
+}
+// 16 bytes per lane from memory to LDS, lane i's to at + 16 * i (`at`: the same for all lanes); lanes beyond the buffer's
+// end leave zeros.
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, unsigned char* at, uint32_t voff, int soff) {
+#if defined(__HIP_DEVICE_COMPILE__)   // (the host pass of the compiler knows no such address space)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)at, 16, (int)voff, soff, 0, 0);
+#endif
+}
+__device__ __forceinline__ void block_barrier() {
+    asm volatile("" ::: "memory");   // (a fence would also wait for every load into LDS in flight)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // CADD: the addend of a data gradient comes in the compact form described at IgemmArgs::add_stride (a variant of its
@@ -484,39 +521,44 @@ template <int BM, int BN, int WM, int WN, bool DGRAD, bool STREAM, bool CADD = f
 __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
     static_assert(DGRAD || !(CADD || MBITS), "only data gradients add a tensor or apply a mask");
     constexpr int NT = WM * WN * 64;                // threads
-    constexpr int NS = 2;                           // LDS stages
+    constexpr int NS = ring_stages(BM, BN, STREAM); // LDS stages
+    constexpr bool DIRECT = ring_direct(BM, BN, STREAM);   // loads go straight to LDS
+    constexpr int AHEAD = DIRECT ? NS - 1 : 2;      // steps between a step's loads and its product
     constexpr int MI = BM / (WM * 32), NJ = BN / (WN * 32);   // 32x32 MFMA tiles per wavefront
     constexpr int HM = BM / MI;                     // rows per epilogue pass; wavefront rows: i*HM + wm*32
     constexpr int TN = BN / WN;
-    constexpr int KV = BK / 8;                      // 16-byte vectors per tile row
+    constexpr int KV = BK / 8;                     // 16-byte vectors per tile row
     constexpr int RPP = NT / KV;                    // tile rows loaded per pass
     constexpr int PA = BM / RPP, PB = BN / RPP;
-    constexpr int ROWB = BK * 2;                    // bytes per LDS row
+    constexpr int ROWB = BK * 2;                   // bytes per LDS row
     constexpr int STAGE = (BM + BN) * ROWB;         // bytes per ring stage
     constexpr int LDC = BN + 8;                     // staging pitch (elements)
     constexpr int NSLOT = WM * WN;                  // one statistics slot per wavefront
-    static_assert(BK == 64 && KV == 8, "rows of eight 16-byte vectors");
+    static_assert(KV == 8, "rows of eight 16-byte vectors");
     static_assert(BM % RPP == 0 && BN % RPP == 0 && HM == WM * 32, "tile / thread mismatch");
     static_assert((HM * LDC * 2) % 16 == 0, "alignment of the regions behind the staging tile");
     static_assert(sizeof(RowInfo) == 16, "one 16-byte LDS read per row");
 
-    // 256-column tiles (forward, statistics epilogue only): the two stages take 128 KB, so the staging tile of the
-    // epilogue lies in the stage that the tile's last K step was multiplied from.  Behind the barrier of that step no
-    // wavefront reads it any more, and the next tile's steps are not written into it before the barrier at the top of
-    // the next tile, which every wavefront reaches after its last read of the staging tile.
-    constexpr bool ALIAS = BN == 256;
-    static_assert(!ALIAS || (!DGRAD && HM * LDC * 2 <= STAGE), "the staging tile must fit a stage");
+    // Where the stages leave no room for it (ALIAS), the staging tile of the epilogue lies in the stage that the tile's last
+    // K step was multiplied from.  Behind the barrier of that step no wavefront reads it any more, the loads in flight go to
+    // the other stages, and the next one to be loaded into it is issued behind the barrier at the top of the next tile,
+    // which every wavefront reaches after its last read of the staging tile.
+    constexpr bool ALIAS = ring_alias(BM, BN);
+    constexpr bool PART_ALIAS = ALIAS && HM * LDC * 2 + 2 * NSLOT * BN * 4 <= STAGE;   // the statistics slots too
+    static_assert(!ALIAS || HM * LDC * 2 <= STAGE, "the staging tile must fit a stage");
+    static_assert(BN != 256 || !DGRAD, "forward only");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16_t* Cst = (bf16_t*)(smem + NS * STAGE);      // [HM][LDC] staging tile of the epilogue (ALIAS: set per tile)
     float* s_part = ALIAS ? (float*)(smem + NS * STAGE) : (float*)(Cst + HM * LDC);   // [2 stats][WM*2 slots][BN] statistics slots
-    RowInfo* s_row = (RowInfo*)(s_part + 2 * NSLOT * BN);   // [2][BM]: rows of the current and of the next tile
+    RowInfo* s_row = (RowInfo*)(s_part + (PART_ALIAS ? 0 : 2 * NSLOT * BN));   // [2][BM]: rows of the current and of the next tile
     int* s_arow = (int*)(s_row + 2 * BM);                   // [2][BM]: row of a compact addend (-1: none), dgrad only
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int lrow = tid / KV;                                   // row within a load pass
-    const int kvec = (tid % KV) ^ ((lrow >> 1) & 7);             // K vector this thread fetches (see layout above)
+    const int kvec = (tid % KV) ^ ((lrow >> 1) & 7);            // K vector this thread fetches (see layout above)
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const bool do_stats = (!DGRAD) && a.stats != nullptr;
     const bool fuse_mask = DGRAD && (MBITS ? a.act_bits != nullptr : a.act != nullptr);   // ReLU mask in the epilogue ...
     const bool fuse_bn = fuse_mask && a.ybn != nullptr;      // ... and the BatchNorm-backward sums of the masked values
@@ -545,7 +587,7 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
     // Producer view of one tile.  Everything but the per-row offsets and masks is the same for all threads.
     struct Ctx {
         int n0, nth, ntw, a0h, a0w, ntaps;
-        int nk;               // K steps of the tile, at least two (steps beyond the data multiply zeros)
+        int nk;               // K steps of the tile, at least AHEAD (steps beyond the data multiply zeros)
         uint32_t aoff[PA];    // byte offset of (row's tap origin, this thread's K vector) in the biased buffer
         uint32_t amask[PA];
         uint32_t boff[PB];    // byte offset of (output channel row, this thread's K vector) in the weights
@@ -621,7 +663,7 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
         c.nth = a.nth[cls]; c.ntw = a.ntw[cls]; c.a0h = a.a0h[cls]; c.a0w = a.a0w[cls];
         c.ntaps = a.KT * c.nth * c.ntw;
         c.nk = c.ntaps * (a.Cs / BK);
-        if (c.nk < 2) c.nk = 2;
+        if (c.nk < AHEAD) c.nk = AHEAD;
 #pragma unroll
         for (int i = 0; i < PA; ++i) {
             const RowInfo ri = s_row[rb * BM + i * RPP + lrow];
@@ -680,17 +722,23 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
         }
         return p;
     };
-    // One 16-byte piece of a K step per call: pieces 0..PA-1 are A rows, the rest B rows.  A piece is loaded
-    // into its register during one step and written to the ring during the next one.
-    u32x4 greg[NP];
-    auto load_piece = [&](const Plan& p, int i) {
-        greg[i] = i < PA ? __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, (int)p.v[i], p.soff_a, 0)
-                         : __builtin_amdgcn_raw_buffer_load_b128(rsrc_b, (int)p.v[i], p.soff_b, 0);
+    // One 16-byte piece per thread of a K step per call, straight into its stage or into its register (it is written to LDS
+    // during the next step then): pieces 0..PA-1 are A rows, the rest B
+    // rows; thread -> row lrow of the piece's pass, position tid % KV.  A wavefront's 64 pieces are contiguous in LDS.
+    u32x4 greg[DIRECT ? 1 : NP];
+    auto load_piece = [&](const Plan& p, int stage, int i) {
+        const int row0 = i < PA ? i * RPP : BM + (i - PA) * RPP;
+        unsigned char* const at = smem + stage * STAGE + row0 * ROWB + wave_u * 1024;
+        const __amdgpu_buffer_rsrc_t r = i < PA ? rsrc_a : rsrc_b;
+        const int soff = i < PA ? p.soff_a : p.soff_b;
+        if constexpr (DIRECT) load_lds16(r, at, p.v[i], soff);
+        else greg[i] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)p.v[i], soff, 0);
     };
-    auto store_piece = [&](int stage, int i) {   // thread -> row lrow of the piece's pass, position tid % 8
+    auto store_piece = [&](int stage, int i) {
         const int row0 = i < PA ? i * RPP : BM + (i - PA) * RPP;
         *(u32x4*)(smem + stage * STAGE + row0 * ROWB + tid * 16) = greg[i];
     };
+    auto stage_of = [&](int k) { return NS == 2 ? k & 1 : k >= NS ? k - NS : k; };   // k < 2 * NS
 
     // fragment addresses inside a stage: row (lane % 32) of the wavefront's first row block, K vector
     // 2*ks + lane/32 at its swizzled position
@@ -707,7 +755,11 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
 
     int tile = next_tile(blockIdx.x);
     int rb = 0;
-    int cstage = 0;                  // stage being multiplied; the other one is being filled
+    int cstage = 0;                  // stage being multiplied; the others are being filled
+    // What may still be outstanding, counted in order, behind the tile's first AHEAD steps: 0 nothing (the block's first tile),
+    // 1 they have landed, 2 the previous tile's stores, one per thread and 16 bytes.
+    int behind = 0;
+    constexpr int STORES = BM * (BN / 8) / NT;
     Ctx pc;                          // producer position
     int p_left = 0;                  // K steps the producer still has to fetch for its tile
     bool p_on_next = false;          // the producer has moved on to the tile after the current one
@@ -715,22 +767,25 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
     __syncthreads();                 // also orders the zeroing of the statistics row
     if (tile >= 0) {
         pc = make_ctx(tile, 0);
-        p_left = pc.nk - 2;
-        Plan p0 = plan(pc, true);
+        p_left = pc.nk - AHEAD;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) load_piece(p0, i);
+        for (int k = 0; k < AHEAD; ++k) {
+            const Plan p0 = plan(pc, true);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) store_piece(0, i);
-        Plan p1 = plan(pc, true);
+            for (int i = 0; i < NP; ++i) load_piece(p0, k, i);
+            if (!DIRECT && k == 0) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i) load_piece(p1, i);
+                for (int i = 0; i < NP; ++i) store_piece(0, i);
+            }
+        }
+        wait_vm_lds<DIRECT ? (AHEAD - 1) * NP : 63>();
     }
     int cur_nk = tile >= 0 ? pc.nk : 0, cur_n0 = tile >= 0 ? pc.n0 : 0;
     // Fragment registers live across K steps and tiles: the first fragments of a step are read from its stage
     // while the last MFMA group of the step before is still in the pipeline (see the main loop).
     constexpr int KS = BK / 16;
     bf16x8 af[2][MI], bfr[2][NJ];
-    __syncthreads();                 // stage 0 holds the first step
+    block_barrier();                 // stage 0 holds the first step
 #pragma unroll
     for (int i = 0; i < MI; ++i) af[0][i] = *(const bf16x8*)(smem + a_rd[0] + i * HM * ROWB);
 #pragma unroll
@@ -756,11 +811,11 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-        // Main loop.  On entry to step g (stream position of the block, across tiles) stage g % 2 holds step g
-        // and the registers hold step g+1, loaded during step g-1.  While step g is multiplied, the registers
-        // are written to the other stage piece by piece and each freed register is reloaded with its piece of
-        // step g+2.  The pieces are spread over the MFMA groups: issued in one burst, the loads of all eight
-        // wavefronts would fill the address unit's queue and stall the wavefronts in front of their MFMAs.
+        // Main loop.  On entry to step g (stream position of the block, across tiles) stage g % NS holds step g and the
+        // loads of the AHEAD - 1 steps behind it are in flight.  While step g is multiplied, those of step g + AHEAD go to
+        // the stage that step g - 1 has left (or the registers of step g + 1 to the other stage and step g + 2 into them).
+        // The pieces are spread over the MFMA groups: issued in one burst, the loads
+        // of all eight wavefronts would fill the address unit's queue and stall the wavefronts in front of their MFMAs.
         int next_nk = 0, next_n0 = 0;
         // Plans the step the producer fetches next; the producer crosses into the next tile when it has
         // fetched all steps of its tile.
@@ -781,12 +836,13 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
         __syncthreads();       // the next tile's rows are decoded
         Plan pl = plan_next();
         for (int kc = 0; kc < cur_nk; ++kc) {
-            // One barrier per step, in front of the last MFMA group: by then every wavefront has written its pieces
-            // of the next step into the other stage and has read its last fragments of this stage, so behind the
-            // barrier the next step's first fragments are read (their latency overlaps the last MFMA group) and
-            // the next step may overwrite this stage.
+            // One barrier per step, in front of the last MFMA group.  Every wavefront first waits for its own pieces of the
+            // next step (the loads behind them, (AHEAD - 1) * NP, may stay in flight) and for its last fragments of this
+            // stage, so behind the barrier the next step's first fragments are read (their latency overlaps the last MFMA
+            // group) and the step after next may overwrite this stage.
+            const int nstage = stage_of(cstage + 1), fstage = stage_of(cstage + NS - 1);
             const unsigned char* st = smem + cstage * STAGE;
-            const unsigned char* stn = smem + (cstage ^ 1) * STAGE;
+            const unsigned char* stn = smem + nstage * STAGE;
             constexpr int PPK = (NP + KS - 2) / (KS - 1);     // pieces handled after each of the first KS-1 groups
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -797,12 +853,20 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) bfr[nb][j] = *(const bf16x8*)(st + b_rd[ks + 1] + j * 32 * ROWB);
                 } else {
-                    __syncthreads();
+                    if constexpr (DIRECT) {
+                        if (behind == 0 || kc >= AHEAD - 1) wait_vm_lds<(AHEAD - 1) * NP>();
+                        else if (behind == 1) wait_vm_lds<63>();
+                        else wait_vm_lds<(AHEAD - 1) * NP + STORES>();
+                        block_barrier();
+                    } else {
+                        __syncthreads();
+                    }
 #pragma unroll
                     for (int i = 0; i < MI; ++i) af[nb][i] = *(const bf16x8*)(stn + a_rd[0] + i * HM * ROWB);
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) bfr[nb][j] = *(const bf16x8*)(stn + b_rd[0] + j * 32 * ROWB);
                 }
+                if constexpr (DIRECT) __builtin_amdgcn_sched_barrier(0);   // the reads first: their latency overlaps these MFMAs
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -812,22 +876,25 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cb][j], af[cb][i], acc[i][j], 0, 0, 0);
 #pragma unroll
                 for (int q = ks * PPK; q < (ks + 1) * PPK && q < NP; ++q) {
-                    store_piece(cstage ^ 1, q);
-                    load_piece(pl, q);
+                    if (!DIRECT) store_piece(nstage, q);
+                    load_piece(pl, fstage, q);
                 }
                 __builtin_amdgcn_sched_barrier(0);   // keep the pieces where they are
             }
             // the address arithmetic of the next step runs while the last MFMAs of this one are in the pipeline
             if (kc + 1 < cur_nk) pl = plan_next();
-            cstage ^= 1;
+            cstage = nstage;
         }
+        const int last = stage_of(cstage + NS - 1);   // the stage of the tile's last step
 
-        // ---- epilogue, one pass per row block through the staging tile; the registers and the other LDS
-        // stage already hold the first two K steps of the next tile.
+        // ---- epilogue, one pass per row block through the staging tile; the first AHEAD K steps of the next tile are on
+        // their way to the other stages.
         // fused BatchNorm backward: this thread stores the same eight columns of every row it handles
         // (forward with an affine epilogue keeps scale / shift of the same eight columns in mu / rs)
-        if (ALIAS) Cst = (bf16_t*)(smem + (cstage ^ 1) * STAGE);
-        const bool affine = !DGRAD && !ALIAS && a.ep_scale != nullptr;
+        behind = !DGRAD && (tile_mt(tile) + 1) * BM <= a.F * hw_d && cur_n0 + BN <= a.Cd ? 2 : 1;
+        if (ALIAS) Cst = (bf16_t*)(smem + last * STAGE);
+        if (PART_ALIAS) s_part = (float*)(Cst + HM * LDC);
+        const bool affine = !DGRAD && BN != 256 && a.ep_scale != nullptr;
         float mu[FV], rs[FV];
 #pragma unroll
         for (int q = 0; q < FV; ++q) mu[q] = rs[q] = 0.f;
@@ -900,6 +967,9 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
                     *(uint2*)(dstp + 8 * q) = w;
                 }
             }
+            // A later wait for the next tile's first steps, counted in order, has to know how many stores stand behind them:
+            // where that depends on the rows they land before the first store.
+            if (DIRECT && h == 0 && behind == 1) wait_vm_lds<0>();
             __syncthreads();
             if (!DGRAD) {
 #pragma unroll
@@ -2441,11 +2511,8 @@ template <int BM, int BN, int WM, int WN, bool DGRAD, bool STREAM, bool CADD = f
 static int launch_igemm_ring_s(IgemmArgs& a, const char* name, hipStream_t s) {
     const int mtiles = setup_classes(a, DGRAD, BM);
     a.ntiles = (a.Cd + BN - 1) / BN;
-    // two operand stages, staging tile of one epilogue pass, statistics slots, two row buffers
-    const size_t smem = (size_t)2 * (BM + BN) * BK * sizeof(bf16_t) + (BN == 256 ? 0 : (size_t)(WM * 32) * (BN + 8) * sizeof(bf16_t)) +
-                        (size_t)2 * WM * WN * BN * sizeof(float) + (size_t)2 * BM * sizeof(RowInfo) + (size_t)2 * BM * sizeof(int);
-    static_assert((size_t)2 * (BM + BN) * BK * sizeof(bf16_t) + (BN == 256 ? 0 : (size_t)(WM * 32) * (BN + 8) * sizeof(bf16_t)) +
-                  (size_t)2 * WM * WN * BN * sizeof(float) + (size_t)2 * BM * sizeof(RowInfo) + (size_t)2 * BM * sizeof(int) <= 160 * 1024, "LDS budget");
+    constexpr size_t smem = ring_smem(BM, BN, WM, WN, STREAM);   // operand stages, staging tile of one epilogue pass, statistics slots, two row buffers
+    static_assert(smem <= 160 * 1024, "LDS budget");
     auto kern = igemm_ring_kernel<BM, BN, WM, WN, DGRAD, STREAM, CADD, MBITS>;
     static bool configured = false;
     if (!configured) {
