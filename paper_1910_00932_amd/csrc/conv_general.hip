@@ -3,12 +3,13 @@
 //
 // Both storage types run the same code: a K step is 128 bytes of every tile row (32 floats or 64 bf16), staged through
 // LDS, and only the instruction that multiplies a 16-byte fragment pair differs -- v_mfma_f32_32x32x16_bf16, or four
-// v_mfma_f32_32x32x2_f32 (fp32 products and sums: no precision is given up against a scalar fmaf loop).
+// v_mfma_f32_32x32x2_f32 (fp32 products and sums: no precision is given up against a scalar fmaf loop).  The fp32 weight gradient
+// forms its products of bf16 parts (split_f32.h).
 //
-// What bounds them: in fp32 the matrix cores' fp32 rate (157 TFLOP/s; 64 cycles per instruction and 4 KB of LDS fragments per 4096
-// of those cycles: neither LDS nor memory comes close), of which a barrier per step that stops all four wavefronts at
-// once leaves 57 TFLOP/s (6272 x 2304 -> 256; conv_ksplit.hip, without that barrier, 92).  Tiles are chosen for how well they
-// fill the last round.
+// What bounds them: forward and data gradient in fp32 the matrix cores' fp32 rate (140 TFLOP/s measured; 64 cycles per instruction
+// and 4 KB of LDS fragments per 4096 of those cycles: neither LDS nor memory comes close), of which a barrier per step that stops
+// all four wavefronts at once leaves 57 TFLOP/s (6272 x 2304 -> 256; conv_ksplit.hip, without that barrier, 92 with the same
+// instructions).  Tiles are chosen for how well they fill the last round.
 //
 // Against one thread per output element (1.2 TFLOP/s whatever the layer; those kernels are kept in direct.hip for strides
 // beyond 2 and filters beyond 8): fp32 train step at 4 clips of 8 x 224^2 655 -> 16.1 ms; bf16 72 -> 200 channels 3x3 at
@@ -20,8 +21,10 @@
 // put together from one masked load per group; where rows are not 16-byte aligned (channel counts that are no multiple
 // of the vector) it is loaded element by element.
 #include <algorithm>
+#include <type_traits>
 #include "internal.h"
 #include "taps_inside.h"
+#include "split_f32.h"
 
 namespace tsm {
 
@@ -127,28 +130,30 @@ __device__ __forceinline__ void mma(const u32x4* a, const u32x4* b, f32x16 (&acc
 }
 
 // The accumulators of a lane that hold NaN, and a new value for one of them.
-template <int MI, int NJ>
-__device__ __forceinline__ uint64_t nan_mask(const f32x16 (&acc)[MI][NJ]) {
-    static_assert(MI * NJ * 16 <= 64, "one bit each");
+template <int MI, int NJ, typename Acc>
+__device__ __forceinline__ uint64_t nan_mask(const Acc (&acc)[MI][NJ]) {
+    constexpr int RN = sizeof(Acc) / 4;
+    static_assert(MI * NJ * RN <= 64, "one bit each");
     uint64_t m = 0;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (acc[i][j][r] != acc[i][j][r]) m |= 1ull << ((i * NJ + j) * 16 + r);
+            for (int r = 0; r < RN; ++r)
+                if (acc[i][j][r] != acc[i][j][r]) m |= 1ull << ((i * NJ + j) * RN + r);
     return m;
 }
-template <int MI, int NJ>
-__device__ __forceinline__ void set_at(f32x16 (&acc)[MI][NJ], int at, float v) {
+template <int MI, int NJ, typename Acc>
+__device__ __forceinline__ void set_at(Acc (&acc)[MI][NJ], int at, float v) {
+    constexpr int RN = sizeof(Acc) / 4;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[i][j][r] = at == (i * NJ + j) * 16 + r ? v : acc[i][j][r];
+            for (int r = 0; r < RN; ++r)
+                acc[i][j][r] = at == (i * NJ + j) * RN + r ? v : acc[i][j][r];
 }
 
 struct GenRow {
@@ -381,16 +386,22 @@ static constexpr int GPX = 32;   // pixels per step
 
 // (Buffer loads and 32-bit divisions in the decode instead of conditional loads and 64-bit ones: 26912 pixels 72 -> 200 3x3
 // bf16 49.3 -> 46.2 us, 115200 pixels 160 -> 128 129.3 -> 112.1, 51200 pixels 264 -> 264 242.8 -> 206.1.)
-// Operand rows go to LDS as loaded, [pixel][channel].  fp32: a lane reads its channel of pixel 2k + lane/32 (32
-// consecutive words per half-wavefront).  bf16: the transposing read, rows padded by 64 bytes so that the four pixels
-// x two channel blocks that 32 lanes read together fall into different banks.
+// Operand rows go to LDS as loaded, [pixel][channel], padded by 64 bytes so that the four pixels that a wavefront reads together
+// fall into different banks.  fp32: a lane reads its channel of eight pixels and cuts them into three parts; the vector
+// instructions for that take as long as the matrix instructions they feed (us with fp32 instructions and now: 6272 pixels 256 ->
+// 256 3x3 92 and 70, 1568 pixels 512 -> 512 3x3 93 and 67, 1568 pixels 2048 -> 512 51 and 43; 64 -> 64 3x3 level).  bf16: the
+// transposing read.
 template <typename T, int BCO, int BCI, int WM, int WN, bool RAG>
 __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
     static_assert(WM * WN == 4, "four wavefronts");
     constexpr int TM = BCO / WM, TN = BCI / WN;
-    constexpr int MI = TM / 32, NJ = TN / 32;
+    constexpr bool SPLIT = sizeof(T) == 4;             // fp32 on the bf16 matrix cores (see split_f32.h)
+    constexpr int TB = SPLIT ? 16 : 32, RN = SPLIT ? 4 : 16;   // result blocks of TB x TB, RN values per lane
+    constexpr int MI = TM / TB, NJ = TN / TB;
+    typedef std::conditional_t<SPLIT, f32x4, f32x16> Acc;
+    auto row_of = [](int lane, int r) { return SPLIT ? 4 * (lane >> 4) + r : 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
     constexpr int VE = 16 / (int)sizeof(T);
-    constexpr int PADB = sizeof(T) == 2 ? 64 : 0;
+    constexpr int PADB = 64;
     constexpr int ROWA = BCO * (int)sizeof(T) + PADB, ROWB = BCI * (int)sizeof(T) + PADB;
     constexpr int STAGE = GPX * (ROWA + ROWB);
     constexpr int AV = BCO / VE, BV = BCI / VE;
@@ -476,53 +487,45 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
                 br[i] = load_shifted<T, RAG>((const T*)a.x + r.off + toff, col_ok && (r.mask & need) == need, r.mask, ch, a.Cin, a.fold, d0, frame);
         }
     };
-    auto store = [&](int buf) {
+    auto store = [&](int buf, int st) {
         unsigned char* S = smem + buf * STAGE;
 #pragma unroll
-        for (int i = 0; i < PA; ++i) *(u32x4*)(S + (arow + i * RA) * ROWA + avec * 16) = ar[i];
+        for (int i = 0; i < PA; ++i) {
+            if constexpr (SPLIT) ar[i] ^= (st & 1) ? 0x80000000u : 0u;   // (every other step's sums are formed of -dy)
+            *(u32x4*)(S + (arow + i * RA) * ROWA + avec * 16) = ar[i];
+        }
 #pragma unroll
         for (int i = 0; i < PB; ++i) *(u32x4*)(S + GPX * ROWA + (brow + i * RB) * ROWB + bvec * 16) = br[i];
     };
 
-    f32x16 acc[MI][NJ];
+    // fp32: every step's 32 pixels are a sum of their own, added to the others in fp32 (523 pixels at 1568 x 512 -> 512 3x3: one
+    // chain over them is off by 2.6e-7 against 64 bits, two levels of sums by 1.1e-7).
+    Acc acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < RN; ++r) acc[i][j][r] = 0.f;
 
-    // fp32: every step's 32 pixels are a sum of their own.  Against 64 bits one chain over a chunk (523 pixels at 1568 x 512 -> 512
-    // 3x3) is off by 2.6e-7, two levels of sums by 1.1e-7 and a sum per frame of 7 x 7, one thread each, by 1.3e-7; the
-    // additions hide behind the matrix instructions (fp32 step at 4 clips 12.75 and 12.73 ms).
-    constexpr bool TWO_SUMS = sizeof(T) == 4;
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 sum[TWO_SUMS ? MI : 1][TWO_SUMS ? NJ : 1];
-    if constexpr (TWO_SUMS) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) sum[i][j] = zero16;
-    }
-
-    auto multiply = [&](int buf) {
+    auto multiply = [&](int buf, float sign) {
         const unsigned char* A = smem + buf * STAGE;
         const unsigned char* B = A + GPX * ROWA;
         if constexpr (sizeof(T) == 4) {
-            const float* pa = (const float*)(A + (lane >> 5) * ROWA) + wm * TM + (lane & 31);
-            const float* pb = (const float*)(B + (lane >> 5) * ROWB) + wn * TN + (lane & 31);
+            // a lane supplies pixels lane/16 + {0, 4, .. 28} of its channel, to both operands
+            auto frag = [&](const unsigned char* base, int row, int chan) {
+                const unsigned char* p = base + (lane >> 4) * row + (chan + (lane & 15)) * 4;
+                float f[8];
 #pragma unroll
-            for (int k = 0; k < GPX; k += 2) {
-                float af[MI], bf[NJ];
+                for (int e = 0; e < 8; ++e) f[e] = *(const float*)(p + 4 * e * row);
+                return split3(f);
+            };
+            static_assert(GPX == 32, "one chain per step");
+            Split3 bf[NJ];
 #pragma unroll
-                for (int i = 0; i < MI; ++i) af[i] = pa[k * (ROWA / 4) + i * 32];
+            for (int j = 0; j < NJ; ++j) bf[j] = frag(B, ROWB, wn * TN + j * 16);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) bf[j] = pb[k * (ROWB / 4) + j * 32];
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
-            }
+            for (int i = 0; i < MI; ++i) mma_split_b<NJ>(frag(A, ROWA, wm * TM + i * 16), bf, sign, acc[i]);
         } else {
             // lane = 32*kg + 16*mblk + 4*e + c supplies channels 4c.. of pixel 8*kg + e and receives four pixels of one channel
             const int c = lane & 3, e = (lane >> 2) & 3, mblk = (lane >> 4) & 1, kg = lane >> 5;
@@ -549,36 +552,21 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
     if (nsteps > 1) decode(1);
     __syncthreads();
     load(0);
-    store(0);
+    store(0, 0);
     __syncthreads();
     for (int st = 0; st < nsteps; ++st) {
         const int buf = st & 1;
         if (st + 2 < nsteps) decode(st + 2);
         if (st + 1 < nsteps) load(st + 1);
-        multiply(buf);
-        if constexpr (TWO_SUMS) {
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    sum[i][j] += acc[i][j];
-                    acc[i][j] = zero16;
-                }
-        }
-        if (st + 1 < nsteps) store(buf ^ 1);
+        multiply(buf, (st & 1) ? -1.f : 1.f);
+        if (st + 1 < nsteps) store(buf ^ 1, st + 1);
         __syncthreads();
-    }
-    if constexpr (TWO_SUMS) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[i][j] += sum[i][j];
     }
     uint64_t nan = a.inside_only ? nan_mask(acc) : 0ull;
     while (__builtin_expect(nan != 0, 0)) {
-        const int at = __ffsll((long long)nan) - 1, i = at / (NJ * 16), j = at / 16 % NJ, r = at % 16;
+        const int at = __ffsll((long long)nan) - 1, i = at / (NJ * RN), j = at / RN % NJ, r = at % RN;
         nan &= nan - 1;
-        const int col = j0 + wn * TN + j * 32 + (lane & 31), co = co0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int col = j0 + wn * TN + j * TB + lane % TB, co = co0 + wm * TM + i * TB + row_of(lane, r);
         const int tp = col / a.CinP, ci = col - tp * a.CinP;
         if (col >= a.K || ci >= a.Cin || co >= a.Cout) continue;
         const int w_ = tp % a.KW, h_ = tp / a.KW % a.KH, dk = tp / (a.KW * a.KH) - a.KT / 2;
@@ -596,14 +584,14 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-        const int col = j0 + wn * TN + j * 32 + (lane & 31);
+        const int col = j0 + wn * TN + j * TB + lane % TB;
         const int tp = col / a.CinP, ci = col - tp * a.CinP;
         if (col >= a.K || ci >= a.Cin) continue;
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int co = co0 + wm * TM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            for (int r = 0; r < RN; ++r) {
+                const int co = co0 + wm * TM + i * TB + row_of(lane, r);
                 if (co < a.Cout) atomicAdd(a.dw + (long)co * a.so + (long)ci * a.si + (long)tp * a.st, acc[i][j][r]);
             }
     }

@@ -6,14 +6,17 @@
 // 64 CUs: 39 us, 0.5 us per step of 64).  Here the wavefronts of a block take every KS-th chunk of 128 bytes of K each,
 // with LDS of their own, so that no barrier stands in the loop and eight chunks are in flight per CU; their partial tiles
 // meet in LDS once at the end (fp32, added in a fixed order).  One tile per block, no persistence: what fills the chip at
-// small sizes is tiles of 32 or 64 rows.  fp32 layers have the fp32 matrix rate of 157 TFLOP/s as their bound at every size;
-// there the point is that the two wavefronts of a SIMD are never in phase (92 TFLOP/s at 6272 x 2304 -> 256, 57 with a block-wide
-// barrier per step).  Two chunks in flight per wavefront instead of one change nothing on the small layers: bytes per CU, not
+// small sizes is tiles of 32 or 64 rows.  fp32 layers run here at every size; their products are six bf16 products each
+// (split_f32.h), which a wavefront cuts its operands for as it reads them out of LDS: 5.5 vector instructions per value, as long as
+// the matrix instructions they feed, is what bounds them then (us with the fp32 instructions, which bound them at 140 TFLOP/s, and
+// now: 100352 x 576 -> 64 97 and 76, 25088 x 1152 -> 128 88 and 68, 6272 x 2304 -> 256 86 and 66 = 112 TFLOP/s, 1568 x 4608 -> 512
+// 84 and 65).  Two chunks in flight per wavefront instead of one change nothing on the small layers: bytes per CU, not
 // latency, are what is left (392 x 4608 -> 512 in 32 x 32 tiles reads 590 KB per CU).
 #include <stdlib.h>
 #include <algorithm>
 #include "internal.h"
 #include "taps_inside.h"
+#include "split_f32.h"
 
 namespace tsm {
 
@@ -226,17 +229,24 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
         }
     };
 
-    f32x16 acc[MI][NJ];
+    f32x16 acc[ES == 2 ? MI : 1][ES == 2 ? NJ : 1];         // bf16: blocks of 32 x 32
+    f32x4 sums[ES == 4 ? 2 * MI : 1][ES == 4 ? 2 * NJ : 1];   // fp32: of 16 x 16
+    if constexpr (ES == 2) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+            for (int j = 0; j < 2 * NJ; ++j) sums[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     unsigned char* const st = smem + wave * STAGE;
     if (wave < nch) {
         const int wr = lr * 256 + (lane & 7) * 16;
-        const int r = lane & 31, hi = lane >> 5, sw = (r >> 1) & 7;
         load(wave);
         for (int q = wave; q < nch; q += KS) {
 #pragma unroll
@@ -245,30 +255,37 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
             for (int j = 0; j < PB; ++j) *(u32x4*)(st + TM * 128 + wr + (j & 1) * 128 + (j >> 1) * 2048) = breg[j];
             wave_lds_order();
             if (q + KS < nch) load(q + KS);
+            if constexpr (ES == 2) {
+                const int r = lane & 31, hi = lane >> 5, sw = (r >> 1) & 7;
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int pos = ((2 * ks + hi) ^ sw) * 16;
-                u32x4 af[MI], bf[NJ];
+                for (int ks = 0; ks < 4; ++ks) {
+                    const int pos = ((2 * ks + hi) ^ sw) * 16;
+                    u32x4 af[MI], bf[NJ];
 #pragma unroll
-                for (int i = 0; i < MI; ++i) af[i] = *(const u32x4*)(st + (i * 32 + r) * 128 + pos);
+                    for (int i = 0; i < MI; ++i) af[i] = *(const u32x4*)(st + (i * 32 + r) * 128 + pos);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) bf[j] = *(const u32x4*)(st + (TM + j * 32 + r) * 128 + pos);
-                // (result blocks are [channel][pixel]: a lane holds four consecutive channels of one pixel per quad)
-                if constexpr (ES == 2) {
+                    for (int j = 0; j < NJ; ++j) bf[j] = *(const u32x4*)(st + (TM + j * 32 + r) * 128 + pos);
+                    // (result blocks are [channel][pixel]: a lane holds four consecutive channels of one pixel per quad)
 #pragma unroll
                     for (int i = 0; i < MI; ++i)
 #pragma unroll
                         for (int j = 0; j < NJ; ++j)
                             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bf[j]), __builtin_bit_cast(bf16x8, af[i]), acc[i][j], 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-#pragma unroll
-                            for (int j = 0; j < NJ; ++j)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(bf[j][e]), __uint_as_float(af[i][e]), acc[i][j], 0, 0, 0);
                 }
+            } else {
+                // two vectors of a row, four apart, are the eight values a lane supplies to 32 products (both operands alike)
+                const int r = lane & 15, g = lane >> 4;
+                auto frag = [&](int row) {
+                    const int sw = (row >> 1) & 7;
+                    const f32x4 u = *(const f32x4*)(st + row * 128 + (g ^ sw) * 16), v = *(const f32x4*)(st + row * 128 + ((g + 4) ^ sw) * 16);
+                    const float f[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
+                    return split3(f);
+                };
+                Split3 bf[2 * NJ];
+#pragma unroll
+                for (int j = 0; j < 2 * NJ; ++j) bf[j] = frag(TM + j * 16 + r);
+#pragma unroll
+                for (int i = 0; i < 2 * MI; ++i) mma_split<2 * NJ>(bf, frag(i * 16 + r), sums[i]);
             }
             wave_lds_order();
         }
@@ -331,16 +348,21 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
         }
     }
     if (wave < nact) {   // the wavefront's partial tile, rows of SL 16-byte slots, slot s of row r at position s ^ (r % SL)
+        auto put = [&](int row, int slot, const f32x4& v) { *(f32x4*)(st + row * (TN * 4) + ((slot ^ (row & (SL - 1))) * 16)) = v; };
+        if constexpr (ES == 2) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int row = i * 32 + (lane & 31), slot = j * 8 + 2 * q + (lane >> 5);
-                    *(f32x4*)(st + row * (TN * 4) + ((slot ^ (row & (SL - 1))) * 16)) =
-                        f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                }
+                    for (int q = 0; q < 4; ++q)
+                        put(i * 32 + (lane & 31), j * 8 + 2 * q + (lane >> 5), f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2 * NJ; ++j) put(i * 16 + (lane & 15), j * 4 + (lane >> 4), sums[i][j]);
+        }
     }
     __syncthreads();
     auto add_up = [&](int v, float* f) {
