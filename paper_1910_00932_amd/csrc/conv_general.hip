@@ -391,8 +391,13 @@ static constexpr int GPX = 32;   // pixels per step
 // instructions for that take as long as the matrix instructions they feed (us with fp32 instructions and now: 6272 pixels 256 ->
 // 256 3x3 92 and 70, 1568 pixels 512 -> 512 3x3 93 and 67, 1568 pixels 2048 -> 512 51 and 43; 64 -> 64 3x3 level).  bf16: the
 // transposing read.
-template <typename T, int BCO, int BCI, int WM, int WN, bool RAG>
-__global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
+//
+// Two groups of four wavefronts with LDS of their own take half of a block's pixels each and meet in LDS at the end: as many
+// wavefronts per CU as two blocks, half the atomic additions, which were up to a third of the time (us with one group, with its
+// additions as plain stores, with two groups: 26912 pixels 72 -> 200 3x3 bf16 45.8, 30.1, 39.6, 25088 pixels 128 -> 128 3x3 fp32 79.7,
+// 60.8, 72.5, 25088 pixels 512 -> 128 1x1 44.3, 36.1, 41.9).
+template <typename T, int BCO, int BCI, int WM, int WN, int GW_GROUPS, bool RAG>
+__global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradArgs a) {
     static_assert(WM * WN == 4, "four wavefronts");
     constexpr int TM = BCO / WM, TN = BCI / WN;
     constexpr bool SPLIT = sizeof(T) == 4;             // fp32 on the bf16 matrix cores (see split_f32.h)
@@ -408,17 +413,22 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
     constexpr int RA = 256 / AV, RB = 256 / BV;        // rows per load pass
     constexpr int PA = GPX / RA, PB = GPX / RB;
     static_assert(256 % AV == 0 && 256 % BV == 0 && GPX % RA == 0 && GPX % RB == 0, "tile / thread mismatch");
-    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * STAGE];
-    __shared__ GenRow s_pix[3][GPX];
+    constexpr int NR = MI * NJ * RN;                   // sums per lane
+    static_assert(GW_GROUPS == 1 || (GW_GROUPS == 2 && NR / 2 * 256 * 4 <= 2 * STAGE && (MI % 2 == 0 || NJ == 1)), "half of them travel through the group's stages");
+    __shared__ __attribute__((aligned(16))) unsigned char s_mem[GW_GROUPS][2 * STAGE];
+    __shared__ GenRow s_row[GW_GROUPS][3][GPX];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int grp = GW_GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
+    unsigned char* const smem = s_mem[grp];
+    GenRow (*const s_pix)[GPX] = s_row[grp];
     const int wm = wave / WN, wn = wave % WN;
     const int co0 = ((int)blockIdx.y / a.col_tiles) * BCO;
     const int j0 = ((int)blockIdx.y % a.col_tiles) * BCI;
-    const long mbeg = (long)blockIdx.x * a.chunk;
-    long mend = mbeg + a.chunk;
+    const long half = a.chunk / GW_GROUPS;            // (whole steps; a group beyond the last pixel adds zeros)
+    const long mbeg = (long)blockIdx.x * a.chunk + grp * half;
+    long mend = mbeg + half;
     if (mend > a.M) mend = a.M;
-    if (mbeg >= mend) return;
     const int hw = a.Ho * a.Wo;
     const long frame = (long)a.H * a.W * a.Cin;
 
@@ -547,7 +557,7 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
         }
     };
 
-    const int nsteps = (int)((mend - mbeg + GPX - 1) / GPX);
+    const int nsteps = (int)(half / GPX);
     decode(0);
     if (nsteps > 1) decode(1);
     __syncthreads();
@@ -582,18 +592,31 @@ __global__ void __launch_bounds__(256, 2) gen_wgrad_kernel(GenWgradArgs a) {
         }
         set_at(acc, at, v);
     }
+    // a group keeps the first or the second half of its sums and hands over the other
+    constexpr int NK = NR / GW_GROUPS;
+    auto at = [&](int k) { return acc[k / (NJ * RN)][k / RN % NJ][k % RN]; };
+    const float* const theirs = (const float*)s_mem[GW_GROUPS - 1 - grp];
+    if constexpr (GW_GROUPS == 2) {
+        float* const mine = (float*)smem;
+#pragma unroll
+        for (int k = 0; k < NK; ++k) mine[k * 256 + tid] = grp == 0 ? at(k + NK) : at(k);
+        __syncthreads();
+    }
+    bool ok[NJ];
+    long off[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int col = j0 + wn * TN + j * TB + lane % TB;
         const int tp = col / a.CinP, ci = col - tp * a.CinP;
-        if (col >= a.K || ci >= a.Cin) continue;
+        ok[j] = col < a.K && ci < a.Cin;
+        off[j] = (long)ci * a.si + (long)tp * a.st;
+    }
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int r = 0; r < RN; ++r) {
-                const int co = co0 + wm * TM + i * TB + row_of(lane, r);
-                if (co < a.Cout) atomicAdd(a.dw + (long)co * a.so + (long)ci * a.si + (long)tp * a.st, acc[i][j][r]);
-            }
+    for (int k = 0; k < NK; ++k) {
+        const float v = GW_GROUPS == 1 ? at(k) : (grp == 0 ? at(k) : at((k + NK) % NR)) + theirs[k * 256 + tid];
+        const int idx = k + grp * NK, i = idx / (NJ * RN), r = idx % RN, j = k / RN % NJ;
+        const int co = co0 + wm * TM + i * TB + row_of(lane, r);
+        if (ok[j] && co < a.Cout) atomicAdd(a.dw + (long)co * a.so + off[j], v);
     }
 }
 
@@ -763,15 +786,23 @@ static int gen_wgrad_launch(GenWgradArgs& a, hipStream_t s) {
     const int bco = big ? 128 : 64, bci = big ? 128 : 64;
     a.col_tiles = cdiv(a.K, bci);
     const long tiles = (long)cdiv(a.Cout, bco) * a.col_tiles;
-    // two blocks per CU, and at least eight steps per block against the atomics of its tile
-    long want = 2L * cu_count() / tiles;
-    if (want < 1) want = 1;
-    long chunk = (a.M + want - 1) / want;
-    if (chunk < 8L * GPX) chunk = 8L * GPX;
-    a.chunk = (chunk + GPX - 1) / GPX * GPX;
-    const dim3 grid((unsigned)((a.M + a.chunk - 1) / a.chunk), (unsigned)tiles);
-    if (big) gen_wgrad_kernel<T, 128, 128, 2, 2, RAG><<<grid, dim3(256), 0, s>>>(a);
-    else gen_wgrad_kernel<T, 64, 64, 2, 2, RAG><<<grid, dim3(256), 0, s>>>(a);
+    // one round of blocks, eight wavefronts per CU, and at least eight steps per block against the atomics of its tile.  Two groups
+    // per block with the small tile for layers of a few steps (3136 pixels 64 -> 64 3x3 fp32 15.3 and 12.0 us, but 100352 pixels
+    // 108 and 116), and with the large one in bf16 where they leave no more CUs without one than single groups do (25600 pixels
+    // 312 -> 312 3x3, 66 tiles: 140 and 157).  Large fp32 layers run beside data gradients, which find room between small
+    // blocks: alone 80 and 71 us (figures above), in the step at 4 clips 10.43 and 10.76 ms.
+    const long cus = cu_count();
+    auto splits = [&](long slots) { return std::max(1L, slots / tiles); };
+    auto filled = [&](long slots) { const long n = splits(slots) * tiles; return (double)n / (double)((n + slots - 1) / slots * slots); };
+    const bool two = big ? sizeof(T) == 2 && filled(cus) >= 0.95 * filled(2 * cus) : a.M <= 8L * GPX * splits(2 * cus);
+    const long want = splits(two ? cus : 2 * cus), unit = two ? 2L * GPX : (long)GPX;
+    a.chunk = (std::max((a.M + want - 1) / want, 8L * GPX) + unit - 1) / unit * unit;
+    const dim3 grid((unsigned)((a.M + a.chunk - 1) / a.chunk), (unsigned)tiles), block(two ? 512 : 256);
+    if constexpr (sizeof(T) == 2)
+        if (big && two) gen_wgrad_kernel<T, 128, 128, 2, 2, 2, RAG><<<grid, block, 0, s>>>(a);
+    if (big && !two) gen_wgrad_kernel<T, 128, 128, 2, 2, 1, RAG><<<grid, block, 0, s>>>(a);
+    if (!big && two) gen_wgrad_kernel<T, 64, 64, 2, 2, 2, RAG><<<grid, block, 0, s>>>(a);
+    if (!big && !two) gen_wgrad_kernel<T, 64, 64, 2, 2, 1, RAG><<<grid, block, 0, s>>>(a);
     return check_launch(sizeof(T) == 4 ? "gen_wgrad_f32" : "gen_wgrad_bf16");
 }
 
