@@ -369,6 +369,10 @@ int block_tail_fwd(int dtype, const void* y, long rows, int C, const float* scal
 }
 
 // ---- backward, pass A: ReLU mask + the two BatchNorm reductions -------------------------------------
+// Up to five streams of memory with few wavefronts (512 blocks: every block is a partial row): what it runs at is how many
+// loads each has in flight.  Rows ahead, us, five tensors of 200704 x 256 bf16 and the five launches of a 64-clip step: none 135
+// and 1060 (3.8 TB/s), two 111 and 868 (4.6), four 122 and 892; 1024 blocks 112 and 925 - 1037, and more rows to add up.
+static constexpr int RBR_UR = 2;
 template <typename T, int V>
 __global__ void __launch_bounds__(256) relu_bn_bwd_reduce_kernel(
     const T* __restrict__ dout, const T* __restrict__ act, const T* __restrict__ y, long rows, int C, int cv,
@@ -389,20 +393,41 @@ __global__ void __launch_bounds__(256) relu_bn_bwd_reduce_kernel(
                 rs2[j] = rstd2[cvi * V + j];
             }
         }
-        for (long r = (long)blockIdx.x * blockDim.y + threadIdx.y; r < rows; r += (long)gridDim.x * blockDim.y) {
-            const long off = r * C + (long)cvi * V;
-            Pack<T, V> d = *(const Pack<T, V>*)(dout + off), a, yy = *(const Pack<T, V>*)(y + off), o, yy2;
-            if (act) a = *(const Pack<T, V>*)(act + off);
-            if (y2) yy2 = *(const Pack<T, V>*)(y2 + off);
+        // the next RBR_UR rows are on their way while these are added up (rows beyond the end re-read the last one)
+        const long step = (long)gridDim.x * blockDim.y, first = (long)blockIdx.x * blockDim.y + threadIdx.y;
+        Pack<T, V> d[RBR_UR], a[RBR_UR], yy[RBR_UR], yy2[RBR_UR];
+        auto load = [&](long r0) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) {
-                const float dz = (!act || Elem<T>::ld(a.v[j]) > 0.f) ? Elem<T>::ld(d.v[j]) : 0.f;
-                o.v[j] = Elem<T>::st(dz);
-                s1[j] += dz;
-                s2[j] = fmaf(dz, (Elem<T>::ld(yy.v[j]) - mu[j]) * rs[j], s2[j]);
-                if (y2) s3[j] = fmaf(dz, (Elem<T>::ld(yy2.v[j]) - mu2[j]) * rs2[j], s3[j]);
+            for (int u = 0; u < RBR_UR; ++u) {
+                const long r = r0 + u * step, off = (r < rows ? r : rows - 1) * C + (long)cvi * V;
+                d[u] = *(const Pack<T, V>*)(dout + off);
+                yy[u] = *(const Pack<T, V>*)(y + off);
+                if (act) a[u] = *(const Pack<T, V>*)(act + off);
+                if (y2) yy2[u] = *(const Pack<T, V>*)(y2 + off);
             }
-            if (dz_out) *(Pack<T, V>*)(dz_out + off) = o;
+        };
+        if (first < rows) load(first);
+        for (long r0 = first; r0 < rows; r0 += RBR_UR * step) {
+            Pack<T, V> o[RBR_UR];
+#pragma unroll
+            for (int u = 0; u < RBR_UR; ++u) {
+                const bool in = r0 + u * step < rows;
+#pragma unroll
+                for (int j = 0; j < V; ++j) {
+                    const float dz = in && (!act || Elem<T>::ld(a[u].v[j]) > 0.f) ? Elem<T>::ld(d[u].v[j]) : 0.f;
+                    o[u].v[j] = Elem<T>::st(dz);
+                    s1[j] += dz;
+                    s2[j] = fmaf(dz, (Elem<T>::ld(yy[u].v[j]) - mu[j]) * rs[j], s2[j]);
+                    if (y2) s3[j] = fmaf(dz, (Elem<T>::ld(yy2[u].v[j]) - mu2[j]) * rs2[j], s3[j]);
+                }
+            }
+            const long rn = r0 + RBR_UR * step;
+            if (rn < rows) load(rn);
+            if (dz_out) {
+#pragma unroll
+                for (int u = 0; u < RBR_UR; ++u)
+                    if (r0 + u * step < rows) *(Pack<T, V>*)(dz_out + (r0 + u * step) * C + (long)cvi * V) = o[u];
+            }
         }
     }
     block_partial_2<V>(s1, s2, cvi, cv, C, partial + (size_t)blockIdx.x * 2 * C);
