@@ -163,8 +163,9 @@ struct GenRow {
 };
 
 // D[pixels x channels], one tile per block.
-template <typename T, int BM, int BN, int WM, int WN, bool DGRAD, bool RAG>
+template <typename T, int BM, int BN, int WM, int WN, bool DGRAD, bool RAG, bool BUF>
 __global__ void __launch_bounds__(256, 2) gen_igemm_kernel(GenArgs a) {
+    static_assert(!BUF || (!RAG && !DGRAD), "whole vectors of one shift group, paddings that are not negative");
     static_assert(WM * WN == 4, "four wavefronts");
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 32, NJ = TN / 32;
@@ -242,9 +243,31 @@ __global__ void __launch_bounds__(256, 2) gen_igemm_kernel(GenArgs a) {
     };
     wrap();
 
+    // BUF: buffer loads, padding lanes beyond the end: no load stands under a condition, where it would be awaited at once (us
+    // without and with: 26912 x 648 -> 200 28 and 24, 50176 x 1080 -> 64 29 and 24, 25600 x 2808 -> 312 122 and 92 = 486 TFLOP/s)
+    constexpr uint32_t OOB = 0x80000000u;
+    constexpr int ES = (int)sizeof(T);
+    const uint32_t bias = BUF ? (uint32_t)(((long)a.padh * a.Ws + a.padw) * a.Cs * ES) : 0u;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.src - bias), 0, (int)((uint32_t)(a.F * frame * ES) + bias), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.wp, 0, (int)(uint32_t)((long)a.Cd * a.Kp * ES), 0x00020000);
     u32x4 areg[PA], breg[PB];
     auto load = [&]() {
         const bool kvalid = ltap < ntaps;
+        if constexpr (BUF) {
+            const int d = kt - a.KT / 2 + (DGRAD ? 0 : grp_dt(ch, a.fold));
+            const uint32_t need = (1u << th) | (1u << (8 + tw)) | (d > 0 ? 1u << 30 : 0u) | (d < 0 ? 1u << 31 : 0u);
+            const uint32_t va = (uint32_t)(((th * a.Ws + tw) * a.Cs + ch + d * (int)frame) * ES) + bias;
+            const uint32_t vb = (uint32_t)((((kt * a.KH + a.a0h[cls] + th * a.cstep) * a.KW + a.a0w[cls] + tw * a.cstep) * a.CsP + ch) * ES);
+#pragma unroll
+            for (int i = 0; i < PA; ++i)
+                areg[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(kvalid && (amask[i] & need) == need ? (uint32_t)((const char*)aptr[i] - (const char*)a.src) + va : OOB), 0, 0);
+#pragma unroll
+            for (int j = 0; j < PB; ++j)
+                breg[j] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(kvalid && bptr[j] ? (uint32_t)((const char*)bptr[j] - (const char*)a.wp) + vb : OOB), 0, 0);
+            ch += KE;
+            wrap();
+            return;
+        }
         const uint32_t need = (1u << th) | (1u << (8 + tw));
         const int d0 = kt - a.KT / 2;
         const int toff = (th * a.Ws + tw) * a.Cs;
@@ -732,9 +755,21 @@ static int gen_launch(GenArgs& a, hipStream_t s) {
     gen_classes(a, DGRAD, t.bm);
     a.ntiles = (a.Cd + t.bn - 1) / t.bn;
     const dim3 grid((unsigned)((a.mtiles + 7) / 8 * 8 * a.ntiles));
-    if (t.bm == 128 && t.bn == 128) gen_igemm_kernel<T, 128, 128, 2, 2, DGRAD, RAG><<<grid, dim3(256), 0, s>>>(a);
-    else if (t.bm == 128) gen_igemm_kernel<T, 128, 64, 2, 2, DGRAD, RAG><<<grid, dim3(256), 0, s>>>(a);
-    else gen_igemm_kernel<T, 64, 64, 2, 2, DGRAD, RAG><<<grid, dim3(256), 0, s>>>(a);
+    auto run = [&](auto buf) {
+        constexpr bool BUF = decltype(buf)::value;
+        if (t.bm == 128 && t.bn == 128) gen_igemm_kernel<T, 128, 128, 2, 2, DGRAD, RAG, BUF><<<grid, dim3(256), 0, s>>>(a);
+        else if (t.bm == 128) gen_igemm_kernel<T, 128, 64, 2, 2, DGRAD, RAG, BUF><<<grid, dim3(256), 0, s>>>(a);
+        else gen_igemm_kernel<T, 64, 64, 2, 2, DGRAD, RAG, BUF><<<grid, dim3(256), 0, s>>>(a);
+    };
+    // bf16 layers on a shifted copy, below 2 GiB with the padding in front of the first pixel and the taps behind the last
+    const long es = (long)sizeof(T), src = (long)a.F * a.Hs * a.Ws * a.Cs * es;
+    const long edge = 2 * (((long)a.KH + a.padh) * a.Ws + a.KW + a.padw) * a.Cs * es;
+    if constexpr (sizeof(T) == 2 && !DGRAD && !RAG) {
+        if (a.KT == 1 && src + edge < 0x7ff00000L && (long)a.Cd * a.Kp * es < 0x7ff00000L) run(std::true_type());
+        else run(std::false_type());
+    } else {
+        run(std::false_type());
+    }
     if (sizeof(T) == 4) return check_launch(DGRAD ? "gen_dgrad_f32" : "gen_fwd_f32");
     return check_launch(DGRAD ? "gen_dgrad_bf16" : "gen_fwd_bf16");
 }
