@@ -645,9 +645,11 @@ int block_bwd_flush(hipStream_t s) {
 // 5 us.  In a chain of small blocks a block's weight gradients share one, behind its last BatchNorm: they run beside the
 // next block's kernels.  Train step of 2 clips of 160 x 160, four micro-batches, output tensors of 1.6 to 13 MB: 11282 -> 11014
 // us.  Large tensors leave the caches in between: 8 clips of 224 x 224 with every block 6553 -> 6809, up to 30 MB 6594.
-static bool few_forks(const BlockPlan& b) {
+// A block on its own shares one where it is so small that the host's part is what bounds it: fp32 basic block of 64 channels on
+// 16 frames of 14 x 14 131 -> 122 us.
+static bool few_forks(const BlockPlan& b, bool chain) {
     const ConvP& p = b.st[b.nst - 1].p;
-    return p.rows_out() * p.Cout * (long)dtype_size(b.dtype) <= (8L << 20);
+    return p.rows_out() * p.Cout * (long)dtype_size(b.dtype) <= (chain ? 8L << 20 : 1L << 20);
 }
 
 // lag_slot < 0: the launch stream joins the weight-gradient stream at the end of the block.  lag_slot 0 / 1 (a chain of
@@ -659,7 +661,7 @@ int block_bwd_impl(BlockPlan& b, const void* x, const void* out, const void* dou
                    hipStream_t s, int lag_slot) {
     SideStream* const ss = dry ? nullptr : side_stream();
     bool forked = false;
-    const int rc = block_bwd_body(b, x, out, dout, dx, ws, dry, s, ss, lag_slot >= 0 && few_forks(b), forked);
+    const int rc = block_bwd_body(b, x, out, dout, dx, ws, dry, s, ss, few_forks(b, lag_slot >= 0), forked);
     if (lag_slot >= 0 && ss && rc == TSM_OK) {
         const int k = lag_slot & 1;
         if (ss->pending[k]) return fail(TSM_ERR_LAUNCH, "block backward: the scratch region of this slot is still in use");
