@@ -1095,6 +1095,7 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
         cur_n0 = next_n0;
         p_on_next = false;
     }
+    if constexpr (DIRECT) wait_vm_lds<0>();   // (the loads behind the last tile's steps, zeros, still go to this block's LDS)
 }
 
 // ---------------------------------------------------------------------------------
