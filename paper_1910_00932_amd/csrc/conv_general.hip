@@ -419,9 +419,22 @@ static constexpr int GPX = 32;   // pixels per step
 // wavefronts per CU as two blocks, half the atomic additions, which were up to a third of the time (us with one group, with its
 // additions as plain stores, with two groups: 26912 pixels 72 -> 200 3x3 bf16 45.8, 30.1, 39.6, 25088 pixels 128 -> 128 3x3 fp32 79.7,
 // 60.8, 72.5, 25088 pixels 512 -> 128 1x1 44.3, 36.1, 41.9).
-template <typename T, int BCO, int BCI, int WM, int WN, int GW_GROUPS, bool RAG>
-__global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradArgs a) {
+template <typename T, int BCO, int BCI, int GW_GROUPS>
+struct GenWgradLds {
+    static constexpr int PADB = 64;
+    static constexpr int ROWA = BCO * (int)sizeof(T) + PADB, ROWB = BCI * (int)sizeof(T) + PADB;
+    static constexpr int STAGE = GPX * (ROWA + ROWB);
+    __attribute__((aligned(16))) unsigned char mem[GW_GROUPS][2 * STAGE];
+    GenRow row[GW_GROUPS][3][GPX];
+    int lossy[2];          // fp32: set by any wavefront, behind the first step and behind the last
+};
+
+// EXACT: fp32 products by fp32 instructions.  Without it, fp32: false, and nothing added, where the parts of an operand do not hold
+// it or a sum leaves the range (see split_f32.h); the same for all threads of a block.
+template <typename T, int BCO, int BCI, int WM, int WN, int GW_GROUPS, bool RAG, bool EXACT>
+__device__ __forceinline__ bool gen_wgrad_block(const GenWgradArgs& a, GenWgradLds<T, BCO, BCI, GW_GROUPS>& lds, const int thread) {
     static_assert(WM * WN == 4, "four wavefronts");
+    typedef GenWgradLds<T, BCO, BCI, GW_GROUPS> Lds;
     constexpr int TM = BCO / WM, TN = BCI / WN;
     constexpr bool SPLIT = sizeof(T) == 4;             // fp32 on the bf16 matrix cores (see split_f32.h)
     constexpr int TB = SPLIT ? 16 : 32, RN = SPLIT ? 4 : 16;   // result blocks of TB x TB, RN values per lane
@@ -429,22 +442,17 @@ __global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradA
     typedef std::conditional_t<SPLIT, f32x4, f32x16> Acc;
     auto row_of = [](int lane, int r) { return SPLIT ? 4 * (lane >> 4) + r : 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
     constexpr int VE = 16 / (int)sizeof(T);
-    constexpr int PADB = 64;
-    constexpr int ROWA = BCO * (int)sizeof(T) + PADB, ROWB = BCI * (int)sizeof(T) + PADB;
-    constexpr int STAGE = GPX * (ROWA + ROWB);
+    constexpr int ROWA = Lds::ROWA, ROWB = Lds::ROWB, STAGE = Lds::STAGE;
     constexpr int AV = BCO / VE, BV = BCI / VE;
     constexpr int RA = 256 / AV, RB = 256 / BV;        // rows per load pass
     constexpr int PA = GPX / RA, PB = GPX / RB;
     static_assert(256 % AV == 0 && 256 % BV == 0 && GPX % RA == 0 && GPX % RB == 0, "tile / thread mismatch");
     constexpr int NR = MI * NJ * RN;                   // sums per lane
     static_assert(GW_GROUPS == 1 || (GW_GROUPS == 2 && NR / 2 * 256 * 4 <= 2 * STAGE && (MI % 2 == 0 || NJ == 1)), "half of them travel through the group's stages");
-    __shared__ __attribute__((aligned(16))) unsigned char s_mem[GW_GROUPS][2 * STAGE];
-    __shared__ GenRow s_row[GW_GROUPS][3][GPX];
-
-    const int grp = GW_GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
-    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
-    unsigned char* const smem = s_mem[grp];
-    GenRow (*const s_pix)[GPX] = s_row[grp];
+    const int grp = GW_GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(thread >> 8);
+    const int tid = thread & 255, lane = tid & 63, wave = tid >> 6;
+    unsigned char* const smem = lds.mem[grp];
+    GenRow (*const s_pix)[GPX] = lds.row[grp];
     const int wm = wave / WN, wn = wave % WN;
     const int co0 = ((int)blockIdx.y / a.col_tiles) * BCO;
     const int j0 = ((int)blockIdx.y % a.col_tiles) * BCI;
@@ -520,11 +528,24 @@ __global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradA
                 br[i] = load_shifted<T, RAG>((const T*)a.x + r.off + toff, col_ok && (r.mask & need) == need, r.mask, ch, a.Cin, a.fold, d0, frame);
         }
     };
+    // fp32: twice the bits, less one, of the smallest operand other than zero.  Taken as they are stored, once in a block: a
+    // comparison where they are cut, twice in the large tile, costs that tile's loop spills.
+    uint32_t least = ~0u;
     auto store = [&](int buf, int st) {
         unsigned char* S = smem + buf * STAGE;
+        if constexpr (SPLIT && !EXACT) {
+#pragma unroll
+            for (int i = 0; i < PA; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) least = min(least, (ar[i][q] << 1) - 1u);
+#pragma unroll
+            for (int i = 0; i < PB; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) least = min(least, (br[i][q] << 1) - 1u);
+        }
 #pragma unroll
         for (int i = 0; i < PA; ++i) {
-            if constexpr (SPLIT) ar[i] ^= (st & 1) ? 0x80000000u : 0u;   // (every other step's sums are formed of -dy)
+            if constexpr (SPLIT && !EXACT) ar[i] ^= (st & 1) ? 0x80000000u : 0u;   // (every other step's sums are formed of -dy)
             *(u32x4*)(S + (arow + i * RA) * ROWA + avec * 16) = ar[i];
         }
 #pragma unroll
@@ -544,7 +565,15 @@ __global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradA
     auto multiply = [&](int buf, float sign) {
         const unsigned char* A = smem + buf * STAGE;
         const unsigned char* B = A + GPX * ROWA;
-        if constexpr (sizeof(T) == 4) {
+        if constexpr (SPLIT && EXACT) {
+            auto value = [&](const unsigned char* base, int row, int chan, int e) {
+                return *(const float*)(base + ((lane >> 4) + 4 * e) * row + (chan + (lane & 15)) * 4);
+            };
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+                mma_exact<NJ>([&](int, int e) { return value(A, ROWA, wm * TM + i * 16, e); },
+                              [&](int j, int e) { return value(B, ROWB, wn * TN + j * 16, e); }, acc[i]);
+        } else if constexpr (SPLIT) {
             // a lane supplies pixels lane/16 + {0, 4, .. 28} of its channel, to both operands
             auto frag = [&](const unsigned char* base, int row, int chan) {
                 const unsigned char* p = base + (lane >> 4) * row + (chan + (lane & 15)) * 4;
@@ -581,12 +610,16 @@ __global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradA
     };
 
     const int nsteps = (int)(half / GPX);
+    if (SPLIT && !EXACT && thread == 0) lds.lossy[0] = lds.lossy[1] = 0;
     decode(0);
     if (nsteps > 1) decode(1);
     __syncthreads();
     load(0);
     store(0, 0);
+    if (SPLIT && !EXACT && __any(least < SPLIT_LEAST)) lds.lossy[0] = 1;
     __syncthreads();
+    // (where such operands are many, the steps are not worth while)
+    if (SPLIT && !EXACT && lds.lossy[0]) return false;
     for (int st = 0; st < nsteps; ++st) {
         const int buf = st & 1;
         if (st + 2 < nsteps) decode(st + 2);
@@ -594,6 +627,11 @@ __global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradA
         multiply(buf, (st & 1) ? -1.f : 1.f);
         if (st + 1 < nsteps) store(buf ^ 1, st + 1);
         __syncthreads();
+    }
+    if constexpr (SPLIT && !EXACT) {
+        if (__any(least < SPLIT_LEAST || !split_finite(acc))) lds.lossy[1] = 1;
+        __syncthreads();
+        if (lds.lossy[1]) return false;
     }
     uint64_t nan = a.inside_only ? nan_mask(acc) : 0ull;
     while (__builtin_expect(nan != 0, 0)) {
@@ -618,7 +656,7 @@ __global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradA
     // a group keeps the first or the second half of its sums and hands over the other
     constexpr int NK = NR / GW_GROUPS;
     auto at = [&](int k) { return acc[k / (NJ * RN)][k / RN % NJ][k % RN]; };
-    const float* const theirs = (const float*)s_mem[GW_GROUPS - 1 - grp];
+    const float* const theirs = (const float*)lds.mem[GW_GROUPS - 1 - grp];
     if constexpr (GW_GROUPS == 2) {
         float* const mine = (float*)smem;
 #pragma unroll
@@ -640,6 +678,18 @@ __global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradA
         const int idx = k + grp * NK, i = idx / (NJ * RN), r = idx % RN, j = k / RN % NJ;
         const int co = co0 + wm * TM + i * TB + row_of(lane, r);
         if (ok[j] && co < a.Cout) atomicAdd(a.dw + (long)co * a.so + off[j], v);
+    }
+    return true;
+}
+
+template <typename T, int BCO, int BCI, int WM, int WN, int GW_GROUPS, bool RAG>
+__global__ void __launch_bounds__(256 * GW_GROUPS, 2) gen_wgrad_kernel(GenWgradArgs a) {
+    __shared__ GenWgradLds<T, BCO, BCI, GW_GROUPS> lds;
+    if (gen_wgrad_block<T, BCO, BCI, WM, WN, GW_GROUPS, RAG, false>(a, lds, (int)threadIdx.x)) return;
+    if constexpr (sizeof(T) == 4) {
+        int thread = (int)threadIdx.x;
+        asm volatile("" : "+v"(thread));   // shares no address register with the code above, which has none to spare
+        gen_wgrad_block<T, BCO, BCI, WM, WN, GW_GROUPS, RAG, true>(a, lds, thread);
     }
 }
 

@@ -104,7 +104,7 @@ template <typename T> __device__ __forceinline__ u32x4 pack(const float* f) {
 // w, w + KS, w + 2*KS, ... of it.  RAG: source channels that are no multiple of a chunk (they are one of the vector), and bf16
 // layers with inside_only.
 template <typename T, int MI, int NJ, int KS, bool DGRAD, bool RAG>
-__global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
+__global__ void __launch_bounds__(KS * 64, MI * NJ == 1 ? 4 : 2) ksplit_kernel(KsArgs a) {
     constexpr int NT = KS * 64;
     constexpr int TM = 32 * MI, TN = 32 * NJ;
     constexpr int ES = (int)sizeof(T), VE = 16 / ES, KE = 128 / ES;
@@ -245,14 +245,18 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
             for (int j = 0; j < 2 * NJ; ++j) sums[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     unsigned char* const st = smem + wave * STAGE;
-    if (wave < nch) {
+    auto stage = [&]() {
         const int wr = lr * 256 + (lane & 7) * 16;
+#pragma unroll
+        for (int i = 0; i < PA; ++i) *(u32x4*)(st + wr + (i & 1) * 128 + (i >> 1) * 2048) = areg[i];
+#pragma unroll
+        for (int j = 0; j < PB; ++j) *(u32x4*)(st + TM * 128 + wr + (j & 1) * 128 + (j >> 1) * 2048) = breg[j];
+    };
+    bool lossy = false;    // fp32: an operand whose parts do not hold it, or a sum beyond the range (see split_f32.h)
+    if (wave < nch) {
         load(wave);
         for (int q = wave; q < nch; q += KS) {
-#pragma unroll
-            for (int i = 0; i < PA; ++i) *(u32x4*)(st + wr + (i & 1) * 128 + (i >> 1) * 2048) = areg[i];
-#pragma unroll
-            for (int j = 0; j < PB; ++j) *(u32x4*)(st + TM * 128 + wr + (j & 1) * 128 + (j >> 1) * 2048) = breg[j];
+            stage();
             wave_lds_order();
             if (q + KS < nch) load(q + KS);
             if constexpr (ES == 2) {
@@ -279,7 +283,7 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
                     const int sw = (row >> 1) & 7;
                     const f32x4 u = *(const f32x4*)(st + row * 128 + (g ^ sw) * 16), v = *(const f32x4*)(st + row * 128 + ((g + 4) ^ sw) * 16);
                     const float f[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
-                    return split3(f);
+                    return split3(f, lossy);
                 };
                 Split3 bf[2 * NJ];
 #pragma unroll
@@ -288,6 +292,55 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
                 for (int i = 0; i < 2 * MI; ++i) mma_split<2 * NJ>(bf, frag(i * 16 + r), sums[i]);
             }
             wave_lds_order();
+            if constexpr (ES == 4) if (__builtin_expect(__any(lossy), 0)) break;
+        }
+        if constexpr (ES == 4) lossy |= !split_finite(sums);
+    }
+    const int nact = nch < KS ? nch : KS;
+    // the wavefront's partial tile, rows of SL 16-byte slots, slot s of row r at position s ^ (r % SL)
+    auto put = [&](int row, int slot, const f32x4& v) { *(f32x4*)(st + row * (TN * 4) + ((slot ^ (row & (SL - 1))) * 16)) = v; };
+    auto put_tile = [&]() {
+        if constexpr (ES == 2) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        put(i * 32 + (lane & 31), j * 8 + 2 * q + (lane >> 5), f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2 * NJ; ++j) put(i * 16 + (lane & 15), j * 4 + (lane >> 4), sums[i][j]);
+        }
+    };
+    if (wave < nact) {
+        put_tile();
+        // Such a tile is formed again by fp32 instructions.  Behind the store, where the loop above, which has no register to
+        // spare, shares nothing with it: inside the loop it costs spills.
+        if constexpr (ES == 4) if (__builtin_expect(__any(lossy), 0)) {
+            wave_lds_order();
+#pragma unroll
+            for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2 * NJ; ++j) sums[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            kt = th = tw = 0;
+            cb = wave;
+            if (!RAG) wrap();
+            load(wave);
+            for (int q = wave; q < nch; q += KS) {
+                stage();
+                wave_lds_order();
+                if (q + KS < nch) load(q + KS);
+                const int r = lane & 15, g = lane >> 4;
+                auto value = [&](int row, int e) { return *(const float*)(st + row * 128 + ((g + (e & 4)) ^ ((row >> 1) & 7)) * 16 + (e & 3) * 4); };
+#pragma unroll
+                for (int i = 0; i < 2 * MI; ++i)
+                    mma_exact<2 * NJ>([&](int j, int e) { return value(TM + j * 16 + r, e); }, [&](int, int e) { return value(i * 16 + r, e); }, sums[i]);
+                wave_lds_order();
+            }
+            put_tile();
         }
     }
 
@@ -296,7 +349,6 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
     static_assert(NV == 1 || TM * CV % NT == 0, "tile / thread mismatch");
     const int vcol = tid % CV, r0 = (tid / CV) % TM, col = n0 + vcol * VE;
     const bool colok = col < a.Cd && tid / CV < TM;      // (small tiles have fewer vectors than threads)
-    const int nact = nch < KS ? nch : KS;
     const bool fuse_mask = DGRAD && (a.act_bits != nullptr || a.act != nullptr);
     const bool fuse_bn = fuse_mask && a.ybn != nullptr;
     const bool affine = !DGRAD && ES == 2 && a.ep_scale != nullptr;
@@ -345,23 +397,6 @@ __global__ void __launch_bounds__(KS * 64, 2) ksplit_kernel(KsArgs a) {
         if ((fuse_bn || affine) && colok) {
             mu[q] = DGRAD ? a.bn_mean[col + q] : a.ep_scale[col + q];
             rs[q] = DGRAD ? a.bn_rstd[col + q] : a.ep_shift[col + q];
-        }
-    }
-    if (wave < nact) {   // the wavefront's partial tile, rows of SL 16-byte slots, slot s of row r at position s ^ (r % SL)
-        auto put = [&](int row, int slot, const f32x4& v) { *(f32x4*)(st + row * (TN * 4) + ((slot ^ (row & (SL - 1))) * 16)) = v; };
-        if constexpr (ES == 2) {
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        put(i * 32 + (lane & 31), j * 8 + 2 * q + (lane >> 5), f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
-        } else {
-#pragma unroll
-            for (int i = 0; i < 2 * MI; ++i)
-#pragma unroll
-                for (int j = 0; j < 2 * NJ; ++j) put(i * 16 + (lane & 15), j * 4 + (lane >> 4), sums[i][j]);
         }
     }
     __syncthreads();

@@ -5,8 +5,8 @@
 // the size of the group's sum, and is then added in fp32: the fp32 instruction rounds the whole sum for every two products.
 // Error against 64 bits, 2-norm, that instruction -> this: 1x1 and 3x3 layers of 64 to 4608 products 0.6e-7 .. 4.2e-7 ->
 // 0.3e-7 .. 1.2e-7, weight gradients of 49 to 401408 pixels 0.9e-7 .. 4.1e-7 -> 0.7e-7 .. 3.9e-7 (no layer larger than before).
-// An infinite operand, or one that rounds to an infinite x0, makes NaN of its sums (x - x0): callers form those again.
-// Operands and products below 2^-108 lose the bits that bf16 and fp32 cannot hold.
+// Operands that the parts cannot hold (see split3), and sums that leave fp32's range where the exact one need not (x0*y0 may be
+// larger than x*y), are the caller's to form again by fp32 instructions (mma_exact).
 #pragma once
 #include "common.h"
 
@@ -16,9 +16,16 @@ typedef uint32_t split_u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 split_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float split_f32x4 __attribute__((ext_vector_type(4)));
 
+static constexpr int SPLIT_LOSSY = 0x093;   // class of a float: NaN (bits 0, 1), subnormal (bits 4, 7)
+static constexpr uint32_t SPLIT_LEAST = (17u << 24) - 1u;   // twice the bits of 2^-110, less one: bits of zero, less one, are above it
+
 struct Split3 { split_u32x4 p[3]; };   // eight values, three parts of them
 
-__device__ __forceinline__ Split3 split3(const float (&f)[8]) {
+// From 2^-110 on an operand is its three parts: its last bit is a whole multiple of 2^-133, the smallest bf16, and the matrix cores
+// keep subnormal operands, products and sums.  lossy: set where x2 is subnormal, as it is for every smaller x that is not
+// (below 2^-103 it may be), or NaN: an infinite x, or one that rounds to an infinite x0.  One comparison per value beside the 5.5
+// instructions that cut it.
+__device__ __forceinline__ Split3 split3(const float (&f)[8], bool& lossy) {
     Split3 s;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -27,11 +34,18 @@ __device__ __forceinline__ Split3 split3(const float (&f)[8]) {
         for (int k = 0; k < 3; ++k) {
             const uint32_t w = pack_bf16x2(lo, hi);
             s.p[k][q] = w;
+            if (k == 2) break;
             lo -= __uint_as_float(w << 16);
             hi -= __uint_as_float(w & 0xffff0000u);
         }
+        lossy |= __builtin_amdgcn_classf(lo, SPLIT_LOSSY) || __builtin_amdgcn_classf(hi, SPLIT_LOSSY);
     }
     return s;
+}
+
+__device__ __forceinline__ Split3 split3(const float (&f)[8]) {
+    bool lossy = false;
+    return split3(f, lossy);
 }
 
 // sum[i][j] += a[i] * b (16 x 16 tiles, 32 products each): a chain of its own from zero, the small parts first.
@@ -70,6 +84,34 @@ __device__ __forceinline__ void mma_split_b(const Split3& a, const Split3 (&b)[N
     for (int j = 0; j < N; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) sum[j][r] = fmaf(t[j][r], sign, sum[j][r]);
+}
+
+// Whether all sums are finite numbers.
+template <int M, int N>
+__device__ __forceinline__ bool split_finite(const split_f32x4 (&sum)[M][N]) {
+    bool inf = false;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) inf |= __builtin_amdgcn_classf(sum[i][j][r], 0x207);   // NaN, infinities
+    return !inf;
+}
+
+// sum[j] += 32 products by fp32 instructions, a chain of its own: a(j, e) and b(j, e) are the eight values that a lane supplies to
+// split3.  For the rare operands that cannot be cut, so with few registers.
+template <int N, typename A, typename B>
+__device__ __forceinline__ void mma_exact(A a, B b, split_f32x4 (&sum)[N]) {
+    split_f32x4 t[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) t[j] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int j = 0; j < N; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a(j, e), b(j, e), t[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < N; ++j) sum[j] += t[j];
 }
 
 }  // namespace tsm

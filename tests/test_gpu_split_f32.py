@@ -64,3 +64,54 @@ def test_values_whose_first_part_is_infinite():
         assert torch.isfinite(got).all(), name
         rows = (got - ref).abs() / ref.abs().amax(dim=1, keepdim=True)
         assert float(rows.max()) < 1e-5, name
+
+
+# Operands with bits that three bf16 parts cannot hold (below 2^-110) go through the fp32 instruction, whose sums keep BOUND.  The
+# shapes: every number of wavefronts per tile, whole and ragged chunks, both tiles of the weight gradient, one and two groups.
+TINY_SHAPES = [(2, 5, 7, 32, 32), (8, 14, 14, 64, 128), (8, 33, 31, 40, 72), (32, 28, 28, 128, 64), (16, 56, 56, 64, 192)]
+
+
+@pytest.mark.parametrize("power", [-112, -118, -125])
+@pytest.mark.parametrize("shape", TINY_SHAPES)
+def test_operands_below_the_range_of_the_parts(shape, power):
+    """All of x, then of dy and w, between 2^(power-3) and 2^(power+3); the partner brings the sums back."""
+    for tiny in ("x", "dy", "w"):
+        x, w, dy = _run(*shape, 1.0, 1.0, 1.0)
+        s = {k: torch.tensor(float(power if k == tiny else -power - 20)) for k in ("x", "w", "dy")}
+        x, w, dy = (torch.exp2(s[k]) * v for k, v in (("x", x), ("w", w), ("dy", dy)))
+        for name, (got, ref) in _layer(x, w, dy).items():
+            if not torch.isfinite(ref.float()).all():      # (the product of the two large ones)
+                continue
+            err = float((got - ref).norm() / ref.norm())
+            assert err < BOUND, (tiny, name, err)
+
+
+@pytest.mark.parametrize("shape", TINY_SHAPES)
+def test_a_few_operands_below_the_range(shape):
+    """Single tiny values with a huge partner of their own among ordinary ones: the results that they reach."""
+    F, H, W, cin, cout = shape
+    x, w, dy = _run(*shape, 1.0, 1.0, 1.0)
+    small, large = 1.2345678 * 2.0 ** -124, 2.0 ** 124
+    w[:, 3], x[..., 3] = 0.0, 0.0
+    x[-1, -1, -1, 3], w[cout - 1, 3] = small, large
+    dy[..., 5], dy[0, 0, 0, 5] = 0.0, small
+    w[5] = 0.0
+    w[5, cin - 1] = large
+    out = _layer(x, w, dy)
+    for name in ("y", "dx"):
+        got, ref = out[name]
+        keep = ref.abs() < 1e30
+        err = float((got - ref)[keep].norm() / ref[keep].norm())
+        assert err < BOUND, (name, err)
+    got, ref = out["y"]
+    assert abs(float(got[-1, cout - 1] - ref[-1, cout - 1])) < 1e-5 * max(1.0, abs(float(ref[-1, cout - 1])))
+
+
+def test_results_at_the_top_of_the_range():
+    """x*y = 2^128 (1 - 2^-23), just inside fp32, where the product of the first parts is 2^128."""
+    v = 2.0 ** 64 * (1 - 2.0 ** -24)
+    x, w, dy = torch.zeros(2, 4, 4, 64), torch.zeros(64, 64, 1, 1), torch.zeros(2, 4, 4, 64)
+    x[0, 1, 2, 5], w[7, 5], dy[1, 2, 3, 9], w[9, 11], dy[0, 1, 2, 20] = v, v, v, v, v
+    for name, (got, ref) in _layer(x, w, dy).items():
+        assert torch.isfinite(got).all() and float(ref.abs().max()) > 3.4e38, name
+        assert torch.equal(got.float(), ref.float()), name
