@@ -412,8 +412,8 @@ static constexpr int GPX = 32;   // pixels per step
 // Operand rows go to LDS as loaded, [pixel][channel], padded by 64 bytes so that the four pixels that a wavefront reads together
 // fall into different banks.  fp32: a lane reads its channel of eight pixels and cuts them into three parts; the vector
 // instructions for that take as long as the matrix instructions they feed (us with fp32 instructions and now: 6272 pixels 256 ->
-// 256 3x3 92 and 70, 1568 pixels 512 -> 512 3x3 93 and 67, 1568 pixels 2048 -> 512 51 and 43; 64 -> 64 3x3 level).  bf16: the
-// transposing read.
+// 256 3x3 92 and 74, 1568 pixels 512 -> 512 3x3 95 and 78, 1568 pixels 2048 -> 512 53 and 51, 100352 pixels 64 -> 64 3x3 110 and
+// 113).  bf16: the transposing read.
 //
 // Two groups of four wavefronts with LDS of their own take half of a block's pixels each and meet in LDS at the end: as many
 // wavefronts per CU as two blocks, half the atomic additions, which were up to a third of the time (us with one group, with its
@@ -531,6 +531,9 @@ __device__ __forceinline__ bool gen_wgrad_block(const GenWgradArgs& a, GenWgradL
     // fp32: twice the bits, less one, of the smallest operand other than zero.  Taken as they are stored, once in a block: a
     // comparison where they are cut, twice in the large tile, costs that tile's loop spills.
     uint32_t least = ~0u;
+    // Every other step's sums are formed of -dy (see mma_split_b), and the blocks and groups of a tile begin with different signs, so
+    // that odd numbers of steps leave nothing over either.
+    auto negated = [&](int st) { return ((st + (int)blockIdx.x + grp) & 1) != 0; };
     auto store = [&](int buf, int st) {
         unsigned char* S = smem + buf * STAGE;
         if constexpr (SPLIT && !EXACT) {
@@ -545,7 +548,7 @@ __device__ __forceinline__ bool gen_wgrad_block(const GenWgradArgs& a, GenWgradL
         }
 #pragma unroll
         for (int i = 0; i < PA; ++i) {
-            if constexpr (SPLIT && !EXACT) ar[i] ^= (st & 1) ? 0x80000000u : 0u;   // (every other step's sums are formed of -dy)
+            if constexpr (SPLIT && !EXACT) ar[i] ^= negated(st) ? 0x80000000u : 0u;
             *(u32x4*)(S + (arow + i * RA) * ROWA + avec * 16) = ar[i];
         }
 #pragma unroll
@@ -624,7 +627,7 @@ __device__ __forceinline__ bool gen_wgrad_block(const GenWgradArgs& a, GenWgradL
         const int buf = st & 1;
         if (st + 2 < nsteps) decode(st + 2);
         if (st + 1 < nsteps) load(st + 1);
-        multiply(buf, (st & 1) ? -1.f : 1.f);
+        multiply(buf, negated(st) ? -1.f : 1.f);
         if (st + 1 < nsteps) store(buf ^ 1, st + 1);
         __syncthreads();
     }

@@ -7,10 +7,10 @@
 // with LDS of their own, so that no barrier stands in the loop and eight chunks are in flight per CU; their partial tiles
 // meet in LDS once at the end (fp32, added in a fixed order).  One tile per block, no persistence: what fills the chip at
 // small sizes is tiles of 32 or 64 rows.  fp32 layers run here at every size; their products are six bf16 products each
-// (split_f32.h), which a wavefront cuts its operands for as it reads them out of LDS: 5.5 vector instructions per value, as long as
+// (split_f32.h), which a wavefront cuts its operands for as it reads them out of LDS: 6.5 vector instructions per value, as long as
 // the matrix instructions they feed, is what bounds them then (us with the fp32 instructions, which bound them at 140 TFLOP/s, and
-// now: 100352 x 576 -> 64 97 and 76, 25088 x 1152 -> 128 88 and 68, 6272 x 2304 -> 256 86 and 66 = 112 TFLOP/s, 1568 x 4608 -> 512
-// 84 and 65).  Two chunks in flight per wavefront instead of one change nothing on the small layers: bytes per CU, not
+// now: 100352 x 576 -> 64 97 and 84, 25088 x 1152 -> 128 87 and 76, 6272 x 2304 -> 256 85 and 73 = 102 TFLOP/s, 1568 x 4608 -> 512
+// 85 and 71; 7 to 9 % of it for the comparison that finds operands which cannot be cut).  Two chunks in flight per wavefront instead of one change nothing on the small layers: bytes per CU, not
 // latency, are what is left (392 x 4608 -> 512 in 32 x 32 tiles reads 590 KB per CU).
 #include <stdlib.h>
 #include <algorithm>
@@ -279,22 +279,30 @@ __global__ void __launch_bounds__(KS * 64, MI * NJ == 1 ? 4 : 2) ksplit_kernel(K
             } else {
                 // two vectors of a row, four apart, are the eight values a lane supplies to 32 products (both operands alike)
                 const int r = lane & 15, g = lane >> 4;
-                auto frag = [&](int row) {
+                auto frag = [&](int row, bool negate) {
                     const int sw = (row >> 1) & 7;
                     const f32x4 u = *(const f32x4*)(st + row * 128 + (g ^ sw) * 16), v = *(const f32x4*)(st + row * 128 + ((g + 4) ^ sw) * 16);
                     const float f[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
-                    return split3(f, lossy);
+                    return split3(f, lossy, negate);
                 };
                 Split3 bf[2 * NJ];
 #pragma unroll
-                for (int j = 0; j < 2 * NJ; ++j) bf[j] = frag(TM + j * 16 + r);
+                for (int j = 0; j < 2 * NJ; ++j) bf[j] = frag(TM + j * 16 + r, false);
 #pragma unroll
-                for (int i = 0; i < 2 * MI; ++i) mma_split<2 * NJ>(bf, frag(i * 16 + r), sums[i]);
+                for (int i = 0; i < 2 * MI; ++i) mma_split<2 * NJ>(bf, frag(i * 16 + r, (i & 1) != 0), sums[i]);
             }
             wave_lds_order();
             if constexpr (ES == 4) if (__builtin_expect(__any(lossy), 0)) break;
         }
-        if constexpr (ES == 4) lossy |= !split_finite(sums);
+        if constexpr (ES == 4) {
+            // The matrix core's sums lean towards minus infinity.  Every other 16 pixels are the sums of -x, so that what is added up
+            // over pixels later (BatchNorm's sums, weight gradients) does not lean with them.
+#pragma unroll
+            for (int i = 1; i < 2 * MI; i += 2)
+#pragma unroll
+                for (int j = 0; j < 2 * NJ; ++j) sums[i][j] = -sums[i][j];
+            lossy |= !split_finite(sums);
+        }
     }
     const int nact = nch < KS ? nch : KS;
     // the wavefront's partial tile, rows of SL 16-byte slots, slot s of row r at position s ^ (r % SL)
@@ -667,6 +675,7 @@ static long ks_tiles(const ConvP& p, int dtype, bool dgrad, long* idle = nullptr
 
 // Tile and split by how many 64 x 64 tiles there are for the CUs, which all hold eight wavefronts of the kernel:
 // the fewer, the smaller the tile and the more wavefronts share one.  Measured, us (fp32, then bf16; rows x K -> N):
+// (fp32: with the fp32 instructions)
 //   tiles / CU > 2.5     64x64, 2 wavefronts: 25088 x 1152 -> 128 fp32 82 (4 wavefronts: 90, 8: 97)
 //   tiles / CU > 1       64x64, 4: 6272 x 2304 -> 256 fp32 83 (2: 147, 8: 88), bf16 21 (8: 24)
 //   tiles / CU > 1/2     64x64, 8: 1568 x 4608 -> 512 fp32 83 (4: 90, 32x32: 93), 6272 x 1152 -> 128 bf16 11.0 (11.5, 20)
@@ -696,7 +705,7 @@ static int ks_dispatch(KsArgs& a, KsTile t, hipStream_t s) {
 }
 
 // fp32 layers, and bf16 layers that conv_mfma.hip does not take, run here whenever they can: the alternative is the block-
-// wide schedule of conv_general.hip (fp32 6272 x 2304 -> 256: 129 us there, 83 here; 25088 x 1152 -> 128: 106, 82; bf16
+// wide schedule of conv_general.hip (fp32 6272 x 2304 -> 256: 129 us there, 73 here; 25088 x 1152 -> 128: 106, 76; bf16
 // data gradient 26912 x 1800 -> 72 with split shift groups: 56, 36).  bf16 layers that it does take change over where
 // there are at most two 64 x 64 tiles per CU, and so do forward layers that read a shifted copy (26912 x 648 -> 200, 1684 tiles:
 // its three directions together 132.1 us with the general kernel, 140.0 with this one).  Measured on both sides of the line, us there -> here: 6272 x 2304 -> 256 (392

@@ -1,6 +1,8 @@
-// fp32 products on the bf16 matrix cores.  x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1, all exact
-// (8 + 8 + 8 significant bits), and x*y is the sum of the six products of order 2^-18 and above, each exact in fp32; what is
-// left out, x1*y2 + x2*y1 + x2*y2, is at most 2^-26 of |x*y|.  Per 32 products of a 16 x 16 tile six instructions of 16 cycles stand
+// fp32 products on the bf16 matrix cores, the method of Henry, Tang and Heinecke ("Leveraging the bfloat16 artificial intelligence
+// datatype for higher-precision computations", 2019).  x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1, all
+// exact (8 + 8 + 8 significant bits), and x*y is the sum of the six largest part products, each exact in fp32.  What is left out,
+// x1*y2 + x2*y1 + x2*y2, is at most 2^-24 of |x*y| (the square of 0x3f807fc0, 1 + 2^-8 - 2^-17; 2.7 % of random pairs exceed 2^-26):
+// one rounding of a product, where the fp32 instruction rounds sums only, and no more.  Per 32 products of a 16 x 16 tile six instructions of 16 cycles stand
 // for eight of 32.  Each such group is a chain of its own, the small parts first, so that one rounding of the matrix core is of
 // the size of the group's sum, and is then added in fp32: the fp32 instruction rounds the whole sum for every two products.
 // Error against 64 bits, 2-norm, that instruction -> this: 1x1 and 3x3 layers of 64 to 4608 products 0.6e-7 .. 4.2e-7 ->
@@ -25,11 +27,11 @@ struct Split3 { split_u32x4 p[3]; };   // eight values, three parts of them
 // keep subnormal operands, products and sums.  lossy: set where x2 is subnormal, as it is for every smaller x that is not
 // (below 2^-103 it may be), or NaN: an infinite x, or one that rounds to an infinite x0.  One comparison per value beside the 5.5
 // instructions that cut it.
-__device__ __forceinline__ Split3 split3(const float (&f)[8], bool& lossy) {
+__device__ __forceinline__ Split3 split3(const float (&f)[8], bool& lossy, bool negate = false) {
     Split3 s;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        float lo = f[2 * q], hi = f[2 * q + 1];
+        float lo = negate ? -f[2 * q] : f[2 * q], hi = negate ? -f[2 * q + 1] : f[2 * q + 1];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const uint32_t w = pack_bf16x2(lo, hi);
@@ -65,9 +67,10 @@ __device__ __forceinline__ void mma_split(const Split3 (&a)[M], const Split3& b,
     for (int i = 0; i < M; ++i) sum[i] += t[i];
 }
 
-// The same for one a and several b: sum[j] += sign * (a * b[j]).  The matrix core's own sums lean towards minus infinity
-// (weight gradients over 100352 pixels: 4.2e-7 off 64 bits, 2.0e-7 in fp32 instructions): in long sums every other
-// chain is formed of -a and subtracted.
+// The same for one a and several b: sum[j] += sign * (a * b[j]).  The matrix core's own sums lean towards minus infinity (weight
+// gradients over 100352 pixels: 4.2e-7 off 64 bits, 2.0e-7 in fp32 instructions): in long sums every other chain is formed of -a
+// and subtracted.  Where results are added up later instead (forward, data gradients), half of them are formed of -a: the mean over
+// a tensor of sums of 2048 to 4608 products was off by 6e-8 to 8e-8 of the mean magnitude, and is by 3e-10 (6e-10).
 template <int N>
 __device__ __forceinline__ void mma_split_b(const Split3& a, const Split3 (&b)[N], float sign, split_f32x4 (&sum)[N]) {
     constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};

@@ -115,3 +115,38 @@ def test_results_at_the_top_of_the_range():
     for name, (got, ref) in _layer(x, w, dy).items():
         assert torch.isfinite(got).all() and float(ref.abs().max()) > 3.4e38, name
         assert torch.equal(got.float(), ref.float()), name
+
+
+# The matrix core's sums lean towards minus infinity, by 6e-8 of the mean magnitude over 2048 products and 6e-8 over 100352 pixels
+# where nothing is done about it.  Half of all sums are formed of the negated operand, so the mean over a tensor, of N results that
+# are off by 1e-7 to 3e-7 of it at random, stays within 5 * 3e-7 / sqrt(N) (3e-9 .. 2e-8); fp32 instructions: 1e-9.
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("shape,names,bound", [((8, 14, 14, 2048, 64), ("y",), 6e-9), ((8, 14, 14, 64, 2048), ("dx",), 6e-9),
+                                               ((2, 14, 14, 2048, 32), ("y",), 2e-8), ((1, 12, 12, 1024, 36), ("y",), 2e-8),
+                                               ((32, 56, 56, 64, 64), ("y", "dx", "dw"), 2.5e-8), ((4, 28, 28, 64, 64), ("dw",), 2.5e-8)])
+def test_sums_do_not_lean(shape, names, bound, relu):
+    x, w, dy = _run(*shape, 1.0, 1.0, 1.0)
+    out = _layer(x.relu() if relu else x, w, dy)
+    for name in names:
+        got, ref = out[name]
+        lean = float((got - ref).mean() / ref.abs().mean())
+        assert abs(lean) < bound, (name, lean)
+
+
+@pytest.mark.parametrize("shape", [(2, 7, 7, 4608, 32), (8, 14, 14, 2048, 64), (4, 14, 14, 64, 2048), (16, 28, 28, 256, 256)])
+def test_long_sums_of_one_sign(shape):
+    """Forward and data gradient over up to 4608 products of one sign: a sum per 32 of them, whose additions are off by
+    sqrt(K/32/8) * 2^-25 at most in each of up to eight partial sums, and one rounding: 8e-8 (fp32 instructions: 1.0e-7 .. 1.8e-7)."""
+    out = _layer(*_run(*shape, 1.0, 1.0, 1.0, positive=True))
+    for name in ("y", "dx"):
+        got, ref = out[name]
+        assert float((got - ref).norm() / ref.norm()) < 8e-8, name
+
+
+def test_products_whose_left_out_parts_have_one_sign():
+    """x = 1 + 2^-8 + ..: of all operands the one whose square loses most, 2^-24 of it, by the three part products that are left
+    out; with as much for the rounding of the sum."""
+    v = torch.tensor([0x3f807fc0], dtype=torch.int32).view(torch.float32)
+    x, w, dy = (t * 0 + v for t in _run(8, 14, 14, 256, 128, 1.0, 1.0, 1.0))
+    for name, (got, ref) in _layer(x, w, dy).items():
+        assert float(((got - ref) / ref).abs().max()) <= 2.0 ** -23, name
