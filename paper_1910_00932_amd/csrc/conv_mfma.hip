@@ -464,20 +464,22 @@ __global__ void __launch_bounds__(256, MINB) igemm_kernel(IgemmArgs a) {
 //    instead of 64-bit pointer arithmetic.  Lanes that fall on padding pass an offset beyond the buffer and
 //    receive zeros from the bounds check.  The buffer starts `bias` bytes before the tensor so that the offset
 //    of a row's tap origin, which may lie in the padding in front of the first frame, is never negative.
-//  * LDS holds two to four stages.  A stage is the A rows [BM][64] followed by the B rows [BN][64], 128 bytes per row
+//  * LDS holds two or three stages.  A stage is the A rows [BM][64] followed by the B rows [BN][64], 128 bytes per row
 //    without padding; position p (16 bytes) of row r holds the row's K vector p ^ ((r >> 1) & 7), which spreads
 //    the 16-byte fragment reads of 16 consecutive rows over 16 different bank groups; thread t's piece of a pass lies at
 //    16 * t, so a load can leave it there without a register in between.  The stream of K steps runs across tile
 //    boundaries, so a tile's first steps are on the chip before the previous tile's epilogue starts.
-//  * 128-column tiles and small 64-column results load straight into LDS (three or four stages: two or three steps in flight
-//    behind the one at work): what bounds their steps is the LDS, 128 KB of fragment reads and 48 KB of operands per 64 K of a
+//  * 128-column tiles and small 64-column results load straight into LDS (three stages: two steps in flight behind the
+//    one at work): what bounds their steps is the LDS, 128 KB of fragment reads and 48 KB of operands per 64 K of a
 //    256 x 128 tile at 128 bytes a clock against 1024 clocks of MFMAs, and the loads' way through registers put its
 //    instructions and waits on top.  Us with registers -> without: 12544 x 2304 -> 256 35.0 -> 31.2
 //    (475 TFLOP/s), 25088 x 2304 -> 256 47.8 -> 42.8, 50176 x 1152 -> 128 30.0 -> 27.9, 25088 x 4608 -> 512 (128 x 128) 58.7 -> 51.7,
 //    200704 x 576 -> 64 45.0 -> 41.6; data gradients 100352 x 2304 -> 256 166 -> 154, stride 2 100352 x 4608 -> 512 169 -> 147.
 //    256-column tiles (two 64 KB stages: one step in flight) and streamed 64-column results keep a step in registers: 100352
 //    x 1024 -> 256 66 with, 73 without; 1605632 x 256 -> 64 191, 203.  Four wavefronts of 128 x 64 instead of eight of 64 x 64,
-//    a quarter less to read from LDS, wait on themselves: 25088 x 2304 -> 256 50.0.
+//    a quarter less to read from LDS, wait on themselves: 25088 x 2304 -> 256 50.0.  A fourth stage, for which the 128 x 64 tile has
+//    room, makes three steps of every tile's fewer: 37632 x 64 -> 64 12.9 with three, 13.7 with four (registers 13.1), its data
+//    gradient 12.4, 13.2 (12.4), 37632 x 576 -> 64 20.9 any way, data gradient 19.3, 19.4 (20.3).
 static constexpr uint32_t OOB_OFFSET = 0x80000000u;   // buffers are smaller than 2 GiB
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
@@ -485,7 +487,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 }
 
 constexpr bool ring_direct(int BM, int BN, bool stream) { return BN == 128 || BM == 128 || (BN == 64 && !stream); }
-constexpr int ring_stages(int BM, int BN, bool stream) { return !ring_direct(BM, BN, stream) ? 2 : BM == 128 && BN == 64 ? 4 : 3; }
+constexpr int ring_stages(int BM, int BN, bool stream) { return ring_direct(BM, BN, stream) ? 3 : 2; }
 constexpr bool ring_alias(int BM, int BN) { return BN == 256 || (BM == 256 && BN == 128); }
 constexpr size_t ring_smem(int BM, int BN, int WM, int WN, bool stream) {
     const size_t stage = (size_t)(BM + BN) * BK * 2, cst = (size_t)WM * 32 * (BN + 8) * 2;
@@ -523,7 +525,7 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
     constexpr int NT = WM * WN * 64;                // threads
     constexpr int NS = ring_stages(BM, BN, STREAM); // LDS stages
     constexpr bool DIRECT = ring_direct(BM, BN, STREAM);   // loads go straight to LDS
-    constexpr int AHEAD = DIRECT ? NS - 1 : 2;      // steps between a step's loads and its product
+    constexpr int AHEAD = 2;                        // steps between a step's loads and its product
     constexpr int MI = BM / (WM * 32), NJ = BN / (WN * 32);   // 32x32 MFMA tiles per wavefront
     constexpr int HM = BM / MI;                     // rows per epilogue pass; wavefront rows: i*HM + wm*32
     constexpr int TN = BN / WN;
