@@ -643,13 +643,26 @@ int block_bwd_flush(hipStream_t s) {
 
 // A fork (an event recorded on one stream, waited for on the other) costs the host 12 us, four launches, and the launch stream
 // 5 us.  In a chain of small blocks a block's weight gradients share one, behind its last BatchNorm: they run beside the
-// next block's kernels.  Train step of 2 clips of 160 x 160, four micro-batches, output tensors of 1.6 to 13 MB: 11282 -> 11014
-// us.  Large tensors leave the caches in between: 8 clips of 224 x 224 with every block 6553 -> 6809, up to 30 MB 6594.
-// A block on its own shares one where it is so small that the host's part is what bounds it: fp32 basic block of 64 channels on
-// 16 frames of 14 x 14 131 -> 122 us.
+// next block's kernels.  Us per train step, shared forks for blocks of up to 0, 4, 8, 16, 32 MB of output (runs of one line differ
+// by 0.2 %):
+//   1 clip of 96 x 96 2311 2229 2228 2228 2229    2 of 160 x 160 2819 2776 2757 2757 2756    four micro-batches 11232 11069 10987 10967 10971
+//   4 of 224 x 224 4327 4328 4336 4386 4425       8 of 160 x 160 4397 4395 4396 4448 4464    8 of 224 x 224 6479 6479 6473 6491 6554
+//   fp32: 1 of 96 x 96 3247 3236 3238 3238 3240   2 of 160 x 160 4637 4659 4646 4660 4683    4 of 224 x 224 11055 11076 11051 10983 11017
+// (Large tensors leave the caches in between.)
+// A block on its own has only its last data gradient to run them beside, and shares one where the host's part is what bounds it: fp32
+// with at most 64 channels anywhere and 1 MB of output.  Us per forward and backward pass, a fork for each, one fork (kernels
+// of channels x 3 x 3 on clips of 8 frames, runs differ by 1 to 5 %):
+//   fp32 basic        32, 1 of 7 x 7 121 107     48, 2 of 14 x 14 161 147     64, 2 of 14 x 14 139 130     64, 2 of 20 x 20, 1.6 MB 141 133
+//                     64, 4 of 16 x 16, 2 MB 140 143     80, 1 of 7 x 7 155 163    80, 2 of 14 x 14 180 200    128, 2 of 14 x 14 184 206
+//   fp32 bottleneck   32 channels out, 2 of 14 x 14 175 146     64 177 147     256, 1 of 14 x 14 126 148 or 157 147
+//   bf16              basic 64, 1 of 14 x 14 126 146     bottleneck 256, 2 of 14 x 14 160 194    1024, 1 of 14 x 14 183 216
 static bool few_forks(const BlockPlan& b, bool chain) {
     const ConvP& p = b.st[b.nst - 1].p;
-    return p.rows_out() * p.Cout * (long)dtype_size(b.dtype) <= (chain ? 8L << 20 : 1L << 20);
+    const long bytes = p.rows_out() * p.Cout * (long)dtype_size(b.dtype);
+    if (chain) return bytes <= (8L << 20);
+    for (int i = 0; i < b.nst; ++i)
+        if (b.st[i].p.Cin > 64 || b.st[i].p.Cout > 64) return false;
+    return b.dtype == TSM_F32 && bytes <= (1L << 20);
 }
 
 // lag_slot < 0: the launch stream joins the weight-gradient stream at the end of the block.  lag_slot 0 / 1 (a chain of
