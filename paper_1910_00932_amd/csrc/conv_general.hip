@@ -165,7 +165,7 @@ struct GenRow {
 // D[pixels x channels], one tile per block.
 template <typename T, int BM, int BN, int WM, int WN, bool DGRAD, bool RAG, bool BUF>
 __global__ void __launch_bounds__(256, 2) gen_igemm_kernel(GenArgs a) {
-    static_assert(!BUF || (!RAG && !DGRAD), "whole vectors of one shift group, paddings that are not negative");
+    static_assert(!BUF || (!RAG && !DGRAD), "whole vectors of one shift group, paddings that are not negative");   // (and KT == 1, see gen_launch)
     static_assert(WM * WN == 4, "four wavefronts");
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 32, NJ = TN / 32;
@@ -254,10 +254,10 @@ __global__ void __launch_bounds__(256, 2) gen_igemm_kernel(GenArgs a) {
     auto load = [&]() {
         const bool kvalid = ltap < ntaps;
         if constexpr (BUF) {
-            const int d = kt - a.KT / 2 + (DGRAD ? 0 : grp_dt(ch, a.fold));
+            const int d = grp_dt(ch, a.fold);
             const uint32_t need = (1u << th) | (1u << (8 + tw)) | (d > 0 ? 1u << 30 : 0u) | (d < 0 ? 1u << 31 : 0u);
             const uint32_t va = (uint32_t)(((th * a.Ws + tw) * a.Cs + ch + d * (int)frame) * ES) + bias;
-            const uint32_t vb = (uint32_t)((((kt * a.KH + a.a0h[cls] + th * a.cstep) * a.KW + a.a0w[cls] + tw * a.cstep) * a.CsP + ch) * ES);
+            const uint32_t vb = (uint32_t)(((th * a.KW + tw) * a.CsP + ch) * ES);
 #pragma unroll
             for (int i = 0; i < PA; ++i)
                 areg[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(kvalid && (amask[i] & need) == need ? (uint32_t)((const char*)aptr[i] - (const char*)a.src) + va : OOB), 0, 0);

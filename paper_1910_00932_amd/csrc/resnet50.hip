@@ -548,45 +548,30 @@ __global__ void __launch_bounds__(256) pool_mean_bwd_kernel(const float* __restr
     *(Vec16<T>*)(dfeat + i * V) = o;
 }
 
-// ---- bf16 working copies of all convolution weights, one launch per packing ---------------------
-// Entry l packs params[in_off ..] = fp32 [Cout][Cin][taps] into out + out_off: forward order
-// [Cout][taps][CinP] (channels >= Cin zero) or, with `flip`, the data-gradient order [Cin][flipped taps][Cout].
+// ---- bf16 working copies of all convolution weights in one launch --------------------------------
+// Entry l packs params[in_off ..] = fp32 [Cout][Cin][taps] into out + out_off: forward order [Cout][taps][Cin] or data-gradient
+// order [Cin][flipped taps][Cout].
 struct PackTable {
     int n;
-    unsigned start[56];       // first output element of entry l in the launch's flat index space (start[n] = total)
     unsigned in_off[55];      // element offset into the fp32 parameter vector
     unsigned long long out_off[55];   // bf16 element offset from the output base (the workspace: 64 bits, it exceeds 8 GiB at a few dozen clips)
-    unsigned short cout[55], cin[55], cinp[55], k[55];
-    unsigned tstart[56];      // first 64 x 64 (Cout x Cin) tile of entry l, for pack_tiles_kernel; tiled == 0 if any
-    int tiled;                // entry has a channel count that is not a multiple of 64, padded input channels or a filter other than 1x1 and 3x3
+    unsigned short cout[55], cin[55], k[55];
+    unsigned tstart[56];      // first 64 x 64 (Cout x Cin) tile of entry l
+
+    bool add(size_t in, size_t out, int Cout, int Cin, int K) {
+        if (n >= 55 || Cout % 64 || Cin % 64 || (K != 1 && K != 3)) return false;
+        if (n == 0) tstart[0] = 0;
+        in_off[n] = (unsigned)in;
+        out_off[n] = (unsigned long long)out;
+        cout[n] = (unsigned short)Cout; cin[n] = (unsigned short)Cin; k[n] = (unsigned short)K;
+        tstart[n + 1] = tstart[n] + (unsigned)((Cout / 64) * (Cin / 64));
+        ++n;
+        return true;
+    }
 };
 
-__global__ void __launch_bounds__(256) pack_all_kernel(PackTable t, const float* __restrict__ params,
-                                                       bf16_t* __restrict__ out, int flip) {
-    const unsigned i = blockIdx.x * 256u + threadIdx.x;
-    if (i >= t.start[t.n]) return;
-    int lo = 0, hi = t.n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (t.start[mid] <= i) lo = mid; else hi = mid - 1;
-    }
-    const unsigned e = i - t.start[lo];
-    const int Cout = t.cout[lo], Cin = t.cin[lo], CinP = t.cinp[lo], K = t.k[lo], taps = K * K;
-    const float* w = params + t.in_off[lo];
-    float v = 0.f;
-    if (!flip) {          // e = (co * taps + tap) * CinP + ci
-        const int ci = e % CinP, tap = (e / CinP) % taps, co = e / (CinP * taps);
-        if (ci < Cin) v = w[((size_t)co * Cin + ci) * taps + tap];
-    } else {              // e = (ci * taps + ftap) * Cout + co
-        const int co = e % Cout, ftap = (e / Cout) % taps, ci = e / (Cout * taps);
-        const int kw = K - 1 - ftap % K, kh = K - 1 - ftap / K;
-        v = w[((size_t)co * Cin + ci) * taps + kh * K + kw];
-    }
-    out[(size_t)t.out_off[lo] + e] = f32_to_bf16(v);
-}
-
-// Same packings, both from one read of the fp32 weights, for tables whose channel counts are all multiples of 64 and whose
-// filters are 1x1 or 3x3.  A stream with a transposition in it: a block takes 32 output x 64 input channels with all their
+// Both packings come from one read of the fp32 weights, whose channel counts are all multiples of 64 and whose filters are 1x1 or
+// 3x3.  A stream with a transposition in it: a block takes 32 output x 64 input channels with all their
 // taps, 64 * taps contiguous floats per output channel, reads them as 16-byte vectors, all in flight at once, keeps them
 // in LDS as bf16 in the order they came, and picks the vectors of either packed order out of it (128-byte pieces of the
 // forward order, 64-byte pieces of the data-gradient order).  Blocks of 64 x 64 that went tap by tap, a strided 4-byte load
@@ -650,9 +635,9 @@ __device__ __forceinline__ void pack_tiles(const PackTable& tf, const PackTable&
     else pack_tile<1>(w, of, od, Cout, Cin, co0, ci0, with_dgrad, tile);
 }
 __global__ void __launch_bounds__(256) pack_tiles_kernel(PackTable tf, PackTable td, const float* __restrict__ params,
-                                                         bf16_t* __restrict__ out, int with_dgrad) {
+                                                         bf16_t* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) bf16_t tile[PACK_TILE];
-    pack_tiles(tf, td, params, out, with_dgrad, blockIdx.x, tile);
+    pack_tiles(tf, td, params, out, 1, blockIdx.x, tile);
 }
 
 // ---- inference-mode BatchNorm parameters of the whole network in one launch ---------------------
@@ -876,37 +861,17 @@ static int r50_step(const tsm_r50_desc* d, const void* clips, const int32_t* lab
     // bf16: working copies of the convolution weights in both packings; fp32: the master weights are used directly
     PackTable pk_fwd, pk_dg;
     pk_fwd.n = pk_dg.n = 0;
-    pk_fwd.start[0] = pk_dg.start[0] = 0;
-    pk_fwd.tstart[0] = pk_dg.tstart[0] = 0;
-    pk_fwd.tiled = pk_dg.tiled = 1;
     bf16_t* const pack_base = (bf16_t*)(dry ? nullptr : wsp);   // packed buffers are addressed relative to the workspace
-    auto pack_entry = [&](PackTable& t, const std::string& name, int Cout, int Cin, int k, int CinP, size_t count,
-                          const bf16_t* dst) {
-        const int l = t.n++;
-        t.in_off[l] = (unsigned)table[find_tensor(table, name)].offset;
-        t.out_off[l] = (unsigned long long)(dst - pack_base);
-        t.cout[l] = (unsigned short)Cout; t.cin[l] = (unsigned short)Cin; t.cinp[l] = (unsigned short)CinP;
-        t.k[l] = (unsigned short)k;
-        t.start[l + 1] = t.start[l] + (unsigned)count;
-        t.tstart[l + 1] = t.tstart[l] + (unsigned)((Cout / 64) * (Cin / 64));
-        if (Cout % 64 || Cin % 64 || CinP != Cin || (k != 1 && k != 3)) t.tiled = 0;
-    };
-    auto pack_conv = [&](const std::string& name, int Cout, int Cin, int k, int CinP, const bf16_t** wp,
-                         const bf16_t** wd) -> int {
-        *wp = nullptr;
-        if (wd) *wd = nullptr;
+    auto pack_conv = [&](const std::string& name, int Cout, int Cin, int k, const bf16_t** wp, const bf16_t** wd) -> int {
+        *wp = *wd = nullptr;
         if (!bf) return TSM_OK;
-        if (pk_fwd.n >= 55 || pk_dg.n >= 55) return fail(TSM_ERR_UNSUPPORTED, "%s: too many convolutions", who);
-        const size_t nf = (size_t)Cout * CinP * k * k;
-        bf16_t* a = A.take_n<bf16_t>(nf);
-        pack_entry(pk_fwd, name, Cout, Cin, k, CinP, nf, a);
-        *wp = a;
-        if (wd) {
-            const size_t nd = (size_t)Cout * Cin * k * k;
-            bf16_t* b2 = A.take_n<bf16_t>(nd);
-            pack_entry(pk_dg, name, Cout, Cin, k, Cin, nd, b2);
-            *wd = b2;
-        }
+        const size_t in = (size_t)table[find_tensor(table, name)].offset, n = (size_t)Cout * Cin * k * k;
+        bf16_t* const f = A.take_n<bf16_t>(n);
+        bf16_t* const g = A.take_n<bf16_t>(n);
+        if (!pk_fwd.add(in, (size_t)(f - pack_base), Cout, Cin, k) || !pk_dg.add(in, (size_t)(g - pack_base), Cout, Cin, k))
+            return fail(TSM_ERR_UNSUPPORTED, "%s: %s does not fit the packing", who, name.c_str());
+        *wp = f;
+        *wd = g;
         return TSM_OK;
     };
 
@@ -965,7 +930,7 @@ static int r50_step(const tsm_r50_desc* d, const void* clips, const int32_t* lab
                 const char* bnn[3] = {"bn1", "bn2", "bn3"};
                 for (int i = 0; i < 3; ++i) {
                     StageDef& sd = pl.st[i];
-                    TSM_TRY(pack_conv(pre + cn[i], sd.p.Cout, sd.p.Cin, sd.p.KH, sd.p.Cin, &sd.wp, &sd.wd));
+                    TSM_TRY(pack_conv(pre + cn[i], sd.p.Cout, sd.p.Cin, sd.p.KH, &sd.wp, &sd.wd));
                     sd.w = P(pre + cn[i]);   // fp32 master weights: read by the fp32 kernels only
                     sd.g = P(pre + bnn[i] + ".g"); sd.b = P(pre + bnn[i] + ".b");
                     sd.dw = G(pre + cn[i]); sd.dg = G(pre + bnn[i] + ".g"); sd.db = G(pre + bnn[i] + ".b");
@@ -973,7 +938,7 @@ static int r50_step(const tsm_r50_desc* d, const void* clips, const int32_t* lab
                 }
                 if (pl.proj) {
                     StageDef& sd = pl.ds;
-                    TSM_TRY(pack_conv(pre + "ds.w", sd.p.Cout, sd.p.Cin, 1, sd.p.Cin, &sd.wp, &sd.wd));
+                    TSM_TRY(pack_conv(pre + "ds.w", sd.p.Cout, sd.p.Cin, 1, &sd.wp, &sd.wd));
                     sd.w = P(pre + "ds.w");
                     sd.g = P(pre + "dsbn.g"); sd.b = P(pre + "dsbn.b");
                     sd.dw = G(pre + "ds.w"); sd.dg = G(pre + "dsbn.g"); sd.db = G(pre + "dsbn.b");
@@ -1098,15 +1063,8 @@ static int r50_step(const tsm_r50_desc* d, const void* clips, const int32_t* lab
     RUN(fill_zero(grads, (size_t)nparams * sizeof(float), sp));
     if (dwp_bytes) RUN(fill_zero(dwp_base, dwp_bytes, sp));
     if (bf && !dry) {   // bf16 working copies of all convolution weights in both packings
-        if (pk_fwd.tiled && pk_dg.tiled && pk_fwd.n == pk_dg.n) {
-            pack_tiles_kernel<<<dim3(pk_fwd.tstart[pk_fwd.n] * (64 / PACK_CO)), dim3(256), 0, sp>>>(pk_fwd, pk_dg, params, pack_base, 1);
-            LAUNCH_CHECK("pack_weights");
-        } else {
-            pack_all_kernel<<<dim3(cdiv(pk_fwd.start[pk_fwd.n], 256)), dim3(256), 0, sp>>>(pk_fwd, params, pack_base, 0);
-            LAUNCH_CHECK("pack_weights_fwd");
-            pack_all_kernel<<<dim3(cdiv(pk_dg.start[pk_dg.n], 256)), dim3(256), 0, sp>>>(pk_dg, params, pack_base, 1);
-            LAUNCH_CHECK("pack_weights_dgrad");
-        }
+        pack_tiles_kernel<<<dim3(pk_fwd.tstart[pk_fwd.n] * (64 / PACK_CO)), dim3(256), 0, sp>>>(pk_fwd, pk_dg, params, pack_base);
+        LAUNCH_CHECK("pack_weights");
     }
 
     // ================= forward =================
@@ -1334,25 +1292,14 @@ static int r50_infer(const tsm_r50_desc* d, const void* clips, const float* para
     // ---- forward weights (bf16: packed working copies, one launch)
     PackTable pk;
     pk.n = 0;
-    pk.start[0] = 0;
-    pk.tstart[0] = 0;
-    pk.tiled = 1;
     bf16_t* const pack_base = (bf16_t*)(dry ? nullptr : wsp);
     auto pack_conv = [&](const std::string& name, int Cout, int Cin, int k, const bf16_t** wp) -> int {
         *wp = nullptr;
         if (!bf) return TSM_OK;
-        if (pk.n >= 55) return fail(TSM_ERR_UNSUPPORTED, "%s: too many convolutions", who);
-        const size_t nf = (size_t)Cout * Cin * k * k;
-        bf16_t* a = A.take_n<bf16_t>(nf);
-        const int l = pk.n++;
-        pk.in_off[l] = (unsigned)table[find_tensor(table, name)].offset;
-        pk.out_off[l] = (unsigned long long)(a - pack_base);
-        pk.cout[l] = (unsigned short)Cout; pk.cin[l] = (unsigned short)Cin; pk.cinp[l] = (unsigned short)Cin;
-        pk.k[l] = (unsigned short)k;
-        pk.start[l + 1] = pk.start[l] + (unsigned)nf;
-        pk.tstart[l + 1] = pk.tstart[l] + (unsigned)((Cout / 64) * (Cin / 64));
-        if (Cout % 64 || Cin % 64 || (k != 1 && k != 3)) pk.tiled = 0;
-        *wp = a;
+        bf16_t* const f = A.take_n<bf16_t>((size_t)Cout * Cin * k * k);
+        if (!pk.add((size_t)table[find_tensor(table, name)].offset, (size_t)(f - pack_base), Cout, Cin, k))
+            return fail(TSM_ERR_UNSUPPORTED, "%s: %s does not fit the packing", who, name.c_str());
+        *wp = f;
         return TSM_OK;
     };
 
@@ -1427,7 +1374,7 @@ static int r50_infer(const tsm_r50_desc* d, const void* clips, const float* para
     size_t scratch_need = 0;
 
     // ================= forward =================
-    if (!dry && bf && pk.tiled) {
+    if (!dry && bf) {
         InferFront f;
         f.pk = pk; f.bn = bt;
         f.clips = (const bf16_t*)clips; f.xs = (uint4*)x0; f.S = S; f.Hs = Hs; f.pixels = (long)F * Hs * Hs;
@@ -1441,15 +1388,6 @@ static int r50_infer(const tsm_r50_desc* d, const void* clips, const float* para
     } else if (!dry) {
         bn_eval_params_kernel<<<dim3(cdiv(nch, 256)), dim3(256), 0, s>>>(bt, params, bn_state, d->bn_eps, scale_all, shift_all);
         LAUNCH_CHECK("bn_eval_params");
-        if (bf) {
-            pack_all_kernel<<<dim3(cdiv(pk.start[pk.n], 256)), dim3(256), 0, s>>>(pk, params, pack_base, 0);
-            LAUNCH_CHECK("pack_weights_fwd");
-            const long total = (long)F * Hs * Hs;
-            clips_to_s2d_kernel<<<dim3(cdiv(total, 256)), dim3(256), 0, s>>>((const bf16_t*)clips, (uint4*)x0, S, Hs, total);
-            LAUNCH_CHECK("clips_to_s2d");
-            stem_pack_kernel<<<dim3(64), dim3(256), 0, s>>>(P("conv1.w"), wp0);
-            LAUNCH_CHECK("stem_pack");
-        }
     }
     if (bf) {
         RUN(conv_mfma_fwd(stem, (const bf16_t*)x0, wp0, (bf16_t*)y0, nullptr, nullptr, s));
