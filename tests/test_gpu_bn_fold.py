@@ -1,7 +1,11 @@
 """BatchNorm's sums finished inside the elementwise passes (bn_fold_use: up to 128 partial rows, whole slabs of 128 bytes of
 channels) and, beyond either line, in launches of their own: blocks on both sides against the oracle, at the edges of the pass's
-128-row turns and of its grid, with identity and projection shortcuts, in both storage types."""
+128-row turns and with more rows than its grid takes in one turn, with identity and projection shortcuts, in both storage
+types."""
+import numpy as np
 import pytest
+
+from paper_1910_00932_amd import binding as B
 
 import test_gpu_block as TB
 
@@ -23,7 +27,40 @@ CASES = [
     ("bottleneck", 1, 2, 48, 9, 9, 24, 72, 1, True, 8, "bf16"),    # ragged channels
 ]
 
+# More rows than 512 blocks over all slabs take at 128 each: the loop's later turns, whose rows are loaded before the earlier ones'
+# are stored (in place in the backward pass of a middle stage), the last of them ragged.
+TURNS = [   # block, and the passes that have to be among its kernels
+    # 968 rows of 128 slabs, four blocks each: two turns
+    (("bottleneck", 1, 8, 4096, 11, 11, 32, 4096, 1, False, 8, "f32"), {"bn_fold_relu", "bn_fold_tail", "bn_fold_bwd"}),
+    # two BatchNorms in the tail and in its backward pass
+    (("bottleneck", 1, 8, 64, 11, 11, 32, 4096, 1, True, 8, "f32"), {"bn_fold_relu", "bn_fold_tail", "bn_fold_bwd"}),
+    # (the forward sums have more partial rows)
+    (("bottleneck", 1, 8, 64, 11, 11, 64, 8192, 1, True, 8, "bf16"), {"bn_fold_bwd"}),
+    # middle stages of 7938 rows, 9 slabs, 56 blocks each: two turns, in place backward
+    (("bottleneck", 1, 2, 32, 63, 63, 288, 32, 1, True, 8, "f32"), {"bn_fold_relu", "bn_fold_bwd"}),
+]
+
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
 def test_blocks_on_both_sides_of_the_rule(case):
     TB.run_block(*case, "nthwc")
+
+
+@pytest.mark.parametrize("case,names", TURNS, ids=lambda c: "-".join(str(v) for v in c) if isinstance(c, tuple) else "")
+def test_several_turns_of_the_grid(case, names, monkeypatch):
+    """The values in front of a ReLU are spread around 2 and -2: of millions around zero fp32 takes one or two ReLU decisions other
+    than the oracle, and each moves dx by a few 1e-4."""
+    make_params = TB.make_params
+
+    def far_from_zero(*args, **kw):
+        p = make_params(*args, **kw)
+        for k in p:
+            if k.startswith("b"):
+                p[k] = p[k] + np.where(np.arange(p[k].size) % 4 == 3, -2, 2).astype(np.float32)
+        return p
+
+    monkeypatch.setattr(TB, "make_params", far_from_zero)
+    B.tsm_profile_begin()
+    TB.run_block(*case, "nthwc")
+    ran = B.tsm_profile_end()
+    assert names <= set(ran) and not {"bn_bwd_coeffs", "bn_bwd_apply2"} & set(ran), sorted(ran)
