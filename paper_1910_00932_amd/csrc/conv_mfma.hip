@@ -489,11 +489,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 constexpr bool ring_direct(int BM, int BN, bool stream) { return BN == 128 || BM == 128 || (BN == 64 && !stream); }
 constexpr int ring_stages(int BM, int BN, bool stream) { return ring_direct(BM, BN, stream) ? 3 : 2; }
 constexpr bool ring_alias(int BM, int BN) { return BN == 256 || (BM == 256 && BN == 128); }
+// (the statistics slots too where they have no room of their own: 37632 x 64 -> 256 18.8 us with them there, 18.45 at a fixed place)
+constexpr bool ring_part_alias(int BM, int BN) { return BM == 256 && BN == 128; }
 constexpr size_t ring_smem(int BM, int BN, int WM, int WN, bool stream) {
     const size_t stage = (size_t)(BM + BN) * BK * 2, cst = (size_t)WM * 32 * (BN + 8) * 2;
     const size_t part = (size_t)2 * WM * WN * BN * 4;
     const bool alias = ring_alias(BM, BN);
-    return ring_stages(BM, BN, stream) * stage + (alias ? 0 : cst) + (alias && cst + part <= stage ? 0 : part) + (size_t)2 * BM * sizeof(RowInfo) + (size_t)2 * BM * sizeof(int);
+    return ring_stages(BM, BN, stream) * stage + (alias ? 0 : cst) + (ring_part_alias(BM, BN) ? 0 : part) + (size_t)2 * BM * sizeof(RowInfo) + (size_t)2 * BM * sizeof(int);
 }
 
 // Waits until at most VM of this wavefront's memory operations (loads into LDS among them) and none of its LDS accesses are
@@ -546,8 +548,8 @@ __global__ void __launch_bounds__(WM * WN * 64) igemm_ring_kernel(IgemmArgs a) {
     // the other stages, and the next one to be loaded into it is issued behind the barrier at the top of the next tile,
     // which every wavefront reaches after its last read of the staging tile.
     constexpr bool ALIAS = ring_alias(BM, BN);
-    constexpr bool PART_ALIAS = ALIAS && HM * LDC * 2 + 2 * NSLOT * BN * 4 <= STAGE;   // the statistics slots too
-    static_assert(!ALIAS || HM * LDC * 2 <= STAGE, "the staging tile must fit a stage");
+    constexpr bool PART_ALIAS = ring_part_alias(BM, BN);
+    static_assert(!ALIAS || HM * LDC * 2 + (PART_ALIAS ? 2 * NSLOT * BN * 4 : 0) <= STAGE, "the staging tile must fit a stage");
     static_assert(BN != 256 || !DGRAD, "forward only");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     bf16_t* Cst = (bf16_t*)(smem + NS * STAGE);      // [HM][LDC] staging tile of the epilogue (ALIAS: set per tile)
