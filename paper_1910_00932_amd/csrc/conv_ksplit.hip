@@ -301,7 +301,7 @@ __global__ void __launch_bounds__(KS * 64, MI * NJ == 1 ? 4 : 2) ksplit_kernel(K
             for (int i = 1; i < 2 * MI; i += 2)
 #pragma unroll
                 for (int j = 0; j < 2 * NJ; ++j) sums[i][j] = -sums[i][j];
-            lossy |= !split_finite(sums);
+            lossy |= split_overflow(sums);   // (an instruction per two sums: tiles of one or two chunks per wavefront notice four)
         }
     }
     const int nact = nch < KS ? nch : KS;

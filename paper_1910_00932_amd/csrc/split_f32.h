@@ -89,6 +89,20 @@ __device__ __forceinline__ void mma_split_b(const Split3& a, const Split3 (&b)[N
         for (int r = 0; r < 4; ++r) sum[j][r] = fmaf(t[j][r], sign, sum[j][r]);
 }
 
+// Whether a sum is infinite.  Sees no NaN: that comes with an operand that split3 reports, or of two infinite sums of opposite sign,
+// which callers look for anyway (taps_inside.h).
+template <int M, int N>
+__device__ __forceinline__ bool split_overflow(const split_f32x4 (&sum)[M][N]) {
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) top = fmaxf(top, fabsf(sum[i][j][r]));
+    return top == __builtin_inff();
+}
+
 // Whether all sums are finite numbers.
 template <int M, int N>
 __device__ __forceinline__ bool split_finite(const split_f32x4 (&sum)[M][N]) {
