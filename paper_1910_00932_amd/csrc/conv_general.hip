@@ -456,9 +456,12 @@ __device__ __forceinline__ bool gen_wgrad_block(const GenWgradArgs& a, GenWgradL
     const int wm = wave / WN, wn = wave % WN;
     const int co0 = ((int)blockIdx.y / a.col_tiles) * BCO;
     const int j0 = ((int)blockIdx.y % a.col_tiles) * BCI;
-    const long half = a.chunk / GW_GROUPS;            // (whole steps; a group beyond the last pixel adds zeros)
-    const long mbeg = (long)blockIdx.x * a.chunk + grp * half;
-    long mend = mbeg + half;
+    // steps of each group: the block's pixels, fewer than a chunk in a layer's last block, over the groups (beyond the last pixel
+    // they add zeros)
+    const long left = a.M - (long)blockIdx.x * a.chunk;
+    const int nsteps = (int)(((left < a.chunk ? left : a.chunk) + GW_GROUPS * GPX - 1) / (GW_GROUPS * GPX));
+    const long mbeg = (long)blockIdx.x * a.chunk + (long)grp * nsteps * GPX;
+    long mend = mbeg + (long)nsteps * GPX;
     if (mend > a.M) mend = a.M;
     const int hw = a.Ho * a.Wo;
     const long frame = (long)a.H * a.W * a.Cin;
@@ -612,7 +615,6 @@ __device__ __forceinline__ bool gen_wgrad_block(const GenWgradArgs& a, GenWgradL
         }
     };
 
-    const int nsteps = (int)(half / GPX);
     if (SPLIT && !EXACT && thread == 0) lds.lossy[0] = lds.lossy[1] = 0;
     decode(0);
     if (nsteps > 1) decode(1);
