@@ -872,8 +872,16 @@ int gen_conv_dgrad(const ConvP& p, int dtype, const void* dy, const void* wd, vo
 
 template <typename T, bool RAG>
 static int gen_wgrad_launch(GenWgradArgs& a, hipStream_t s) {
-    const bool big = a.Cout > 64 && a.K > 64;
-    const int bco = big ? 128 : 64, bci = big ? 128 : 64;
+    const long cus = cu_count();
+    // Large tiles are 128 x 128, and 64 x 128 where fp32 is loaded element by element: addresses and operands of the square one do
+    // not fit the registers then.  Those layers take the small tile where it leaves a block fewer than eight steps.  Us with 128 x
+    // 128, 64 x 128, 64 x 64: 3136 pixels 33 -> 65 3x3 51.9, 34.7, 20.6, 12544 130 -> 70 3x3 104, 77.0, 87.9, 25088 127 -> 255 3x3 257,
+    // 218, 282, 392 255 -> 513 1x1 53, 32.1, 18.5; around the line 392 511 -> 257 3x3 (9 steps) 57, 40.6, 42.1, 12544 3 -> 67 7x7 (6
+    // steps) 53, 39.5, 30.5.  (No more than 64 results: 25088 63 -> 61 3x3 62.9 with 64 x 128, 55.7.)
+    constexpr bool TALL = sizeof(T) == 4 && RAG;
+    const long small_tiles = (long)cdiv(a.Cout, 64) * cdiv(a.K, 64);
+    const bool big = a.Cout > 64 && a.K > 64 && (!TALL || small_tiles * a.M >= 8L * GPX * 2 * cus);
+    const int bco = big && !TALL ? 128 : 64, bci = big ? 128 : 64;
     a.col_tiles = cdiv(a.K, bci);
     const long tiles = (long)cdiv(a.Cout, bco) * a.col_tiles;
     // one round of blocks, eight wavefronts per CU, and at least eight steps per block against the atomics of its tile.  Two groups
@@ -881,7 +889,6 @@ static int gen_wgrad_launch(GenWgradArgs& a, hipStream_t s) {
     // 108 and 116), and with the large one in bf16 where they leave no more CUs without one than single groups do (25600 pixels
     // 312 -> 312 3x3, 66 tiles: 140 and 157).  Large fp32 layers run beside data gradients, which find room between small
     // blocks: alone 80 and 71 us (figures above), in the step at 4 clips 10.43 and 10.76 ms.
-    const long cus = cu_count();
     auto splits = [&](long slots) { return std::max(1L, slots / tiles); };
     auto filled = [&](long slots) { const long n = splits(slots) * tiles; return (double)n / (double)((n + slots - 1) / slots * slots); };
     const bool two = big ? sizeof(T) == 2 && filled(cus) >= 0.95 * filled(2 * cus) : a.M <= 8L * GPX * splits(2 * cus);
@@ -890,7 +897,7 @@ static int gen_wgrad_launch(GenWgradArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)((a.M + a.chunk - 1) / a.chunk), (unsigned)tiles), block(two ? 512 : 256);
     if constexpr (sizeof(T) == 2)
         if (big && two) gen_wgrad_kernel<T, 128, 128, 2, 2, 2, RAG><<<grid, block, 0, s>>>(a);
-    if (big && !two) gen_wgrad_kernel<T, 128, 128, 2, 2, 1, RAG><<<grid, block, 0, s>>>(a);
+    if (big && !two) gen_wgrad_kernel<T, TALL ? 64 : 128, 128, 2, 2, 1, RAG><<<grid, block, 0, s>>>(a);
     if (!big && two) gen_wgrad_kernel<T, 64, 64, 2, 2, 2, RAG><<<grid, block, 0, s>>>(a);
     if (!big && !two) gen_wgrad_kernel<T, 64, 64, 2, 2, 1, RAG><<<grid, block, 0, s>>>(a);
     return check_launch(sizeof(T) == 4 ? "gen_wgrad_f32" : "gen_wgrad_bf16");

@@ -46,6 +46,21 @@ def test_general_conv_parity_paper_order(case):
     TC._run(case, "bf16", "ntchw")
 
 
+# fp32 weight gradients that are loaded element by element: 64 x 128 tiles from eight steps per block of small tiles on (131072 pixels
+# times tiles of 64 x 64 on 256 CUs), blocks of few pixels, and last blocks shorter than the others with one and two groups
+@pytest.mark.parametrize("case", [
+    (1, 13, 33, 29, 29, 65, 3, 1, 1, 4),      # 10933 pixels x 12 small tiles: the large one; 65 results, 297 columns
+    (1, 12, 33, 30, 30, 65, 3, 1, 1, 4),      # 10800: the small one
+    (2, 13, 70, 29, 29, 129, 3, 1, 1, 8),     # split shift groups, three row tiles
+    (1, 4, 33, 4, 4, 65, 3, 1, 1, 0),         # 64 pixels, two steps
+    (1, 1, 64, 7, 47, 66, 1, 1, 0, 0),        # 329 pixels: a block of 256 and one of 73
+    (1, 4, 64, 28, 28, 64, 3, 1, 1, 0),       # two groups per block, whole vectors
+    (1, 3, 64, 28, 29, 64, 3, 1, 1, 0),       # 2436 pixels: the last block's groups share 132
+], ids=lambda c: "-".join(map(str, c)))
+def test_weight_gradient_tiles(case):
+    TC._run(case, "f32", "nthwc")
+
+
 SMALL = [  # case, dtype, directions of (fwd, dgrad, wgrad) that run on the plain kernels
     ((1, 1, 4, 1, 1, 4, 1, 1, 0, 0), "f32", (1, 1, 1)),
     ((1, 2, 5, 9, 8, 7, 3, 1, 1, 4), "bf16", (1, 1, 0)),        # 38 and 53 products per sum on average; 72 pixels per thread

@@ -67,8 +67,9 @@ def test_values_whose_first_part_is_infinite():
 
 
 # Operands with bits that three bf16 parts cannot hold (below 2^-110) go through the fp32 instruction, whose sums keep BOUND.  The
-# shapes: every number of wavefronts per tile, whole and ragged chunks, both tiles of the weight gradient, one and two groups.
-TINY_SHAPES = [(2, 5, 7, 32, 32), (8, 14, 14, 64, 128), (8, 33, 31, 40, 72), (32, 28, 28, 128, 64), (16, 56, 56, 64, 192)]
+# shapes: every number of wavefronts per tile, whole and ragged chunks, the weight gradient's tiles, one and two groups.
+TINY_SHAPES = [(2, 5, 7, 32, 32), (8, 14, 14, 64, 128), (8, 33, 31, 40, 72), (32, 28, 28, 128, 64), (16, 56, 56, 64, 192),
+               (33, 33, 31, 67, 67)]
 
 
 @pytest.mark.parametrize("power", [-112, -118, -125])
@@ -123,7 +124,8 @@ def test_results_at_the_top_of_the_range():
 @pytest.mark.parametrize("relu", [False, True])
 @pytest.mark.parametrize("shape,names,bound", [((8, 14, 14, 2048, 64), ("y",), 6e-9), ((8, 14, 14, 64, 2048), ("dx",), 6e-9),
                                                ((2, 14, 14, 2048, 32), ("y",), 2e-8), ((1, 12, 12, 1024, 36), ("y",), 2e-8),
-                                               ((32, 56, 56, 64, 64), ("y", "dx", "dw"), 2.5e-8), ((4, 28, 28, 64, 64), ("dw",), 2.5e-8)])
+                                               ((32, 56, 56, 64, 64), ("y", "dx", "dw"), 2.5e-8), ((4, 28, 28, 64, 64), ("dw",), 2.5e-8),
+                                               ((33, 33, 31, 67, 67), ("dw",), 2.5e-8)])
 def test_sums_do_not_lean(shape, names, bound, relu):
     x, w, dy = _run(*shape, 1.0, 1.0, 1.0)
     out = _layer(x.relu() if relu else x, w, dy)
