@@ -470,9 +470,10 @@ __global__ void __launch_bounds__(256, MINB) igemm_kernel(IgemmArgs a) {
 //    16 * t, so a load can leave it there without a register in between.  The stream of K steps runs across tile
 //    boundaries, so a tile's first steps are on the chip before the previous tile's epilogue starts.
 //  * 128-column tiles and small 64-column results load straight into LDS (three stages: two steps in flight behind the
-//    one at work): what bounds their steps is the LDS, 128 KB of fragment reads and 48 KB of operands per 64 K of a
-//    256 x 128 tile at 128 bytes a clock against 1024 clocks of MFMAs, and the loads' way through registers put its
-//    instructions and waits on top.  Us with registers -> without: 12544 x 2304 -> 256 35.0 -> 31.2
+//    one at work).  No unit bounds their steps: data gradients of a step of 64 clips have the matrix cores busy 33 % of the
+//    clocks and the LDS 19 % (a 16-byte read takes 4 of them), and their wavefronts wait, 36 % of the time for loads and at the
+//    barrier.  The loads' way through registers put its instructions and waits on top (9 % of the time for the LDS to
+//    take an instruction, 2 % without).  Us with registers -> without: 12544 x 2304 -> 256 35.0 -> 31.2
 //    (475 TFLOP/s), 25088 x 2304 -> 256 47.8 -> 42.8, 50176 x 1152 -> 128 30.0 -> 27.9, 25088 x 4608 -> 512 (128 x 128) 58.7 -> 51.7,
 //    200704 x 576 -> 64 45.0 -> 41.6; data gradients 100352 x 2304 -> 256 166 -> 154, stride 2 100352 x 4608 -> 512 169 -> 147.
 //    256-column tiles (two 64 KB stages: one step in flight) and streamed 64-column results keep a step in registers: 100352
