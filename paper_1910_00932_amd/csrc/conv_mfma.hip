@@ -2882,6 +2882,8 @@ static bool pw_shape_ok(const IgemmArgs& a) {
     const long rows = (long)a.F * a.Hd * a.Wd;
     const char* t = getenv("TSM_PW_MIN_ROWS");
     const long min_rows = t ? atol(t) : 32L * 8 * num_cu() / (a.Cd / nb);
+    // (the grid has to fall into streams of Cd / nb blocks: results of three, five, six or seven parts do not on 256 CUs)
+    if (igemm_grid((int)((rows + 255) / 256), a.Cd, 128, 1) % (a.Cd / nb) != 0) return false;
     return rows <= 0x7fffffffL && rows * a.Cs * 2 < 0x7ff00000L && ring_eligible(a.Cs, rows * a.Cs + a.Cs, (long)a.Cd * a.Cs, false) &&
            ring_rows(rows, a.Cd) == 256 && rows >= min_rows;
 }

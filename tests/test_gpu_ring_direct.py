@@ -30,6 +30,11 @@ CASES = [
     (14, 54, 55, 192, 64, 1, "r128x64", "256x128"),      # three
     (12, 56, 56, 64, 64, 3, "r128x64", "r128x64"),       # nine
     (13, 53, 53, 128, 64, 3, "r128x64", "r128x128"),     # eighteen, ragged
+    # short in K and three, five and seven parts wide: not for the short-K kernels, whose blocks fall into streams of one block per part
+    (12, 50, 56, 64, 768, 1, "256x256", "r128x64"),
+    (8, 50, 56, 768, 128, 1, "r128x64", "256x128"),
+    (8, 50, 56, 256, 640, 1, "256x128", "r128x128"),
+    (8, 50, 56, 896, 256, 1, "r128x128", "256x128"),
 ]
 
 
