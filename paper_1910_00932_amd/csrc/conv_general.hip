@@ -877,7 +877,8 @@ static int gen_wgrad_launch(GenWgradArgs& a, hipStream_t s) {
     // not fit the registers then.  Those layers take the small tile where it leaves a block fewer than eight steps.  Us with 128 x
     // 128, 64 x 128, 64 x 64: 3136 pixels 33 -> 65 3x3 51.9, 34.7, 20.6, 12544 130 -> 70 3x3 104, 77.0, 87.9, 25088 127 -> 255 3x3 257,
     // 218, 282, 392 255 -> 513 1x1 53, 32.1, 18.5; around the line 392 511 -> 257 3x3 (9 steps) 57, 40.6, 42.1, 12544 3 -> 67 7x7 (6
-    // steps) 53, 39.5, 30.5.  (No more than 64 results: 25088 63 -> 61 3x3 62.9 with 64 x 128, 55.7.)
+    // steps) 53, 39.5, 30.5.  (No more than 64 results: 25088 63 -> 61 3x3 62.9 with 64 x 128, 55.7.)  The longest pay for the smaller tile's
+    // loads: 4704 1512 -> 426 3x3 1109 with fp32 instructions on 128 x 128, 1228 with 64 x 128, 25088 127 -> 255 221, 219.
     constexpr bool TALL = sizeof(T) == 4 && RAG;
     const long small_tiles = (long)cdiv(a.Cout, 64) * cdiv(a.K, 64);
     const bool big = a.Cout > 64 && a.K > 64 && (!TALL || small_tiles * a.M >= 8L * GPX * 2 * cus);
@@ -887,11 +888,23 @@ static int gen_wgrad_launch(GenWgradArgs& a, hipStream_t s) {
     // one round of blocks, eight wavefronts per CU, and at least eight steps per block against the atomics of its tile.  Two groups
     // per block with the small tile for layers of a few steps (3136 pixels 64 -> 64 3x3 fp32 15.3 and 12.0 us, but 100352 pixels
     // 108 and 116), and with the large one in bf16 where they leave no more CUs without one than single groups do (25600 pixels
-    // 312 -> 312 3x3, 66 tiles: 140 and 157).  Large fp32 layers run beside data gradients, which find room between small
+    // 312 -> 312 3x3, 66 tiles: 140 and 157) and at most 150 steps per block share the atomics' time among them (us with one and with two:
+    // 50176 pixels 72 -> 200 3x3, 37 steps, 66, 57, 200704, 149 steps, 169, 170, 200704 96 -> 520 3x3, 448 steps, 438, 456, 37632 288 -> 1408
+    // 3x3, 588 steps, 585, 614).  Large fp32 layers run beside data gradients, which find room between small
     // blocks: alone 80 and 71 us (figures above), in the step at 4 clips 10.43 and 10.76 ms.
+    // Layers loaded element by element wait for their loads, which eight wavefronts at one barrier do together: beyond four tiles and
+    // ten steps they take two groups only where the tiles that read one stretch of pixels then spread over fewer XCDs (blocks go to the XCDs in
+    // turn, so over 8 / gcd(8, blocks per tile)) and find it in their L2.  Us with one and with two, blocks per tile:  140 -> 140 3x3
+    // 6272 pixels (9 steps) 65, 60, 12544 106, 120, 200704 1475, 1778 (23, 11); 28 -> 430 3x3 12544 70, 66, 50176 233, 248, 200704 852,
+    // 946 (42, 21); 526 -> 238 3x3 50176 1390, 1515 (6, 3); 250 -> 250 3x3 50176 622, 641 (14, 7); but 130 -> 256 3x3 50176 285, 266 (25,
+    // 12), 100 -> 300 3x3 50176 448, 432 (21, 10), 200704 1753, 1692, 36 -> 200 3x3 50176 114, 98 (85, 42); two to four tiles: 20 -> 100 3x3
+    // 200704 172, 158, 70 -> 330 1x1 243, 231, 200 -> 250 1x1 218, 209.
     auto splits = [&](long slots) { return std::max(1L, slots / tiles); };
     auto filled = [&](long slots) { const long n = splits(slots) * tiles; return (double)n / (double)((n + slots - 1) / slots * slots); };
-    const bool two = big ? sizeof(T) == 2 && filled(cus) >= 0.95 * filled(2 * cus) : a.M <= 8L * GPX * splits(2 * cus);
+    auto together = [&](long slots) { const long n = splits(slots); return std::min(8L, n & -n); };
+    const long steps = cdiv(a.M, GPX * splits(2 * cus));
+    const bool beside = RAG ? tiles <= 4 || steps <= 10 || together(cus) > together(2 * cus) : steps <= 150;
+    const bool two = big ? sizeof(T) == 2 && beside && filled(cus) >= 0.95 * filled(2 * cus) : a.M <= 8L * GPX * splits(2 * cus);
     const long want = splits(two ? cus : 2 * cus), unit = two ? 2L * GPX : (long)GPX;
     a.chunk = (std::max((a.M + want - 1) / want, 8L * GPX) + unit - 1) / unit * unit;
     const dim3 grid((unsigned)((a.M + a.chunk - 1) / a.chunk), (unsigned)tiles), block(two ? 512 : 256);

@@ -116,6 +116,25 @@ def test_weight_gradient_of_ragged_bf16_layers_on_both_sides_of_the_line(case, k
     assert {k for k in classes if "wgrad" in k and not k.startswith("unpack")} == {kernel}, sorted(classes)
 
 
+@pytest.mark.parametrize("frames,cin,cout", [(8, 140, 140), (16, 140, 140), (16, 28, 430), (32, 28, 430), (16, 100, 300), (33, 20, 100)])
+def test_weight_gradient_of_large_ragged_bf16_layers_in_one_and_two_groups(frames, cin, cout):
+    """Few and many steps per block, few and many tiles, odd and even numbers of blocks per tile, against fp64 (exact products, fp32 sums of up to 25088 of random
+    sign: a few 1e-7 of the tensor; bound 1e-5)."""
+    g = torch.Generator(device="cuda").manual_seed(frames)
+    x = torch.randn(frames, 28, 28, cin, generator=g, device="cuda").bfloat16()
+    dy = torch.randn(frames, 28, 28, cout, generator=g, device="cuda").bfloat16()
+    d = B.ConvDesc(N=1, T=frames, Cin=cin, H=28, W=28, Cout=cout, kh=3, kw=3, stride=1, pad=1, fold_div=0, dtype=B.TSM_BF16, layout=B.TSM_NTHWC)
+    ws = torch.empty(max(16, B.tsm_conv_workspace_bytes(d)), dtype=torch.uint8, device="cuda")
+    dw = torch.empty(cout, cin, 3, 3, device="cuda")
+    B.tsm_conv_wgrad(d, x, dy, dw, 0, ws)
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    dyt = dy.double().reshape(-1, cout).t().contiguous()
+    for i in range(3):
+        for j in range(3):
+            ref = dyt @ xp[:, i:i + 28, j:j + 28].reshape(-1, cin)
+            assert float((dw[:, :, i, j].double() - ref).norm() / ref.norm()) < 1e-5, (i, j)
+
+
 def test_noalloc_forward_whose_packed_weights_do_not_fit_the_fixed_scratch():
     """1024 x 512 x 3x3 fp32 weights are 18.9 MB packed, the built-in scratch is 16 MiB: the plain kernel runs."""
     N, T, Cin, H, Cout, k = 1, 2, 1024, 3, 512, 3
