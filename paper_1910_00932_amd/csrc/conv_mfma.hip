@@ -480,7 +480,10 @@ __global__ void __launch_bounds__(256, MINB) igemm_kernel(IgemmArgs a) {
 //    x 1024 -> 256 66 with, 73 without; 1605632 x 256 -> 64 191, 203.  Four wavefronts of 128 x 64 instead of eight of 64 x 64,
 //    a quarter less to read from LDS, wait on themselves: 25088 x 2304 -> 256 50.0.  A fourth stage, for which the 128 x 64 tile has
 //    room, makes three steps of every tile's fewer: 37632 x 64 -> 64 12.9 with three, 13.7 with four (registers 13.1), its data
-//    gradient 12.4, 13.2 (12.4), 37632 x 576 -> 64 20.9 any way, data gradient 19.3, 19.4 (20.3).
+//    gradient 12.4, 13.2 (12.4), 37632 x 576 -> 64 20.9 any way, data gradient 19.3, 19.4 (20.3).  Large forward 1x1 layers of 128 to 448
+//    channels with 64 results lose by it, their data gradients and all others gain (us straight, through registers: 401408 x
+//    128 51.4, 47.3, data gradient 47.6, 47.7; 401408 x 256 59.4, 57.8; 100352 x 256 23.5, 23.1, data gradient 22.2, 23.1; 100352 x 512 29.5,
+//    30.4; 100352 x 2304 63.4, 67.0, data gradient 59.3, 67.0).
 static constexpr uint32_t OOB_OFFSET = 0x80000000u;   // buffers are smaller than 2 GiB
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
